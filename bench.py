@@ -63,9 +63,9 @@ COUNTER_SOURCES = {
 
 
 # the kernels of one PageRank iteration: the pull (iteration kernel plus the
-# sum of cut lists) or propagation blocking (two binning levels and the
-# accumulation)
-PR_KERNELS = ["pr_iter_kernel", "pr_segmented_kernel", "pb_bin1_kernel", "pb_bin2_kernel", "pb_accum_kernel"]
+# sum of cut lists) or propagation blocking (contributions sent to their
+# places, sums, and the sums of bins shared by several workgroups)
+PR_KERNELS = ["pr_iter_kernel", "pr_segmented_kernel", "pb_send_kernel", "pb_sum_kernel", "pb_finish_kernel"]
 
 
 # counter passes of a counter summary: each runs the same counter-run
@@ -119,15 +119,9 @@ def measured_counters(key: str, workload: str, layout: str, phase: str):
 
 
 def _kernel_key(name: str) -> str:
-    """Base name of a kernel in a trace ("void lg::pb_bin1_kernel<lg::PlainAcc<
-    false>, true>(...)" -> "pb_bin1_kernel[count]" for the counting instance)."""
-    base = name.split("(")[0]
-    tmpl = base[base.find("<"):] if "<" in base else ""
-    base = base.split("<")[0].replace("void ", "").strip()
-    base = base.split("::")[-1]
-    if base == "pb_bin1_kernel" and tmpl.rstrip(">").rstrip().endswith("true"):
-        base += "[count]"
-    return base
+    """Base name of a kernel in a trace ("void lg::pb_sum_kernel<14u, 1024u>(
+    ...)" -> "pb_sum_kernel")."""
+    return name.split("(")[0].split("<")[0].replace("void ", "").strip().split("::")[-1]
 
 
 def counter_summary_main(args):
@@ -621,12 +615,12 @@ def main():
             "bytes_per_edge_algorithmic": round(k["bytes_per_edge_algorithmic"], 4)}
         if rooflines[layout]["traffic"]:
             rooflines[layout]["bytes_per_edge_measured"] = round(rooflines[layout]["traffic"] / M, 4)
-        if "pb_bin1_kernel" in k["kernels"]:
-            # propagation blocking streams more than the algorithmic bytes by
-            # design: level 1 reads the structure and the contributions and
-            # writes 8 B per entry, level 2 reads 8 B and writes 6 B per entry,
-            # the accumulation reads 6 B per entry and writes 4 B per vertex
-            design = s["structure_bytes"] + 4.0 * n + 28.0 * M + 4.0 * n
+        if "pb_send_kernel" in k["kernels"]:
+            # propagation blocking streams, by design, 2 B of source numbers
+            # read and 4 B of contributions written per entry, then those 4 B
+            # and 2 B of destination numbers read back, and per vertex the
+            # contribution and the degree read and the contribution written
+            design = 12.0 * M + 12.0 * n
             rooflines[layout]["design_bytes_per_launch"] = design
             rooflines[layout]["design_frac"] = round(design / (k["avg_launch_ms"] / 1000.0) / 1e9 / HBM_PEAK_GBS, 4)
         tb = measured_counters("traffic_bytes_per_phase", args.workload, layout, "bfs")

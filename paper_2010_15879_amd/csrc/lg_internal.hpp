@@ -363,13 +363,13 @@ lg_status bfs_run(lg_graph *g, BfsWork &w, const uint32_t *roots, uint32_t r, in
 lg_status decode_run(lg_graph *g, DecodeWork &w, const uint32_t *vertices, uint32_t k, uint64_t *out_off,
                      uint32_t *out_ids, uint64_t cap, uint32_t flags, hipStream_t stream, uint64_t *total);
 lg_status pr_free(lg_graph *g);
-// PageRank by propagation blocking: the graphs it serves, its driver, its
+// PageRank by propagation blocking: the calls it serves, its driver, its
 // workspace (lg_pagerank_pb.hip)
-bool pb_applies(const lg_graph *g);
+bool pb_applies(const lg_graph *g, uint32_t iters);
 lg_status pagerank_pb(lg_graph *g, float damping, uint32_t iters, float *scores, hipStream_t s);
 uint64_t pb_bytes(const lg_graph *g);
 void pb_free(lg_graph *g);
-void pb_trim();  // frees the bin buffers parked for the next graph
+void pb_trim();  // frees the entry buffers parked for the next graph
 lg_status sssp_free(lg_graph *g);
 uint64_t sssp_bytes(const lg_graph *g);
 
