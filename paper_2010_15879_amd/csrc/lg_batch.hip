@@ -4,13 +4,17 @@
 // Every workgroup is a worker: it takes the next job (graph, root) from a
 // device counter, runs that BFS to the end itself (level-synchronous, with
 // workgroup barriers between levels), and takes the next job until none is
-// left -- so the exit condition is reached by every workgroup.  A level is
-// taken `chunk` frontier vertices at a time: a vertex of degree below
-// `wave_threshold` is expanded by one thread, a larger one by a whole wave
-// (lanes over its list, coalesced).  Both knobs are picked per plan by
-// timing candidate settings on the actual batch.  Visiting is the BFS rule
-// of the single-query path (CAS on depth, smallest-label parent by
-// atomicMin), so every result equals the per-query result bit for bit.
+// left -- so the exit condition is reached by every workgroup.  A vertex of
+// degree below `wave_threshold` is handled by one thread, a larger one by a
+// whole wave (lanes over its list, coalesced); top-down levels stage `chunk`
+// frontier vertices at a time.  The knobs are picked per plan by timing
+// candidate settings on the actual batch.  The rule is that of the
+// single-query path (the parent is the smallest label one level up), so
+// every result equals the per-query result bit for bit.
+//
+// Two kernels: bfs_batch_kernel keeps a search's bitmaps in LDS and changes
+// direction like the single-query path; bfs_batch_large_kernel, for plans
+// with a graph whose bitmaps do not fit, goes top-down over depths in memory.
 //
 // A plan captures "reset the job counter + the persistent launch" in a HIP
 // graph, replayed by lg_bfs_batch_run.
@@ -31,6 +35,7 @@ template <class Acc>
 struct BatchGraph {
     Acc acc;
     uint32_t n;
+    uint64_t m;
 };
 
 struct BatchJob {
@@ -53,7 +58,7 @@ __device__ __forceinline__ void batch_visit(uint32_t u, uint32_t v, int32_t nd, 
 }
 
 template <class Acc, int kThreads>
-__global__ __launch_bounds__(kThreads) void bfs_batch_kernel(
+__global__ __launch_bounds__(kThreads) void bfs_batch_large_kernel(
     const BatchGraph<Acc> *__restrict__ graphs, const BatchJob *__restrict__ jobs, uint32_t num_jobs,
     uint32_t *__restrict__ job_counter, int32_t *__restrict__ depth, int32_t *__restrict__ parent,
     int32_t max_depth, uint32_t *__restrict__ queues, uint64_t qcap, uint32_t chunk, uint32_t wave_threshold) {
@@ -203,6 +208,330 @@ __global__ __launch_bounds__(kThreads) void bfs_batch_kernel(
     }
 }
 
+// ---------------------------------------------------------------------------
+// searches with their bitmaps in LDS, direction-optimizing
+// ---------------------------------------------------------------------------
+
+// A graph's three bitmaps (visited, frontier, next) in LDS, at most: one
+// workgroup per compute unit, which is still 14 times faster at 2^18 vertices
+// (96 KB).  Above it (349,525 vertices) the large kernel.
+constexpr uint64_t kBatchLdsBytes = 128u << 10;
+inline uint64_t batch_bitmap_bytes(uint64_t n) { return (n + 63) / 64 * 8 * 3; }
+
+// Direction of a level: bottom-up when the frontier's entries exceed the
+// unexplored ones / 14, back when the frontier falls below n / 24 (the
+// customary constants of direction-optimizing BFS).
+constexpr uint64_t kBatchAlpha = 14, kBatchBeta = 24;
+
+struct BatchBits {
+    uint32_t *vis, *fr, *nx;
+    __device__ __forceinline__ bool in(const uint32_t *b, uint32_t u) const { return b[u >> 5] >> (u & 31) & 1u; }
+    __device__ __forceinline__ bool mark(uint32_t u) const {  // first to mark it?
+        const uint32_t bit = 1u << (u & 31);
+        return !(atomicOr(&nx[u >> 5], bit) & bit);
+    }
+};
+
+// top-down: an edge v -> u; every claimant of the level lowers the parent
+__device__ __forceinline__ void batch_claim(const BatchBits &B, uint32_t u, uint32_t v, int32_t nd,
+                                            int32_t *__restrict__ D, uint32_t *__restrict__ P,
+                                            uint32_t *__restrict__ qnext, uint32_t *s_tail) {
+    if (B.in(B.vis, u)) return;
+    if (P) atomicMin(&P[u], v);
+    if (B.mark(u)) {
+        D[u] = nd;
+        qnext[atomicAdd(s_tail, 1u)] = u;
+    }
+}
+
+// fn(label) over the list of one vertex by one lane, in order, until it
+// returns false
+template <class Acc, class Fn>
+__device__ __forceinline__ void batch_lane_list(const Acc &acc, uint32_t n, const GapInfo &gi, Fn &&fn) {
+    uint32_t val = 0;
+    for (uint32_t e = 0; e < gi.deg; ++e) {
+        val += acc.get(Acc::entry_bit(gi, e), e ? gi.g : gi.w);
+        if (!fn(val < n ? val : n - 1)) return;
+    }
+}
+template <class Acc, class Fn>
+__device__ __forceinline__ void batch_lane_list(const Acc &acc, uint32_t n, const ulonglong2 &range, Fn &&fn) {
+    // bytes from 8-byte windows
+    uint32_t label = 0, accv = 0, shift = 0, count = 0;
+    for (uint64_t pos = range.x; pos < range.y;) {
+        const uint64_t k = pos >> 3;
+        const uint32_t sh = (uint32_t)(pos & 7) * 8;
+        const uint64_t w0 = acc.word(k * 8), w1 = acc.word(k * 8 + 8);
+        const uint64_t win = sh ? (w0 >> sh) | (w1 << (64 - sh)) : w0;
+        const uint32_t avail = range.y - pos < 8 ? (uint32_t)(range.y - pos) : 8u;
+        for (uint32_t j = 0; j < avail; ++j) {
+            const uint32_t b = (uint32_t)(win >> (8 * j)) & 255u;
+            accv |= (b & 127u) << shift;
+            shift += 7;
+            if (!(b & 128u)) {
+                label = Acc::kDifferences && count ? label + accv : accv;
+                ++count;
+                accv = 0;
+                shift = 0;
+                if (!fn(label < n ? label : n - 1)) return;
+            }
+        }
+        pos += avail;
+    }
+}
+template <class Acc, class Fn>
+__device__ __forceinline__ void batch_lane_list(const Acc &acc, uint32_t, const VInfo &vi, Fn &&fn) {
+    const uint32_t st = Acc::step(vi.w), mk = Acc::mask(vi.w);
+    // four independent loads at a time (clamped), then in order
+    for (uint32_t e = 0; e < vi.deg; e += 4) {
+        uint32_t x[4];
+#pragma unroll
+        for (uint32_t j = 0; j < 4; ++j)
+            x[j] = acc.get(vi.start + (uint64_t)(e + j < vi.deg ? e + j : vi.deg - 1) * st, mk);
+#pragma unroll
+        for (uint32_t j = 0; j < 4; ++j)
+            if (e + j < vi.deg && !fn(x[j])) return;
+    }
+}
+
+// fn(valid, label) over the list of one vertex by a wave, 64 entries (or
+// bytes) per step, until it returns false (fn must return the same in every
+// lane)
+template <class Acc, class Fn>
+__device__ __forceinline__ void batch_wave_list(const Acc &acc, uint32_t n, const GapInfo &gi, Fn &&fn) {
+    const uint32_t lane = lane_id();
+    uint32_t carry = 0;
+    for (uint64_t e0 = 0; e0 < gi.deg; e0 += kWave) {
+        const uint64_t e = e0 + lane;
+        const bool valid = e < gi.deg;
+        const uint32_t x = valid ? acc.get(Acc::entry_bit(gi, e), e ? gi.g : gi.w) : 0u;
+        const uint32_t val = wave_incl_scan(x) + carry;
+        carry = __shfl(val, kWave - 1, kWave);
+        if (!fn(valid, val < n ? val : n - 1)) return;
+    }
+}
+template <class Acc, class Fn>
+__device__ __forceinline__ void batch_wave_list(const Acc &acc, uint32_t n, const ulonglong2 &range, Fn &&fn) {
+    uint32_t prevb = 0, carry = 0;
+    for (uint64_t p0 = range.x; p0 < range.y; p0 += kWave) {
+        uint32_t x;
+        const bool end = varint_step(acc, p0, range.y, prevb, x);
+        uint32_t label = x;
+        if constexpr (Acc::kDifferences) {
+            const uint32_t sc = wave_incl_scan(end ? x : 0u);
+            label = carry + sc;
+            carry += __shfl(sc, kWave - 1, kWave);
+        }
+        if (!fn(end, label < n ? label : n - 1)) return;
+    }
+}
+template <class Acc, class Fn>
+__device__ __forceinline__ void batch_wave_list(const Acc &acc, uint32_t, const VInfo &vi, Fn &&fn) {
+    const uint32_t lane = lane_id();
+    const uint32_t st = Acc::step(vi.w), mk = Acc::mask(vi.w);
+    for (uint32_t e0 = 0; e0 < vi.deg; e0 += kWave) {
+        const uint32_t e = e0 + lane;
+        const bool valid = e < vi.deg;
+        const uint32_t x = acc.get(vi.start + (uint64_t)(valid ? e : 0u) * st, mk);
+        if (!fn(valid, x)) return;
+    }
+}
+
+// a list's place and its length (Varint: its bytes)
+template <class Acc>
+__device__ __forceinline__ auto batch_list(const Acc &acc, uint32_t v) {
+    if constexpr (IsVarintAcc<Acc>::value) {
+        uint64_t b0, b1;
+        acc.offsets(v, b0, b1);
+        return make_ulonglong2(b0, b1);
+    } else {
+        return acc.info(v);
+    }
+}
+__device__ __forceinline__ uint32_t batch_len(const GapInfo &i) { return i.deg; }
+__device__ __forceinline__ uint32_t batch_len(const VInfo &i) { return i.deg; }
+__device__ __forceinline__ uint32_t batch_len(const ulonglong2 &i) { return (uint32_t)(i.y - i.x); }
+
+// One search per workgroup at a time.  What bounds it is latency: a search
+// reads its lists level by level, each vertex a chain offset -> list -> LDS
+// bit, so the bitmaps sit in LDS (a random probe there costs no memory
+// access), four list loads are in flight per lane, and bottom-up levels read
+// a list only to its first frontier neighbour, with no atomics.  1,024
+// searches over 64 Kronecker graphs of 2^12 to 2^16 vertices: 24.1 ms
+// top-down over depths in memory, 1.2 ms; 256 over 16 graphs of 2^14 to 2^18:
+// 50.0 and 3.5 ms.
+template <class Acc, int kThreads>
+__global__ __launch_bounds__(kThreads) void bfs_batch_kernel(
+    const BatchGraph<Acc> *__restrict__ graphs, const BatchJob *__restrict__ jobs, uint32_t num_jobs,
+    uint32_t *__restrict__ job_counter, int32_t *__restrict__ depth, int32_t *__restrict__ parent,
+    int32_t max_depth, uint32_t *__restrict__ queues, uint64_t qcap, uint32_t chunk, uint32_t wave_threshold) {
+    extern __shared__ uint32_t s_bits[];
+    __shared__ uint32_t s_job, s_tail, s_nheavy;
+    __shared__ unsigned long long s_edges;
+    __shared__ uint32_t s_heavy[kMaxChunk];
+    const uint32_t tid = threadIdx.x;
+    const uint32_t lane = lane_id();
+    const uint32_t wv = tid / kWave;
+    constexpr uint32_t kWaves = kThreads / kWave;
+    uint32_t *qa = queues + (uint64_t)blockIdx.x * 2 * qcap;
+    uint32_t *qb = qa + qcap;
+    for (;;) {
+        if (tid == 0) s_job = atomicAdd(job_counter, 1u);
+        __syncthreads();
+        const uint32_t job = s_job;
+        if (job >= num_jobs) break;
+        const BatchJob jb = jobs[job];
+        const BatchGraph<Acc> G = graphs[jb.graph];
+        const uint32_t n = G.n, words = (n + 63) / 64 * 2;
+        const BatchBits B{s_bits, s_bits + words, s_bits + 2 * words};
+        int32_t *D = depth + jb.out_offset;
+        uint32_t *P = parent ? reinterpret_cast<uint32_t *>(parent + jb.out_offset) : nullptr;
+        for (uint32_t i = tid; i < 3 * words; i += kThreads) s_bits[i] = 0;
+        if (P)
+            for (uint32_t v = tid; v < n; v += kThreads) P[v] = v == jb.root ? jb.root : 0xFFFFFFFFu;
+        __syncthreads();
+        if (tid == 0) {
+            qa[0] = jb.root;
+            D[jb.root] = 0;
+            B.vis[jb.root >> 5] = B.fr[jb.root >> 5] = 1u << (jb.root & 31);
+            s_edges = 0;
+        }
+        __syncthreads();
+        uint32_t *qin = qa, *qout = qb;
+        uint32_t F = 1;                  // frontier vertices (the same in every thread, as all below)
+        uint64_t unexplored = G.m;       // entries of the lists not on a frontier yet (Varint: bytes count for entries)
+        bool bottom = false;
+        for (int32_t level = 0; F && !(max_depth >= 0 && level >= max_depth); ++level) {
+            const int32_t nd = level + 1;
+            // the frontier's entries: summed here for a queue, by the level before for a bitmap
+            if (!bottom) {
+                unsigned long long mine = 0;
+                for (uint32_t i = tid; i < F; i += kThreads) mine += batch_len(batch_list(G.acc, qin[i]));
+                mine = wave_sum(mine);
+                if (lane == 0 && mine) atomicAdd(&s_edges, mine);
+                __syncthreads();
+            }
+            const uint64_t edges = s_edges;
+            if (!bottom) bottom = edges > unexplored / kBatchAlpha;
+            else if (F < n / kBatchBeta) {
+                bottom = false;
+                if (tid == 0) s_tail = 0;
+                __syncthreads();
+                for (uint32_t w = tid; w < words; w += kThreads) {
+                    uint32_t x = B.fr[w];
+                    uint32_t at = x ? atomicAdd(&s_tail, (uint32_t)__popc(x)) : 0u;
+                    for (; x; x &= x - 1) qin[at++] = w * 32 + (uint32_t)__ffs((int)x) - 1;
+                }
+            }
+            unexplored = unexplored > edges ? unexplored - edges : 0;
+            __syncthreads();  // s_edges read, the queue written
+            if (tid == 0) {
+                s_tail = 0;
+                s_nheavy = 0;
+                s_edges = 0;
+            }
+            __syncthreads();
+            if (bottom) {
+                // a lane per unvisited vertex; the first frontier neighbour in its
+                // list is the smallest.  Long lists wait for a wave.
+                uint32_t found = 0;
+                unsigned long long sum = 0;
+                for (uint32_t v0 = wv * kWave; v0 < n; v0 += kWaves * kWave) {
+                    const uint32_t v = v0 + lane;
+                    const bool open = v < n && !B.in(B.vis, v);
+                    if (!__ballot(open)) continue;
+                    auto li = [&]() {
+                        if constexpr (IsGapAcc<Acc>::value || IsVarintAcc<Acc>::value)
+                            return batch_list(G.acc, v < n ? v : n - 1);
+                        else
+                            return wave_info(G.acc, v0, n);
+                    }();
+                    if (!open) continue;
+                    const uint32_t len = batch_len(li);
+                    if (len >= wave_threshold) {
+                        qout[atomicAdd(&s_nheavy, 1u)] = v;
+                        continue;
+                    }
+                    batch_lane_list(G.acc, n, li, [&](uint32_t u) {
+                        if (!B.in(B.fr, u)) return true;
+                        B.mark(v);
+                        D[v] = nd;
+                        if (P) P[v] = u;
+                        ++found;
+                        sum += len;
+                        return false;
+                    });
+                }
+                __syncthreads();
+                const uint32_t nh = s_nheavy;
+                for (uint32_t h = wv; h < nh; h += kWaves) {
+                    const uint32_t v = __builtin_amdgcn_readfirstlane(qout[h]);
+                    const auto li = batch_list(G.acc, v);
+                    batch_wave_list(G.acc, n, li, [&](bool valid, uint32_t u) {
+                        const uint64_t hit = __ballot(valid && B.in(B.fr, u));
+                        if (!hit) return true;
+                        if (lane == (uint32_t)__ffsll((long long)hit) - 1) {
+                            B.mark(v);
+                            D[v] = nd;
+                            if (P) P[v] = u;
+                            ++found;
+                            sum += batch_len(li);
+                        }
+                        return false;
+                    });
+                }
+                found = wave_sum(found);
+                sum = wave_sum(sum);
+                if (lane == 0 && found) {
+                    atomicAdd(&s_tail, found);
+                    atomicAdd(&s_edges, sum);
+                }
+            } else {
+                for (uint32_t c0 = 0; c0 < F; c0 += chunk) {
+                    const uint32_t c1 = c0 + chunk < F ? c0 + chunk : F;
+                    for (uint32_t i = c0 + tid; i < c1; i += kThreads) {
+                        const uint32_t v = qin[i];
+                        const auto li = batch_list(G.acc, v);
+                        if (batch_len(li) >= wave_threshold) {
+                            s_heavy[atomicAdd(&s_nheavy, 1u)] = v;
+                        } else {
+                            batch_lane_list(G.acc, n, li, [&](uint32_t u) {
+                                batch_claim(B, u, v, nd, D, P, qout, &s_tail);
+                                return true;
+                            });
+                        }
+                    }
+                    __syncthreads();
+                    const uint32_t nh = s_nheavy;
+                    for (uint32_t h = wv; h < nh; h += kWaves) {
+                        const uint32_t v = __builtin_amdgcn_readfirstlane(s_heavy[h]);
+                        batch_wave_list(G.acc, n, batch_list(G.acc, v), [&](bool valid, uint32_t u) {
+                            if (valid) batch_claim(B, u, v, nd, D, P, qout, &s_tail);
+                            return true;
+                        });
+                    }
+                    __syncthreads();
+                    if (tid == 0) s_nheavy = 0;
+                    __syncthreads();
+                }
+                uint32_t *t = qin; qin = qout; qout = t;
+            }
+            __syncthreads();
+            F = s_tail;
+            for (uint32_t w = tid; w < words; w += kThreads) {
+                const uint32_t x = B.nx[w];
+                B.vis[w] |= x;
+                B.fr[w] = x;
+                B.nx[w] = 0;
+            }
+            __syncthreads();
+        }
+        for (uint32_t v = tid; v < n; v += kThreads)
+            if (!B.in(B.vis, v)) D[v] = -1;
+        __syncthreads();  // s_job and the bitmaps are rewritten next
+    }
+}
+
 __global__ void batch_reset_kernel(uint32_t *__restrict__ counter) {
     if (threadIdx.x == 0 && blockIdx.x == 0) *counter = 0;
 }
@@ -221,6 +550,7 @@ struct lg_batch_plan {
     int32_t *depth = nullptr, *parent = nullptr;
     int32_t max_depth = -1;
     uint32_t threads = 256, chunk = 256, wave_threshold = 32, workgroups = 0;
+    uint64_t lds = 0;  // bytes of the largest graph's bitmaps; 0: the large kernel
     double tuned_ms = 0.0;
     uint32_t candidates = 0;
     lg::DevBuf graphs, jobs, counter, queues;
@@ -232,30 +562,38 @@ struct lg_batch_plan {
 
 namespace lg {
 
+// fn(kernel) with the kernel of the plan's settings
+template <class Acc, class Fn>
+static lg_status batch_kernel(const lg_batch_plan *p, Fn &&fn) {
+    if (!p->lds) return p->threads == 256 ? fn(bfs_batch_large_kernel<Acc, 256>) : fn(bfs_batch_large_kernel<Acc, 512>);
+    if (p->threads == 256) return fn(bfs_batch_kernel<Acc, 256>);
+    if (p->threads == 512) return fn(bfs_batch_kernel<Acc, 512>);
+    return fn(bfs_batch_kernel<Acc, 1024>);
+}
+
 template <class Acc>
 static lg_status batch_launch(lg_batch_plan *p, hipStream_t s) {
     LG_LAUNCH(batch_reset_kernel, 1, 64, 0, s, p->counter.as<uint32_t>());
     LG_CHECK_LAUNCH();
     const auto *G = p->graphs.as<const BatchGraph<Acc>>();
     const auto *J = p->jobs.as<const BatchJob>();
-    if (p->threads == 256)
-        LG_LAUNCH((bfs_batch_kernel<Acc, 256>), p->workgroups, 256, 0, s, G, J, p->num_jobs, p->counter.as<uint32_t>(),
-                  p->depth, p->parent, p->max_depth, p->queues.as<uint32_t>(), p->qcap, p->chunk, p->wave_threshold);
-    else
-        LG_LAUNCH((bfs_batch_kernel<Acc, 512>), p->workgroups, 512, 0, s, G, J, p->num_jobs, p->counter.as<uint32_t>(),
-                  p->depth, p->parent, p->max_depth, p->queues.as<uint32_t>(), p->qcap, p->chunk, p->wave_threshold);
-    LG_CHECK_LAUNCH();
-    return LG_OK;
+    return batch_kernel<Acc>(p, [&](auto bfs_batch_kernel) -> lg_status {
+        LG_LAUNCH(bfs_batch_kernel, p->workgroups, p->threads, (uint32_t)p->lds, s, G, J, p->num_jobs,
+                  p->counter.as<uint32_t>(), p->depth, p->parent, p->max_depth, p->queues.as<uint32_t>(), p->qcap,
+                  p->chunk, p->wave_threshold);
+        LG_CHECK_LAUNCH();
+        return LG_OK;
+    });
 }
 
 template <class Acc>
 static lg_status batch_workgroups(lg_batch_plan *p, uint32_t &wg) {
     int cus = 0, per = 0;
     LG_CHECK_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, p->device));
-    if (p->threads == 256)
-        LG_CHECK_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, bfs_batch_kernel<Acc, 256>, 256, 0));
-    else
-        LG_CHECK_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, bfs_batch_kernel<Acc, 512>, 512, 0));
+    LG_TRY(batch_kernel<Acc>(p, [&](auto kernel) -> lg_status {
+        LG_CHECK_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kernel, (int)p->threads, (size_t)p->lds));
+        return LG_OK;
+    }));
     if (per < 1) per = 1;
     wg = (uint32_t)std::min<uint64_t>((uint64_t)cus * per, p->num_jobs ? p->num_jobs : 1);
     return LG_OK;
@@ -275,6 +613,7 @@ static lg_status batch_build(lg_batch_plan *p, const lg_graph *const *gs, bool a
         else if constexpr (Acc::kPacked) hg[i].acc = Acc{g->packed_view()};
         else hg[i].acc = Acc{g->plain_view()};
         hg[i].n = g->n;
+        hg[i].m = IsVarintAcc<Acc>::value ? g->U / 8 : g->m;
     }
     LG_TRY(p->graphs.alloc(sizeof(BatchGraph<Acc>) * hg.size()));
     LG_CHECK_HIP(hipMemcpy(p->graphs.p, hg.data(), sizeof(BatchGraph<Acc>) * hg.size(), hipMemcpyHostToDevice));
@@ -282,9 +621,14 @@ static lg_status batch_build(lg_batch_plan *p, const lg_graph *const *gs, bool a
     struct Cfg { uint32_t threads, chunk, wt; };
     std::vector<Cfg> cands;
     if (autotune) {
-        for (uint32_t th : {256u, 512u})
-            for (uint32_t ch : {256u, 1024u})
-                for (uint32_t wt : {8u, 32u, 128u}) cands.push_back({th, ch, wt});
+        if (p->lds) {
+            for (uint32_t th : {256u, 512u, 1024u})
+                for (uint32_t wt : {16u, 32u, 64u, 128u}) cands.push_back({th, kMaxChunk, wt});
+        } else {
+            for (uint32_t th : {256u, 512u})
+                for (uint32_t ch : {256u, 1024u})
+                    for (uint32_t wt : {8u, 32u, 128u}) cands.push_back({th, ch, wt});
+        }
     } else {
         cands.push_back({p->threads, p->chunk, p->wave_threshold});
     }
@@ -397,6 +741,7 @@ extern "C" lg_status lg_bfs_batch_plan(const lg_graph *const *graphs, uint32_t n
         p->num_graphs = num_graphs;
         p->num_jobs = num_jobs;
         p->qcap = qcap;
+        p->lds = batch_bitmap_bytes(qcap) <= kBatchLdsBytes ? batch_bitmap_bytes(qcap) : 0;
         p->depth = depth;
         p->parent = parent;
         p->max_depth = max_depth;
