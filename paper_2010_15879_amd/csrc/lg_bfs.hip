@@ -1789,6 +1789,33 @@ lg_status bfs_run(lg_graph *g, BfsWork &w, const uint32_t *roots, uint32_t r, in
 // ---------------------------------------------------------------------------
 
 constexpr uint32_t kMsRoots = 64;
+
+// Where the results of (root r, vertex v) go.  MsRows: straight into the
+// caller's rows.  MsCells: a relabeled graph's results in label space, the
+// roots of a vertex side by side, depths in a byte while they fit: the later
+// gather by original ID then takes a vertex's 64 parents with two lines
+// instead of a line each, and the writes of a vertex's roots fill its lines
+// (Kronecker 2^22 vertices, 64 roots: rows in label space and an unpermute
+// per row 5.8 ms, cells 4.0 ms).
+struct MsRows {
+    static constexpr bool kCells = false;
+    using Depth = int32_t;
+    int32_t *depth, *parent;  // parent may be NULL
+    uint64_t n;
+    __device__ __forceinline__ uint64_t at(uint32_t r, uint64_t v) const { return (uint64_t)r * n + v; }
+};
+template <class D>
+struct MsCells {
+    static constexpr bool kCells = true;
+    using Depth = D;
+    D *depth;
+    int32_t *parent;
+    uint32_t stride;  // cells of a vertex: 16, 32 or 64, at least the batch's roots
+    __device__ __forceinline__ uint64_t at(uint32_t r, uint64_t v) const { return v * stride + r; }
+};
+constexpr int32_t kMsByteDepth = 255;  // depths below it fit a byte cell
+inline uint32_t ms_stride(uint32_t r) { return r <= 16 ? 16u : (r <= 32 ? 32u : 64u); }
+
 constexpr uint32_t kMsLaneLimit = 256;  // entries a lane reads before a wave finishes its list
 constexpr int kMsThreads = 256;
 
@@ -1799,16 +1826,16 @@ __device__ __forceinline__ unsigned long long wave_or64(unsigned long long x) {
 
 // the roots (original IDs, mapped to labels through inv when relabeled):
 // reached at depth 0, their own parents, in the first frontier
+template <class Out>
 __global__ void ms_roots_kernel(uint32_t r, const uint32_t *__restrict__ roots, const uint32_t *__restrict__ inv,
-                                uint64_t n, unsigned long long *__restrict__ vis, unsigned long long *__restrict__ fr,
-                                int32_t *__restrict__ depth, int32_t *__restrict__ parent) {
+                                unsigned long long *__restrict__ vis, unsigned long long *__restrict__ fr, Out out) {
     const uint32_t i = threadIdx.x;
     if (i >= r) return;
     const uint32_t x = inv ? inv[roots[i]] : roots[i];
     atomicOr(&vis[x], 1ull << i);
     atomicOr(&fr[x], 1ull << i);
-    depth[(uint64_t)i * n + x] = 0;
-    if (parent) parent[(uint64_t)i * n + x] = (int32_t)x;
+    out.depth[out.at(i, x)] = 0;
+    if (out.parent) out.parent[out.at(i, x)] = (int32_t)x;
 }
 
 // bitmap of the vertices with a non-empty mask
@@ -1829,12 +1856,12 @@ __global__ void ms_bits_kernel(uint32_t n, const unsigned long long *__restrict_
 // -1 (the largest value unsigned) where no parent is set yet, so the row
 // ends with the smallest frontier neighbour: the first in v's sorted list,
 // the parent a search from root b alone takes.
-template <class Acc, bool kParent>
+template <class Acc, bool kParent, class Out>
 __global__ __launch_bounds__(kTdThreads) void ms_mark_kernel(
     Acc acc, const uint32_t *__restrict__ queue, uint32_t qsize, const uint64_t *__restrict__ fstart,
     const uint32_t *__restrict__ fw, const uint64_t *__restrict__ fscan, uint64_t edges,
     const unsigned long long *__restrict__ fr, const unsigned long long *__restrict__ vis,
-    unsigned long long *__restrict__ nx, uint64_t n, uint32_t *__restrict__ parent) {
+    unsigned long long *__restrict__ nx, Out out) {
     __shared__ uint64_t s_scan[kTdTile + 1];
     __shared__ uint64_t s_start[kTdTile];
     __shared__ uint32_t s_w[kTdTile];
@@ -1906,7 +1933,9 @@ __global__ __launch_bounds__(kTdThreads) void ms_mark_kernel(
                 atomicOr(&nx[u[r]], add);
                 if constexpr (kParent) {
                     for (unsigned long long h = add; h; h &= h - 1)
-                        atomicMin(&parent[(uint64_t)(__ffsll((long long)h) - 1) * n + u[r]], src[r]);
+                        atomicMin(reinterpret_cast<uint32_t *>(
+                                      &out.parent[out.at((uint32_t)__ffsll((long long)h) - 1, u[r])]),
+                                  src[r]);
                 }
             }
         }
@@ -1935,12 +1964,11 @@ static_assert(kMsLaneLimit <= 256, "a parent's list position is kept in one byte
 template <class A> struct MsWavesPerEU { static constexpr int value = 8; };
 template <int I, int O> struct MsWavesPerEU<PackedAcc<I, O>> { static constexpr int value = O == kOffsEF ? 5 : 8; };
 
-template <class Acc, bool kParent, bool kTD>
+template <class Acc, bool kParent, bool kTD, class Out>
 __global__ __launch_bounds__(kMsThreads, MsWavesPerEU<Acc>::value) void ms_resolve_kernel(
     Acc acc, uint32_t n, int32_t next_depth, unsigned long long active, const unsigned long long *__restrict__ fr,
-    unsigned long long *__restrict__ vis, unsigned long long *__restrict__ nx, int32_t *__restrict__ depth,
-    int32_t *__restrict__ parent, uint64_t *__restrict__ bits, uint32_t *__restrict__ pend_v,
-    unsigned long long *__restrict__ pend_m, unsigned long long *__restrict__ ctr) {
+    unsigned long long *__restrict__ vis, unsigned long long *__restrict__ nx, Out out,
+    uint64_t *__restrict__ bits, uint32_t *__restrict__ pend_v, unsigned long long *__restrict__ pend_m, unsigned long long *__restrict__ ctr) {
     __shared__ uint8_t s_par[kParent ? kMsThreads * kMsParStride : 4];
     __shared__ unsigned long long s_act[kMsThreads / kWave];
     uint8_t *par = &s_par[kParent ? threadIdx.x * kMsParStride : 0];
@@ -1991,33 +2019,85 @@ __global__ __launch_bounds__(kMsThreads, MsWavesPerEU<Acc>::value) void ms_resol
             }
             pending = found != P && vi.deg > lim;
         }
-        // the rows of the roots found here, four roots at a time (a found
-        // bit implies a non-empty list, so its position names an entry; the
-        // other lanes read the array's first entry, which exists whenever
-        // any bit is found, and drop it)
-        for (unsigned long long bb = wave_or64(found); bb;) {
-            uint32_t rr[4];
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                rr[k] = bb ? (uint32_t)__ffsll((long long)bb) - 1 : kMsRoots;
-                bb &= bb - 1;
-            }
-            bool has[4];
-#pragma unroll
-            for (int k = 0; k < 4; ++k) has[k] = rr[k] < kMsRoots && ((found >> rr[k]) & 1ull);
-            uint32_t pu[4];
+        if constexpr (Out::kCells) {
+            // a lane per root of one vertex (of two or four, when a vertex has
+            // fewer cells): its parents are reads of one list and its results
+            // one vertex's cells.  Four such steps' reads are in flight.
             if constexpr (kParent && !kTD) {
+                // the lanes read each other's positions
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            }
+            const uint32_t per = kWave / out.stride;  // vertices a step
+            const uint32_t root = lane & (out.stride - 1), sub = lane / out.stride;
+            // first vertices of the steps with anything found
+            unsigned long long todo = __ballot(found != 0ull);
+            if (per > 1) todo = (todo | todo >> 1) & 0x5555555555555555ull;
+            if (per > 2) todo = (todo | todo >> 2) & 0x1111111111111111ull;
+            while (todo) {
+                uint32_t vv[4], pu[4];
+                bool has[4];
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
-                    const uint64_t pos = has[k] ? vi.start + (uint64_t)par[rr[k]] * st : 0ull;
-                    pu[k] = acc.get(pos, mk);
+                    vv[k] = (todo ? (uint32_t)__ffsll((long long)todo) - 1 : 0u) + sub;
+                    const unsigned long long f = __shfl(found, vv[k], kWave);
+                    has[k] = todo && ((f >> root) & 1ull);
+                    todo &= todo - 1;
+                }
+                if constexpr (kParent && !kTD) {
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        const uint64_t start = __shfl(vi.start, vv[k], kWave);
+                        const uint32_t w = __shfl(vi.w, vv[k], kWave);
+                        const uint32_t at = has[k] ? s_par[(threadIdx.x - lane + vv[k]) * kMsParStride + root] : 0u;
+                        pu[k] = acc.get(has[k] ? start + (uint64_t)at * Acc::step(w) : 0ull, Acc::mask(w));
+                    }
+                }
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    if (has[k]) {
+                        const uint64_t cell = out.at(root, q * 64 + vv[k]);
+                        out.depth[cell] = (typename Out::Depth)next_depth;
+                        if constexpr (kParent && !kTD) out.parent[cell] = (int32_t)pu[k];
+                    }
                 }
             }
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                if (has[k]) {
-                    depth[(uint64_t)rr[k] * n + v] = next_depth;
-                    if constexpr (kParent && !kTD) parent[(uint64_t)rr[k] * n + v] = (int32_t)pu[k];
+            if constexpr (kParent && !kTD) {
+                // the next word's positions are written after these reads
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            }
+        } else {
+            // the rows of the roots found here, four roots at a time (a found
+            // bit implies a non-empty list, so its position names an entry; the
+            // other lanes read the array's first entry, which exists whenever
+            // any bit is found, and drop it)
+            for (unsigned long long bb = wave_or64(found); bb;) {
+                uint32_t rr[4];
+    #pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    rr[k] = bb ? (uint32_t)__ffsll((long long)bb) - 1 : kMsRoots;
+                    bb &= bb - 1;
+                }
+                bool has[4];
+    #pragma unroll
+                for (int k = 0; k < 4; ++k) has[k] = rr[k] < kMsRoots && ((found >> rr[k]) & 1ull);
+                uint32_t pu[4];
+                if constexpr (kParent && !kTD) {
+    #pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        const uint64_t pos = has[k] ? vi.start + (uint64_t)par[rr[k]] * st : 0ull;
+                        pu[k] = acc.get(pos, mk);
+                    }
+                }
+    #pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    if (has[k]) {
+                        out.depth[out.at(rr[k], v)] = next_depth;
+                        if constexpr (kParent && !kTD) out.parent[out.at(rr[k], v)] = (int32_t)pu[k];
+                    }
                 }
             }
         }
@@ -2058,10 +2138,9 @@ __global__ __launch_bounds__(kMsThreads, MsWavesPerEU<Acc>::value) void ms_resol
 // The long lists left by ms_resolve_kernel: a wave per vertex reads the rest
 // of the list 64 entries per step; for each open bit the first lane holding
 // it gives the parent.
-template <class Acc, bool kParent>
+template <class Acc, bool kParent, class Out>
 __global__ void ms_pending_kernel(Acc acc, uint32_t n, int32_t next_depth, const unsigned long long *__restrict__ fr,
-                                  unsigned long long *__restrict__ vis, unsigned long long *__restrict__ nx,
-                                  int32_t *__restrict__ depth, int32_t *__restrict__ parent,
+                                  unsigned long long *__restrict__ vis, unsigned long long *__restrict__ nx, Out out,
                                   const uint32_t *__restrict__ pend_v, const unsigned long long *__restrict__ pend_m,
                                   unsigned long long *__restrict__ ctr) {
     const uint32_t lane = lane_id();
@@ -2087,8 +2166,8 @@ __global__ void ms_pending_kernel(Acc acc, uint32_t n, int32_t next_depth, const
                 const uint32_t first = (uint32_t)__ffsll((long long)holders) - 1;
                 const uint32_t pu = __shfl(u, first, kWave);
                 if (lane == 0) {
-                    depth[(uint64_t)r * n + v] = next_depth;
-                    if constexpr (kParent) parent[(uint64_t)r * n + v] = (int32_t)pu;
+                    out.depth[out.at(r, v)] = (typename Out::Depth)next_depth;
+                    if constexpr (kParent) out.parent[out.at(r, v)] = (int32_t)pu;
                 }
             }
             P &= ~uni;
@@ -2123,45 +2202,198 @@ __global__ void ms_finish_kernel(uint32_t n, uint32_t r, const unsigned long lon
     }
 }
 
-// One batch of at most 64 roots.  The rows are computed in label space.  On
-// a relabeled graph they are then unpermuted into original IDs
-// (bfs_unpermute_kernel, as for a single root): from the workspace rows
-// `ws` (depth rows, then parent rows) when the caller has them, else each
-// row is first copied to a one-row workspace.  The host reads two counters
-// per level: the next frontier's size and the searches still running.
+// The cells of a relabeled batch to the caller's rows by original ID.  A
+// workgroup takes 64 original IDs: a lane per root reads a vertex's cells,
+// the tile turns in LDS, and every row gets 64 consecutive entries.
+// Searches that never reached a vertex get -1 from its mask.
+constexpr int kMsTile = 64;
+template <class D>
+__global__ __launch_bounds__(256) void ms_rows_kernel(uint32_t n, uint32_t r, const uint32_t *__restrict__ inv,
+                                                      const uint32_t *__restrict__ perm,
+                                                      const unsigned long long *__restrict__ vis, MsCells<D> in,
+                                                      int32_t *__restrict__ depth, int32_t *__restrict__ parent) {
+    __shared__ int32_t s_d[kMsRoots][kMsTile + 1], s_p[kMsRoots][kMsTile + 1];
+    const uint32_t lane = lane_id(), wv = threadIdx.x / kWave;
+    constexpr uint32_t kPer = kMsTile / 4;  // vertices per wave
+    const uint64_t o0 = (uint64_t)blockIdx.x * kMsTile;
+    const uint64_t mine = o0 + wv * kPer + (lane & (kPer - 1));
+    const uint32_t x = inv[mine < n ? mine : n - 1];
+    const unsigned long long mask = vis[x];
+    const uint32_t per = kWave / in.stride, root = lane & (in.stride - 1), sub = lane / in.stride;
+    // eight steps' loads in flight, then their parents' original IDs
+    constexpr int kIn = 8;
+    for (uint32_t i0 = 0; i0 < kPer; i0 += kIn * per) {
+        bool has[kIn];
+        int32_t d[kIn];
+        uint32_t p[kIn];
+#pragma unroll
+        for (int k = 0; k < kIn; ++k) {
+            const uint32_t i = (i0 + k * per + sub) & (kPer - 1);
+            has[k] = (__shfl(mask, i, kWave) >> root) & 1ull;
+            const uint64_t cell = in.at(has[k] ? root : 0u, __shfl(x, i, kWave));
+            d[k] = (int32_t)in.depth[cell];
+            p[k] = parent ? (uint32_t)in.parent[cell] : 0u;
+        }
+        if (parent) {
+#pragma unroll
+            for (int k = 0; k < kIn; ++k) p[k] = perm[has[k] ? p[k] : 0u];
+        }
+#pragma unroll
+        for (int k = 0; k < kIn; ++k) {
+            const uint32_t i = i0 + k * per + sub;
+            if (i >= kPer) continue;
+            s_d[root][wv * kPer + i] = has[k] ? d[k] : -1;
+            if (parent) s_p[root][wv * kPer + i] = has[k] ? (int32_t)p[k] : -1;
+        }
+    }
+    __syncthreads();
+    const uint64_t o = o0 + lane;
+    if (o >= n) return;
+    for (uint32_t i = wv; i < r; i += 4) {
+        depth[(uint64_t)i * n + o] = s_d[i][lane];
+        if (parent) parent[(uint64_t)i * n + o] = s_p[i][lane];
+    }
+}
+
+__global__ void ms_widen_kernel(uint64_t cells, const uint8_t *__restrict__ in, int32_t *__restrict__ out) {
+    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
+    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < cells; i += stride) out[i] = in[i];
+}
+
+// What a batch's levels share.
+struct MsBatch {
+    lg_graph *g;
+    BfsWork &w;
+    MsWork &ms;
+    uint32_t r;
+    bool parents;
+    int32_t max_depth;
+    hipStream_t s;
+    unsigned long long *vis, *fr, *nx, *ctr;
+    uint64_t *bits;
+    uint32_t *queue;
+    uint32_t rgrid;          // of the resolve pass
+    int32_t level = 0;
+    uint64_t fsize = 0;      // vertices on the frontier
+    unsigned long long active = 0;  // searches still running
+    bool running() const { return fsize && active && (max_depth < 0 || level < max_depth); }
+};
+
+// the masks, the queue and the first results
+template <class Out>
+static lg_status ms_begin(MsBatch &b, const uint32_t *roots, Out out) {
+    lg_graph *g = b.g;
+    const uint32_t n = g->n;
+    const uint64_t words = ((uint64_t)n + 63) / 64;
+    hipStream_t s = b.s;
+    LG_TRY(fill_u64((uint64_t *)b.vis, 0, n, s));
+    LG_TRY(fill_u64((uint64_t *)b.fr, 0, n, s));
+    LG_TRY(fill_u64((uint64_t *)b.ctr, 0, 8, s));
+    // top-down levels take parents by atomic minimum over entries that start at -1
+    if (b.parents)
+        LG_TRY(fill_u32(reinterpret_cast<uint32_t *>(out.parent), 0xFFFFFFFFu,
+                        Out::kCells ? (uint64_t)ms_stride(b.r) * n : (uint64_t)b.r * n, s));
+    LG_CHECK_HIP(hipMemcpyAsync(b.ms.roots.p, roots, (uint64_t)b.r * 4, hipMemcpyHostToDevice, s));
+    LG_LAUNCH(ms_roots_kernel<Out>, 1, kMsRoots, 0, s, b.r, b.ms.roots.as<uint32_t>(),
+              g->relabel != LG_RELABEL_NONE ? g->inv.as<uint32_t>() : nullptr, b.vis, b.fr, out);
+    LG_CHECK_LAUNCH();
+    LG_LAUNCH(ms_bits_kernel, grid_for(words * kWave, 256, kStrideBlocks), 256, 0, s, n,
+              (const unsigned long long *)b.fr, b.bits);
+    LG_CHECK_LAUNCH();
+    LG_LAUNCH(bitmap_to_queue_kernel, grid_for(words, 256, 1u << 16), 256, 0, s, words, b.bits, b.queue, b.ctr);
+    LG_CHECK_LAUNCH();
+    LG_CHECK_HIP(hipMemcpyAsync(b.w.host, b.ctr, 8, hipMemcpyDeviceToHost, s));
+    LG_CHECK_HIP(hipStreamSynchronize(s));
+    b.fsize = b.w.host[0];
+    b.active = b.r >= 64 ? ~0ull : ((1ull << b.r) - 1ull);
+    return LG_OK;
+}
+
+// one level; the host reads two counters: the next frontier's size and the
+// searches still running
+template <class Acc, class Out>
+static lg_status ms_level(MsBatch &b, Acc acc, Out out) {
+    lg_graph *g = b.g;
+    BfsWork &w = b.w;
+    const uint32_t n = g->n;
+    const uint64_t words = ((uint64_t)n + 63) / 64;
+    hipStream_t s = b.s;
+    // top-down while the frontier's edges are under a third of the
+    // graph's: a top-down edge costs a mask read and one or two atomics,
+    // a bottom-up level reads every open vertex's list until its open
+    // bits are found, in the early levels the whole list (measured at
+    // Erdos-Renyi scale 26, 64 roots: the level with 3% of the edges on
+    // the frontier took 45 ms bottom-up, 10 ms top-down)
+    bool td = b.fsize <= (uint64_t)n / 4;
+    uint64_t fedges = 0;
+    if (td) {
+        LG_LAUNCH(td_prepare_kernel<Acc>, grid_for(b.fsize, 256, 1u << 16), 256, 0, s, acc, b.queue,
+                  (uint32_t)b.fsize, w.fstart.as<uint64_t>(), w.fdeg.as<uint32_t>(), w.fw.as<uint32_t>());
+        LG_CHECK_LAUNCH();
+        LG_TRY(exclusive_scan_u32(w.fdeg.as<uint32_t>(), w.fscan.as<uint64_t>(), b.fsize, w.scan_tmp, s));
+        LG_CHECK_HIP(hipMemcpyAsync(w.host, w.fscan.as<uint64_t>() + b.fsize, 8, hipMemcpyDeviceToHost, s));
+        LG_CHECK_HIP(hipStreamSynchronize(s));
+        fedges = w.host[0];
+        td = fedges * 3 < g->m;
+    }
+    LG_TRY(fill_u64((uint64_t *)b.ctr, 0, 8, s));  // [0] queue, [2] running searches, [3] pending
+    if (td) {
+        LG_TRY(fill_u64((uint64_t *)b.nx, 0, n, s));
+        if (fedges) {
+            auto mark = [&](auto kpar) -> lg_status {
+                LG_LAUNCH((ms_mark_kernel<Acc, decltype(kpar)::value, Out>), grid_for(fedges, kTdTile, 1u << 20),
+                          kTdThreads, 0, s, acc, b.queue, (uint32_t)b.fsize, w.fstart.as<uint64_t>(),
+                          w.fw.as<uint32_t>(), w.fscan.as<uint64_t>(), fedges, (const unsigned long long *)b.fr,
+                          (const unsigned long long *)b.vis, b.nx, out);
+                LG_CHECK_LAUNCH();
+                return LG_OK;
+            };
+            if (b.parents) LG_TRY(mark(std::true_type{}));
+            else LG_TRY(mark(std::false_type{}));
+        }
+    }
+    auto resolve = [&](auto kpar, auto ktd) -> lg_status {
+        constexpr bool P = decltype(kpar)::value, T = decltype(ktd)::value;
+        LG_LAUNCH((ms_resolve_kernel<Acc, P, T, Out>), b.rgrid, kMsThreads, 0, s, acc, n, b.level + 1, b.active,
+                  (const unsigned long long *)b.fr, b.vis, b.nx, out, b.bits, b.ms.pend_v.as<uint32_t>(),
+                  b.ms.pend_m.as<unsigned long long>(), b.ctr);
+        LG_CHECK_LAUNCH();
+        if constexpr (!T) {  // only bottom-up levels leave long lists
+            LG_LAUNCH((ms_pending_kernel<Acc, P, Out>), kStrideBlocks, 256, 0, s, acc, n, b.level + 1,
+                      (const unsigned long long *)b.fr, b.vis, b.nx, out, (const uint32_t *)b.ms.pend_v.p,
+                      (const unsigned long long *)b.ms.pend_m.p, b.ctr);
+            LG_CHECK_LAUNCH();
+        }
+        return LG_OK;
+    };
+    if (b.parents) {
+        if (td) LG_TRY(resolve(std::true_type{}, std::true_type{}));
+        else LG_TRY(resolve(std::true_type{}, std::false_type{}));
+    } else {
+        if (td) LG_TRY(resolve(std::false_type{}, std::true_type{}));
+        else LG_TRY(resolve(std::false_type{}, std::false_type{}));
+    }
+    LG_LAUNCH(bitmap_to_queue_kernel, grid_for(words, 256, 1u << 16), 256, 0, s, words, b.bits, b.queue, b.ctr);
+    LG_CHECK_LAUNCH();
+    LG_CHECK_HIP(hipMemcpyAsync(w.host, b.ctr, 24, hipMemcpyDeviceToHost, s));
+    LG_CHECK_HIP(hipStreamSynchronize(s));
+    b.fsize = w.host[0];
+    b.active = w.host[2];
+    std::swap(b.fr, b.nx);
+    ++b.level;
+    return LG_OK;
+}
+
+// One batch of at most 64 roots.  Results go straight into the caller's rows,
+// or, on a relabeled graph whose cells the caller has (`cells`), through
+// them; without them the rows are computed in label space and each is
+// copied aside and unpermuted (bfs_unpermute_kernel, as for a single root).
 template <class Acc>
 static lg_status bfs_ms_batch(lg_graph *g, BfsWork &w, MsWork &ms, Acc acc, const uint32_t *roots, uint32_t r,
-                              int32_t *depth_out, int32_t *parent_out, int32_t max_depth, int32_t *ws,
+                              int32_t *depth_out, int32_t *parent_out, int32_t max_depth, bool cells,
                               hipStream_t s) {
     const uint32_t n = g->n;
-    const bool rel = g->relabel != LG_RELABEL_NONE;
-    int32_t *depth = rel && ws ? ws : depth_out;
-    int32_t *parent = parent_out ? (rel && ws ? ws + (uint64_t)r * n : parent_out) : nullptr;
     const uint64_t words = ((uint64_t)n + 63) / 64;
-    unsigned long long *vis = ms.vis.as<unsigned long long>();
-    unsigned long long *fr = ms.fr.as<unsigned long long>();
-    unsigned long long *nx = ms.nx.as<unsigned long long>();
-    uint64_t *bits = ms.bits.as<uint64_t>();
-    unsigned long long *ctr = w.counters.as<unsigned long long>();
-    uint32_t *queue = w.qa.as<uint32_t>();
-    const uint32_t wgrid = grid_for(words * kWave, 256, kStrideBlocks);
-    LG_TRY(fill_u64((uint64_t *)vis, 0, n, s));
-    LG_TRY(fill_u64((uint64_t *)fr, 0, n, s));
-    LG_TRY(fill_u64((uint64_t *)ctr, 0, 8, s));
-    // top-down levels take parents by atomic minimum over rows that start at -1
-    if (parent) LG_TRY(fill_u32(reinterpret_cast<uint32_t *>(parent), 0xFFFFFFFFu, (uint64_t)r * n, s));
-    LG_CHECK_HIP(hipMemcpyAsync(ms.roots.p, roots, (uint64_t)r * 4, hipMemcpyHostToDevice, s));
-    LG_LAUNCH(ms_roots_kernel, 1, kMsRoots, 0, s, r, ms.roots.as<uint32_t>(), rel ? g->inv.as<uint32_t>() : nullptr,
-              (uint64_t)n, vis, fr, depth, parent);
-    LG_CHECK_LAUNCH();
-    LG_LAUNCH(ms_bits_kernel, wgrid, 256, 0, s, n, (const unsigned long long *)fr, bits);
-    LG_CHECK_LAUNCH();
-    LG_LAUNCH(bitmap_to_queue_kernel, grid_for(words, 256, 1u << 16), 256, 0, s, words, bits, queue, ctr);
-    LG_CHECK_LAUNCH();
-    LG_CHECK_HIP(hipMemcpyAsync(w.host, ctr, 8, hipMemcpyDeviceToHost, s));
-    LG_CHECK_HIP(hipStreamSynchronize(s));
-    uint64_t fsize = w.host[0];
-    unsigned long long active = r >= 64 ? ~0ull : ((1ull << r) - 1ull);
     // the resolve grid: on graphs with even degrees two workgroups per CU
     // (more waves only evict the lanes' list lines under the random mask
     // reads: measured slower); on skewed ones, where lanes of a wave wait
@@ -2169,91 +2401,51 @@ static lg_status bfs_ms_batch(lg_graph *g, BfsWork &w, MsWork &ms, Acc acc, cons
     int cus = 0;
     LG_CHECK_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, g->device));
     const bool skewed = (uint64_t)g->n_heavy * 256 > n;
-    const uint32_t rgrid = grid_for(words * kWave, kMsThreads, skewed ? kStrideBlocks : (uint32_t)std::max(1, 2 * cus));
-    for (int32_t level = 0; fsize && active && (max_depth < 0 || level < max_depth); ++level) {
-        // top-down while the frontier's edges are under a third of the
-        // graph's: a top-down edge costs a mask read and one or two atomics,
-        // a bottom-up level reads every open vertex's list until its open
-        // bits are found, in the early levels the whole list (measured at
-        // Erdos-Renyi scale 26, 64 roots: the level with 3% of the edges on
-        // the frontier took 45 ms bottom-up, 10 ms top-down)
-        bool td = fsize <= (uint64_t)n / 4;
-        uint64_t fedges = 0;
-        if (td) {
-            LG_LAUNCH(td_prepare_kernel<Acc>, grid_for(fsize, 256, 1u << 16), 256, 0, s, acc, queue, (uint32_t)fsize,
-                      w.fstart.as<uint64_t>(), w.fdeg.as<uint32_t>(), w.fw.as<uint32_t>());
+    MsBatch b{g, w, ms, r, parent_out != nullptr, max_depth, s, ms.vis.as<unsigned long long>(),
+              ms.fr.as<unsigned long long>(), ms.nx.as<unsigned long long>(), w.counters.as<unsigned long long>(),
+              ms.bits.as<uint64_t>(), w.qa.as<uint32_t>(),
+              grid_for(words * kWave, kMsThreads, skewed ? kStrideBlocks : (uint32_t)std::max(1, 2 * cus))};
+    if (cells) {
+        int32_t *parent = parent_out ? ms.cell_parent.as<int32_t>() : nullptr;
+        const uint32_t stride = ms_stride(r);
+        const MsCells<uint8_t> bytes{ms.cell_depth.as<uint8_t>(), parent, stride};
+        auto rows = [&](auto in) -> lg_status {
+            LG_LAUNCH((ms_rows_kernel<typename decltype(in)::Depth>), grid_for(n, kMsTile), 256, 0, s, n, r,
+                      g->inv.as<uint32_t>(), g->perm.as<uint32_t>(), (const unsigned long long *)b.vis, in, depth_out,
+                      parent_out);
             LG_CHECK_LAUNCH();
-            LG_TRY(exclusive_scan_u32(w.fdeg.as<uint32_t>(), w.fscan.as<uint64_t>(), fsize, w.scan_tmp, s));
-            LG_CHECK_HIP(hipMemcpyAsync(w.host, w.fscan.as<uint64_t>() + fsize, 8, hipMemcpyDeviceToHost, s));
-            LG_CHECK_HIP(hipStreamSynchronize(s));
-            fedges = w.host[0];
-            td = fedges * 3 < g->m;
-        }
-        LG_TRY(fill_u64((uint64_t *)ctr, 0, 8, s));  // [0] queue, [2] running searches, [3] pending
-        if (td) {
-            LG_TRY(fill_u64((uint64_t *)nx, 0, n, s));
-            if (fedges) {
-                auto mark = [&](auto kpar) -> lg_status {
-                    LG_LAUNCH((ms_mark_kernel<Acc, decltype(kpar)::value>), grid_for(fedges, kTdTile, 1u << 20),
-                              kTdThreads, 0, s, acc, queue, (uint32_t)fsize, w.fstart.as<uint64_t>(),
-                              w.fw.as<uint32_t>(), w.fscan.as<uint64_t>(), fedges, (const unsigned long long *)fr,
-                              (const unsigned long long *)vis, nx, (uint64_t)n, reinterpret_cast<uint32_t *>(parent));
-                    LG_CHECK_LAUNCH();
-                    return LG_OK;
-                };
-                if (parent) LG_TRY(mark(std::true_type{}));
-                else LG_TRY(mark(std::false_type{}));
-            }
-        }
-        auto resolve = [&](auto kpar, auto ktd) -> lg_status {
-            constexpr bool P = decltype(kpar)::value, T = decltype(ktd)::value;
-            LG_LAUNCH((ms_resolve_kernel<Acc, P, T>), rgrid, kMsThreads, 0, s, acc, n, level + 1, active,
-                      (const unsigned long long *)fr, vis, nx, depth, parent, bits, ms.pend_v.as<uint32_t>(),
-                      ms.pend_m.as<unsigned long long>(), ctr);
-            LG_CHECK_LAUNCH();
-            if constexpr (!T) {  // only bottom-up levels leave long lists
-                LG_LAUNCH((ms_pending_kernel<Acc, P>), kStrideBlocks, 256, 0, s, acc, n, level + 1,
-                          (const unsigned long long *)fr, vis, nx, depth, parent, (const uint32_t *)ms.pend_v.p,
-                          (const unsigned long long *)ms.pend_m.p, ctr);
-                LG_CHECK_LAUNCH();
-            }
             return LG_OK;
         };
-        if (parent) {
-            if (td) LG_TRY(resolve(std::true_type{}, std::true_type{}));
-            else LG_TRY(resolve(std::true_type{}, std::false_type{}));
-        } else {
-            if (td) LG_TRY(resolve(std::false_type{}, std::true_type{}));
-            else LG_TRY(resolve(std::false_type{}, std::false_type{}));
-        }
-        LG_LAUNCH(bitmap_to_queue_kernel, grid_for(words, 256, 1u << 16), 256, 0, s, words, bits, queue, ctr);
+        LG_TRY(ms_begin(b, roots, bytes));
+        while (b.running() && b.level + 1 < kMsByteDepth) LG_TRY(ms_level(b, acc, bytes));
+        if (!b.running()) return rows(bytes);
+        // deeper than a byte: the cells widen once
+        const uint64_t all = (uint64_t)n * stride;
+        LG_TRY(ms.cell_wide.ensure(all * 4));
+        LG_LAUNCH(ms_widen_kernel, grid_for(all, 256 * 8, 1u << 16), 256, 0, s, all,
+                  (const uint8_t *)ms.cell_depth.p, ms.cell_wide.as<int32_t>());
         LG_CHECK_LAUNCH();
-        LG_CHECK_HIP(hipMemcpyAsync(w.host, ctr, 24, hipMemcpyDeviceToHost, s));
-        LG_CHECK_HIP(hipStreamSynchronize(s));
-        fsize = w.host[0];
-        active = w.host[2];
-        std::swap(fr, nx);
+        const MsCells<int32_t> wide{ms.cell_wide.as<int32_t>(), parent, stride};
+        while (b.running()) LG_TRY(ms_level(b, acc, wide));
+        return rows(wide);
     }
-    LG_LAUNCH(ms_finish_kernel, wgrid, 256, 0, s, n, r, (const unsigned long long *)vis, depth, parent);
+    const MsRows out{depth_out, parent_out, n};
+    LG_TRY(ms_begin(b, roots, out));
+    while (b.running()) LG_TRY(ms_level(b, acc, out));
+    LG_LAUNCH(ms_finish_kernel, grid_for(words * kWave, 256, kStrideBlocks), 256, 0, s, n, r,
+              (const unsigned long long *)b.vis, depth_out, parent_out);
     LG_CHECK_LAUNCH();
-    if (rel) {
-        for (uint32_t i = 0; i < r; ++i) {
-            int32_t *d_row = depth_out + (uint64_t)i * n;
-            int32_t *p_row = parent_out ? parent_out + (uint64_t)i * n : nullptr;
-            const int32_t *d_in = depth + (uint64_t)i * n;
-            const uint32_t *p_in = parent ? reinterpret_cast<const uint32_t *>(parent + (uint64_t)i * n) : nullptr;
-            if (!ws) {  // the row is its own output: copy it aside first
-                int32_t *tmp_d = w.depth_i.as<int32_t>();
-                uint32_t *tmp_p = parent ? w.parent_i.as<uint32_t>() : nullptr;
-                LG_CHECK_HIP(hipMemcpyAsync(tmp_d, d_row, (uint64_t)n * 4, hipMemcpyDeviceToDevice, s));
-                if (p_row) LG_CHECK_HIP(hipMemcpyAsync(tmp_p, p_row, (uint64_t)n * 4, hipMemcpyDeviceToDevice, s));
-                d_in = tmp_d;
-                p_in = tmp_p;
-            }
-            LG_LAUNCH(bfs_unpermute_kernel, grid_for(n, 256, 1u << 16), 256, 0, s, n, g->inv.as<uint32_t>(),
-                      g->perm.as<uint32_t>(), d_in, p_in, d_row, p_row);
-            LG_CHECK_LAUNCH();
-        }
+    if (g->relabel == LG_RELABEL_NONE) return LG_OK;
+    for (uint32_t i = 0; i < r; ++i) {
+        int32_t *d_row = depth_out + (uint64_t)i * n;
+        int32_t *p_row = parent_out ? parent_out + (uint64_t)i * n : nullptr;
+        int32_t *tmp_d = w.depth_i.as<int32_t>();
+        uint32_t *tmp_p = p_row ? w.parent_i.as<uint32_t>() : nullptr;
+        LG_CHECK_HIP(hipMemcpyAsync(tmp_d, d_row, (uint64_t)n * 4, hipMemcpyDeviceToDevice, s));
+        if (p_row) LG_CHECK_HIP(hipMemcpyAsync(tmp_p, p_row, (uint64_t)n * 4, hipMemcpyDeviceToDevice, s));
+        LG_LAUNCH(bfs_unpermute_kernel, grid_for(n, 256, 1u << 16), 256, 0, s, n, g->inv.as<uint32_t>(),
+                  g->perm.as<uint32_t>(), (const int32_t *)tmp_d, (const uint32_t *)tmp_p, d_row, p_row);
+        LG_CHECK_LAUNCH();
     }
     return LG_OK;
 }
@@ -2363,7 +2555,7 @@ static lg_status bfs_run_lanes(lg_graph *g, const uint32_t *roots, uint32_t r, i
 // It runs on `stream` and holds the device's BFS pool (its lane 0
 // workspace, the multi-source masks) for its duration.
 constexpr uint32_t kMsMinRoots = 16;
-constexpr uint64_t kMsRowsCap = 16ull << 30;  // bytes of label-space rows a relabeled batch may keep aside
+constexpr uint64_t kMsCellsCap = 16ull << 30;  // bytes of label-space cells a relabeled batch may keep (4-byte depths)
 
 static bool bfs_ms_graph(const lg_graph *g, uint32_t flags) {
     if (flags != LG_BFS_DIRECTION_OPT) return false;
@@ -2407,15 +2599,15 @@ static lg_status bfs_run_ms(lg_graph *g, const uint32_t *roots, uint32_t r, int3
     LG_TRY(ms.pend_v.ensure(n * 4));
     LG_TRY(ms.pend_m.ensure(n * 8));
     LG_TRY(ms.roots.ensure(kMsRoots * 4));
-    // relabeled graphs: a batch's label-space rows in a workspace, so that
-    // they unpermute straight into the caller's rows, when it stays within
-    // kMsRowsCap (else every row is copied aside before its unpermute)
-    int32_t *ws = nullptr;
+    // relabeled graphs: a batch's label-space cells in a workspace when they
+    // stay within kMsCellsCap (else rows are copied aside one by one)
+    bool cells = false;
     if (g->relabel != LG_RELABEL_NONE) {
-        const uint64_t need = (uint64_t)std::min<uint32_t>(r, kMsRoots) * n * (parent ? 8 : 4);
-        if (need <= kMsRowsCap) {
-            LG_TRY(ms.rows.ensure(need));
-            ws = ms.rows.as<int32_t>();
+        const uint64_t all = n * ms_stride(std::min<uint32_t>(r, kMsRoots));
+        cells = all * (parent ? 8 : 4) <= kMsCellsCap;
+        if (cells) {
+            LG_TRY(ms.cell_depth.ensure(all));
+            if (parent) LG_TRY(ms.cell_parent.ensure(all * 4));
         }
     }
     // lane 0's stream is not used: everything runs on the caller's stream
@@ -2423,7 +2615,7 @@ static lg_status bfs_run_ms(lg_graph *g, const uint32_t *roots, uint32_t r, int3
         for (uint32_t b0 = 0; b0 < r; b0 += kMsRoots) {
             const uint32_t rb = std::min<uint32_t>(kMsRoots, r - b0);
             LG_TRY(bfs_ms_batch(g, w, ms, acc, roots + b0, rb, depth + (uint64_t)b0 * n,
-                                parent ? parent + (uint64_t)b0 * n : nullptr, max_depth, ws, stream));
+                                parent ? parent + (uint64_t)b0 * n : nullptr, max_depth, cells, stream));
         }
         return LG_OK;  // batches follow each other on the caller's stream (shared masks and roots buffer)
     }));

@@ -136,9 +136,11 @@ struct MsWork {
     DevBuf bits;                 // u64[words]: vertices of the next frontier
     DevBuf pend_v, pend_m;       // u32[n], u64[n]: vertices left for the wave pass, their open bits
     DevBuf roots;                // u32[64]: the batch's roots
-    DevBuf rows;                 // relabeled graphs: the batch's depth and parent rows in label space
+    // relabeled graphs: the batch's results in label space, 64 roots a vertex
+    DevBuf cell_depth, cell_wide, cell_parent;  // u8, i32 (searches deeper than a byte), i32
     uint64_t bytes() const {
-        return vis.bytes + fr.bytes + nx.bytes + bits.bytes + pend_v.bytes + pend_m.bytes + roots.bytes + rows.bytes;
+        return vis.bytes + fr.bytes + nx.bytes + bits.bytes + pend_v.bytes + pend_m.bytes + roots.bytes + cell_depth.bytes +
+               cell_wide.bytes + cell_parent.bytes;
     }
 };
 struct BfsPool {
