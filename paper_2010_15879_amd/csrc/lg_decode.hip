@@ -5,53 +5,205 @@
 // output so that consecutive lanes decode consecutive elements; gap and
 // Varint lists are decoded in order by a wave per list, 64 entries or bytes
 // per wave step.
+#include <algorithm>
 #include <mutex>
 
 #include "lg_device.hpp"
+#include "lg_varint.hpp"
 
 namespace lg {
 
-__global__ void dec_map_kernel(uint32_t n, const uint32_t *__restrict__ vin, uint32_t k,
-                               const uint32_t *__restrict__ inv, uint32_t *__restrict__ labels,
-                               uint32_t *__restrict__ bad) {
-    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < k; i += stride) {
-        const uint32_t v = vin[i];
-        if (v >= n) { atomicOr(bad, 1u); labels[i] = 0; continue; }
-        labels[i] = inv ? inv[v] : v;
-    }
+// What a decode keeps in its head buffer behind the labels and degrees.
+struct DecodeMarks {
+    uint32_t bad;            // a requested vertex >= n
+    uint32_t n_mid, n_long;  // lists left for the block sorts
+    uint32_t n_chunked;      // Varint lists decoded by chunks
+};
+uint64_t decode_head_bytes(uint64_t k) { return k * 8 + sizeof(DecodeMarks); }
+
+// the label of request i (0 where the vertex does not exist)
+__device__ __forceinline__ uint32_t dec_label(uint32_t n, const uint32_t *__restrict__ vin, uint64_t i,
+                                              const uint32_t *__restrict__ inv, bool &bad) {
+    const uint32_t v = vin[i];
+    bad = v >= n;
+    return bad ? 0u : (inv ? inv[v] : v);
 }
 
 template <class Acc>
-__global__ void dec_degree_kernel(Acc acc, const uint32_t *__restrict__ labels, uint32_t k,
-                                  uint32_t *__restrict__ deg) {
+__global__ void dec_map_kernel(Acc acc, uint32_t n, const uint32_t *__restrict__ vin, uint32_t k,
+                               const uint32_t *__restrict__ inv, uint32_t *__restrict__ labels,
+                               uint32_t *__restrict__ deg, DecodeMarks *__restrict__ marks) {
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < k; i += stride)
-        deg[i] = acc.info(labels[i]).deg;
+    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < k; i += stride) {
+        bool bad;
+        const uint32_t x = dec_label(n, vin, i, inv, bad);
+        if (bad) atomicOr(&marks->bad, 1u);
+        labels[i] = x;
+        if constexpr (!IsVarintAcc<Acc>::value) deg[i] = acc.info(x).deg;
+    }
 }
 
 // Varint lists: d_v is the number of bytes with the top bit clear in the
 // list's byte range; one wave per vertex counts them 8 bytes per lane.
 template <class Acc>
+__device__ __forceinline__ uint32_t dec_varint_count(const Acc &acc, uint64_t b0, uint64_t b1) {
+    uint32_t cnt = 0;
+#pragma unroll 4
+    for (uint64_t q = (b0 >> 3) + lane_id(); q * 8 < b1; q += kWave) {
+        const uint64_t p = q * 8;
+        const uint64_t lo = p < b0 ? b0 - p : 0;         // bytes below the list
+        const uint64_t hi = p + 8 > b1 ? p + 8 - b1 : 0;  // bytes above it
+        uint64_t keep = ~0ull << (8 * lo);
+        if (hi) keep &= ~0ull >> (8 * hi);
+        cnt += (uint32_t)__popcll(~acc.word(p) & 0x8080808080808080ull & keep);
+    }
+    return wave_sum(cnt);
+}
+template <class Acc>
+__device__ __forceinline__ uint32_t dec_varint_degree(const Acc &acc, uint32_t label) {
+    uint64_t b0, b1;
+    acc.offsets(label, b0, b1);
+    return dec_varint_count(acc, b0, b1);
+}
+
+template <class Acc>
 __global__ void dec_varint_degree_kernel(Acc acc, const uint32_t *__restrict__ labels, uint32_t k,
                                          uint32_t *__restrict__ deg) {
-    const uint32_t lane = lane_id();
     const uint64_t wave = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave;
     const uint64_t nwaves = ((uint64_t)gridDim.x * blockDim.x) / kWave;
     for (uint64_t i = wave; i < k; i += nwaves) {
-        uint64_t b0, b1;
-        acc.offsets(labels[i], b0, b1);
-        uint32_t cnt = 0;
-        for (uint64_t q = (b0 >> 3) + lane; q * 8 < b1; q += kWave) {
-            const uint64_t p = q * 8;
-            const uint64_t lo = p < b0 ? b0 - p : 0;         // bytes below the list
-            const uint64_t hi = p + 8 > b1 ? p + 8 - b1 : 0;  // bytes above it
-            uint64_t keep = ~0ull << (8 * lo);
-            if (hi) keep &= ~0ull >> (8 * hi);
-            cnt += (uint32_t)__popcll(~acc.word(p) & 0x8080808080808080ull & keep);
+        const uint32_t cnt = dec_varint_degree(acc, labels[i]);
+        if (lane_id() == 0) deg[i] = cnt;
+    }
+}
+
+// A small request in one launch: labels, degrees, their prefix, and the two
+// values the host waits for straight into its pinned memory.  (Clearing the
+// mark, labels, degrees, scan and two copies were six launches, each longer
+// than its work: 64 lists 138 us in two calls, 77 so.)  Up to kDecSmall requests, a thread each; of Varint lists,
+// which a wave counts, up to a sixteenth of that.
+constexpr uint32_t kDecSmall = 1024;
+
+template <class Acc>
+__global__ __launch_bounds__(kDecSmall) void dec_small_kernel(Acc acc, uint32_t n, const uint32_t *__restrict__ vin,
+                                                              uint32_t k, const uint32_t *__restrict__ inv,
+                                                              uint32_t *__restrict__ labels,
+                                                              uint64_t *__restrict__ out_off,
+                                                              DecodeMarks *__restrict__ marks,
+                                                              uint64_t *__restrict__ host) {
+    __shared__ uint32_t s_deg[kDecSmall];
+    __shared__ uint64_t s_wave[kDecSmall / kWave];
+    __shared__ uint32_t s_bad;
+    const uint32_t tid = threadIdx.x, lane = lane_id(), wv = tid / kWave;
+    if (tid == 0) s_bad = 0;
+    s_deg[tid] = 0;
+    __syncthreads();
+    uint32_t x = 0;
+    if (tid < k) {
+        bool bad;
+        x = dec_label(n, vin, tid, inv, bad);
+        if (bad) atomicOr(&s_bad, 1u);
+        labels[tid] = x;
+        if constexpr (!IsVarintAcc<Acc>::value) s_deg[tid] = acc.info(x).deg;
+    }
+    if constexpr (IsVarintAcc<Acc>::value) {
+        __syncthreads();
+        for (uint32_t i = wv; i < k; i += kDecSmall / kWave) {
+            bool bad;
+            const uint32_t cnt = dec_varint_degree(acc, dec_label(n, vin, i, inv, bad));
+            if (lane == 0) s_deg[i] = cnt;
         }
-        cnt = wave_sum(cnt);
-        if (lane == 0) deg[i] = cnt;
+    }
+    __syncthreads();
+    const uint64_t d = s_deg[tid];
+    const uint64_t incl = wave_incl_scan(d);
+    if (lane == kWave - 1) s_wave[wv] = incl;
+    __syncthreads();
+    uint64_t base = 0;
+    for (uint32_t w = 0; w < wv; ++w) base += s_wave[w];
+    if (tid < k) out_off[tid] = base + incl - d;
+    if (tid == kDecSmall - 1) {
+        out_off[k] = base + incl;
+        host[0] = base + incl;
+        host[1] = s_bad;
+        *marks = DecodeMarks{s_bad, 0, 0, 0};
+    }
+}
+
+// The values of bytes [p0, p1) of a Varint list to the output from entry o:
+// 64 bytes per step, one per lane; a lane holding a value's last byte
+// assembles the value (varint_step), whose index is the number of last bytes
+// before it; DMd adds a wave prefix sum of the differences to the running
+// label.  prevb: the bytes before p0 that belong to the list, carry: the
+// label before it.
+template <class Acc, bool kSorted>
+__device__ __forceinline__ void dec_varint_range(const Acc &acc, uint32_t n, uint64_t p0, uint64_t p1,
+                                                 uint32_t prevb, uint32_t carry, uint64_t i, uint64_t o,
+                                                 const uint32_t *__restrict__ perm, uint32_t *__restrict__ out_ids,
+                                                 uint64_t *__restrict__ keys) {
+    for (; p0 < p1; p0 += kWave) {
+        uint32_t val;
+        const bool end = varint_step(acc, p0, p1, prevb, val);
+        const uint64_t ends = __ballot(end);
+        uint32_t label = val;
+        if constexpr (Acc::kDifferences) {
+            const uint32_t sc = wave_incl_scan(end ? val : 0u);
+            label = carry + sc;
+            carry += __shfl(sc, kWave - 1, kWave);
+        }
+        if (end) {
+            // a stored label is < n; the clamp keeps the lookup in
+            // bounds whatever the stream holds
+            const uint32_t u = perm ? perm[label < n ? label : n - 1] : label;
+            const uint64_t j = o + popc_below(ends);
+            if (kSorted) keys[j] = (i << 32) | u;
+            else out_ids[j] = u;
+        }
+        o += (uint64_t)__popcll(ends);
+    }
+}
+
+// Varint lists in byte chunks (the traversals' chunk tables: a value belongs
+// to the chunk holding its last byte, and the label before every chunk is
+// stored): a workgroup per list takes a chunk per wave at a time, counts
+// their values, and every wave decodes its chunk from its place.  (One wave
+// walked a hub's list alone: 0.52 ms for 256,000 lists of a relabeled 2^22
+// Kronecker graph, now 0.27 for the others and 0.07 for the hubs'.)
+template <class Acc, bool kSorted>
+__global__ __launch_bounds__(1024) void dec_varint_chunks_kernel(
+    Acc acc, uint32_t n, const uint32_t *__restrict__ labels, const uint64_t *__restrict__ out_off,
+    const uint32_t *__restrict__ perm, uint32_t *__restrict__ out_ids, uint64_t *__restrict__ keys,
+    const uint32_t *__restrict__ more, const DecodeMarks *__restrict__ marks, const uint32_t *__restrict__ heavy,
+    uint32_t n_heavy, const uint64_t *__restrict__ hb0, const uint64_t *__restrict__ hb1,
+    const uint64_t *__restrict__ seg_off, const uint32_t *__restrict__ seg_base, uint32_t chunk) {
+    constexpr uint32_t kWaves = 1024 / kWave;
+    __shared__ uint32_t s_cnt[kWaves];
+    const uint32_t lane = lane_id(), wv = threadIdx.x / kWave;
+    const uint32_t lists = marks->n_chunked;
+    for (uint32_t l = blockIdx.x; l < lists; l += gridDim.x) {
+        const uint32_t i = more[l];
+        const uint32_t h = heavy_index(heavy, n_heavy, labels[i]);
+        const uint64_t b0 = hb0[h], b1 = hb1[h], s0 = seg_off[h], chunks = seg_off[h + 1] - s0;
+        uint64_t o = out_off[i];
+        for (uint64_t c0 = 0; c0 < chunks; c0 += kWaves) {
+            const uint64_t c = c0 + wv;
+            const uint64_t pa = c < chunks ? b0 + c * chunk : b1;
+            const uint64_t pz = pa + chunk < b1 ? pa + chunk : b1;
+            const uint32_t cnt = dec_varint_count(acc, pa, pz);
+            if (lane == 0) s_cnt[wv] = cnt;
+            __syncthreads();
+            uint64_t before = 0, all = 0;
+            for (uint32_t w = 0; w < kWaves; ++w) {
+                if (w < wv) before += s_cnt[w];
+                all += s_cnt[w];
+            }
+            if (c < chunks)
+                dec_varint_range<Acc, kSorted>(acc, n, pa, pz, varint_chunk_prevb(acc, b0, pa),
+                                               Acc::kDifferences ? seg_base[s0 + c] : 0u, i, o + before, perm,
+                                               out_ids, keys);
+            o += all;
+            __syncthreads();  // the counts are rewritten
+        }
     }
 }
 
@@ -59,7 +211,8 @@ __global__ void dec_varint_degree_kernel(Acc acc, const uint32_t *__restrict__ l
 template <class Acc, bool kSorted>
 __global__ void dec_lists_kernel(Acc acc, uint32_t n, const uint32_t *__restrict__ labels, uint32_t k,
                                  const uint64_t *__restrict__ out_off, const uint32_t *__restrict__ perm,
-                                 uint32_t *__restrict__ out_ids, uint64_t *__restrict__ keys) {
+                                 uint32_t *__restrict__ out_ids, uint64_t *__restrict__ keys, uint64_t split,
+                                 uint32_t *__restrict__ more, DecodeMarks *__restrict__ marks) {
     const uint32_t lane = lane_id();
     const uint64_t wave = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave;
     const uint64_t nwaves = ((uint64_t)gridDim.x * blockDim.x) / kWave;
@@ -88,54 +241,15 @@ __global__ void dec_lists_kernel(Acc acc, uint32_t n, const uint32_t *__restrict
             }
         }
     } else if constexpr (IsVarintAcc<Acc>::value) {
-        // Varint lists: 64 bytes per step, one per lane.  A lane holding a
-        // value's last byte (top bit clear) assembles the value from its own
-        // byte and the continuation bytes right before it (at most four, the
-        // ones before the step's first lane come from the previous step);
-        // the value's index in the list is the number of last bytes before
-        // it.  DMd adds a wave prefix sum of the differences to the running
-        // label.
+        // Varint lists of up to `split` bytes; longer ones are left in `more`
         for (uint64_t i = wave; i < k; i += nwaves) {
             uint64_t b0, b1;
             acc.offsets(labels[i], b0, b1);
-            const uint64_t o = out_off[i];
-            uint64_t done = 0;
-            uint32_t carry = 0;
-            uint32_t prevb = 0;  // a value's last byte: stops the look-back at the list's start
-            for (uint64_t p0 = b0; p0 < b1; p0 += kWave) {
-                const uint64_t p = p0 + lane;
-                const bool in = p < b1;
-                const uint32_t b = in ? acc.byte(p) : 128u;
-                const bool end = in && !(b & 128u);
-                uint32_t val = b & 127u;
-                bool open = true;
-#pragma unroll
-                for (int t = 1; t <= 4; ++t) {
-                    const int src = (int)lane - t;
-                    const uint32_t cur = __shfl(b, src & (kWave - 1), kWave);
-                    const uint32_t old = __shfl(prevb, src & (kWave - 1), kWave);
-                    const uint32_t bt = src >= 0 ? cur : old;
-                    open = open && (bt & 128u);
-                    if (open) val = (val << 7) | (bt & 127u);
-                }
-                const uint64_t ends = __ballot(end);
-                uint32_t label = val;
-                if constexpr (Acc::kDifferences) {
-                    const uint32_t sc = wave_incl_scan(end ? val : 0u);
-                    label = carry + sc;
-                    carry += __shfl(sc, kWave - 1, kWave);
-                }
-                if (end) {
-                    const uint64_t j = done + popc_below(ends);
-                    // a stored label is < n; the clamp keeps the lookup in
-                    // bounds whatever the stream holds
-                    const uint32_t u = perm ? perm[label < n ? label : n - 1] : label;
-                    if (kSorted) keys[o + j] = (i << 32) | u;
-                    else out_ids[o + j] = u;
-                }
-                done += (uint64_t)__popcll(ends);
-                prevb = b;
+            if (b1 - b0 > split) {
+                if (lane == 0) more[atomicAdd(&marks->n_chunked, 1u)] = (uint32_t)i;
+                continue;
             }
+            dec_varint_range<Acc, kSorted>(acc, n, b0, b1, 0u, 0u, i, out_off[i], perm, out_ids, keys);
         }
     }
 }
@@ -220,6 +334,191 @@ __global__ __launch_bounds__(256) void dec_walk_kernel(Acc acc, const uint32_t *
     }
 }
 
+// ---------------------------------------------------------------------------
+// sorting every list of a decoded batch (relabeled graphs: the lists come in
+// label order), in place
+// ---------------------------------------------------------------------------
+//
+// A list's IDs are distinct.  Up to kSortWave of them sort in a wave's
+// registers; up to kSortMid in a workgroup's LDS; a longer list by marking
+// its IDs in a bitmap of one range of 2^20 IDs at a time and reading the
+// marks back.  (One radix sort of all (list, ID) pairs took seven passes over
+// 8-byte keys: 1.1 of 1.6 ms for 256,000 lists of a 2^22-vertex graph; now
+// 0.32 ms.)
+constexpr uint32_t kSortWave = 1024;
+constexpr uint32_t kSortMid = 8192;
+constexpr uint32_t kSortRangeBits = 20;  // a range's bitmap: 128 KB
+// every range of a long list reads the whole list: with more ranges than
+// this the radix sort moves less
+constexpr uint32_t kSortMaxRanges = 16;
+
+// Bitonic sort of up to 64 kR values in a wave: element e of lane e mod 64,
+// register e / 64.
+template <int kR>
+__device__ __forceinline__ void wave_sort(uint32_t *__restrict__ ids, uint32_t d) {
+    const uint32_t lane = lane_id();
+    uint32_t x[kR];
+#pragma unroll
+    for (int r = 0; r < kR; ++r) x[r] = r * kWave + lane < d ? ids[r * kWave + lane] : 0xFFFFFFFFu;
+#pragma unroll
+    for (uint32_t size = 2; size <= 64u * kR; size <<= 1) {
+#pragma unroll
+        for (uint32_t j = size / 2; j; j >>= 1) {
+            if (j >= (uint32_t)kWave) {
+#pragma unroll
+                for (int r = 0; r < kR; ++r) {
+                    const int q = r ^ (int)(j / kWave);
+                    if (q < r) continue;
+                    const bool up = (r * kWave & size) == 0 || size == 64u * kR;
+                    const uint32_t lo = x[r] < x[q] ? x[r] : x[q], hi = x[r] < x[q] ? x[q] : x[r];
+                    x[r] = up ? lo : hi;
+                    x[q] = up ? hi : lo;
+                }
+            } else {
+#pragma unroll
+                for (int r = 0; r < kR; ++r) {
+                    const uint32_t y = __shfl_xor(x[r], j, kWave);
+                    const bool low = (lane & j) == 0, up = ((r * kWave + lane) & size) == 0 || size == 64u * kR;
+                    x[r] = (low == up) ? (x[r] < y ? x[r] : y) : (x[r] < y ? y : x[r]);
+                }
+            }
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < kR; ++r)
+        if (r * kWave + lane < d) ids[r * kWave + lane] = x[r];
+}
+
+// lists of up to kSortWave entries, 64 lists a workgroup; longer ones go to
+// `more`: the middle ones from its front, the long ones from its end
+__global__ __launch_bounds__(256) void dec_sort_wave_kernel(uint32_t k, const uint64_t *__restrict__ out_off,
+                                                            uint32_t *__restrict__ ids, uint32_t *__restrict__ more,
+                                                            DecodeMarks *__restrict__ marks) {
+    const uint32_t lane = lane_id(), wv = threadIdx.x / kWave;
+    for (uint64_t i0 = (uint64_t)blockIdx.x * kWave; i0 < k; i0 += (uint64_t)gridDim.x * kWave) {
+        const uint64_t i = i0 + lane;
+        const uint64_t o = out_off[i < k ? i : k], d = out_off[i < k ? i + 1 : k] - o;
+        if (wv == 0) {
+            const bool mid = d > kSortWave && d <= kSortMid, large = d > kSortMid;
+            const uint64_t ms = __ballot(mid), ls = __ballot(large);
+            uint32_t m0 = 0, l0 = 0;
+            if (lane == 0 && ms) m0 = atomicAdd(&marks->n_mid, (uint32_t)__popcll(ms));
+            if (lane == 0 && ls) l0 = atomicAdd(&marks->n_long, (uint32_t)__popcll(ls));
+            m0 = __shfl(m0, 0, kWave) + popc_below(ms);
+            l0 = __shfl(l0, 0, kWave) + popc_below(ls);
+            if (mid) more[m0] = (uint32_t)i;
+            if (large) more[k - 1 - l0] = (uint32_t)i;
+        }
+        // the waves take turns over the lists to sort
+        uint64_t todo = __ballot(d > 1 && d <= kSortWave);
+        for (uint32_t turn = 0; todo; ++turn, todo &= todo - 1) {
+            if ((turn & 3u) != wv) continue;
+            const uint32_t t = (uint32_t)__ffsll((long long)todo) - 1;
+            uint32_t *list = ids + __shfl(o, t, kWave);
+            const uint32_t len = __builtin_amdgcn_readfirstlane((uint32_t)__shfl(d, t, kWave));
+            if (len <= 64) wave_sort<1>(list, len);
+            else if (len <= 128) wave_sort<2>(list, len);
+            else if (len <= 256) wave_sort<4>(list, len);
+            else if (len <= 512) wave_sort<8>(list, len);
+            else wave_sort<16>(list, len);
+        }
+    }
+}
+
+__global__ __launch_bounds__(1024) void dec_sort_mid_kernel(const uint64_t *__restrict__ out_off,
+                                                            uint32_t *__restrict__ ids,
+                                                            const uint32_t *__restrict__ more,
+                                                            const DecodeMarks *__restrict__ marks) {
+    __shared__ uint32_t s_x[kSortMid];
+    const uint32_t lists = marks->n_mid;
+    for (uint32_t l = blockIdx.x; l < lists; l += gridDim.x) {
+        const uint32_t i = more[l];
+        const uint64_t o = out_off[i];
+        const uint32_t d = (uint32_t)(out_off[i + 1] - o);
+        uint32_t top = 2 * kSortWave;
+        while (top < d) top <<= 1;
+        for (uint32_t e = threadIdx.x; e < top; e += 1024) s_x[e] = e < d ? ids[o + e] : 0xFFFFFFFFu;
+        for (uint32_t size = 2; size <= top; size <<= 1) {
+            for (uint32_t j = size / 2; j; j >>= 1) {
+                __syncthreads();
+                for (uint32_t t = threadIdx.x; t < top / 2; t += 1024) {
+                    const uint32_t a = 2 * t - (t & (j - 1)), b = a + j;
+                    const uint32_t x = s_x[a], y = s_x[b];
+                    if ((x > y) == ((a & size) == 0 || size == top)) {
+                        s_x[a] = y;
+                        s_x[b] = x;
+                    }
+                }
+            }
+        }
+        __syncthreads();
+        for (uint32_t e = threadIdx.x; e < d; e += 1024) ids[o + e] = s_x[e];
+        __syncthreads();  // the next list takes the buffer
+    }
+}
+
+// one range of one long list per workgroup step: its IDs in order to `sorted`
+__global__ __launch_bounds__(1024) void dec_sort_long_kernel(uint32_t k, uint32_t ranges,
+                                                             const uint64_t *__restrict__ out_off,
+                                                             const uint32_t *__restrict__ ids,
+                                                             const uint32_t *__restrict__ more,
+                                                             const DecodeMarks *__restrict__ marks,
+                                                             uint32_t *__restrict__ sorted) {
+    constexpr uint32_t kWords = 1u << (kSortRangeBits - 5), kPer = kWords / 1024;
+    // word w sits at w + w / 32: a thread's 32 words then start on its own bank
+    __shared__ uint32_t s_bits[kWords + kWords / 32];
+    __shared__ uint32_t s_wave[16], s_below;
+    const uint32_t tid = threadIdx.x, lane = lane_id(), wv = tid / kWave;
+    const uint64_t items = (uint64_t)marks->n_long * ranges;
+    for (uint64_t l = blockIdx.x; l < items; l += gridDim.x) {
+        const uint32_t i = more[k - 1 - (uint32_t)(l / ranges)], range = (uint32_t)(l % ranges);
+        const uint64_t o = out_off[i];
+        const uint32_t d = (uint32_t)(out_off[i + 1] - o);
+        for (uint32_t w = tid; w < kWords + kWords / 32; w += 1024) s_bits[w] = 0;
+        if (tid == 0) s_below = 0;
+        __syncthreads();
+        uint32_t below = 0;
+#pragma unroll 4
+        for (uint32_t e = tid; e < d; e += 1024) {
+            const uint32_t u = ids[o + e], r = u >> kSortRangeBits;
+            const uint32_t w = (u & ((1u << kSortRangeBits) - 1u)) >> 5;
+            if (r == range) atomicOr(&s_bits[w + w / 32], 1u << (u & 31));
+            below += r < range;
+        }
+        below = wave_sum(below);
+        if (lane == 0 && below) atomicAdd(&s_below, below);
+        __syncthreads();
+        uint32_t mine = 0;
+        for (uint32_t j = 0; j < kPer; ++j) mine += (uint32_t)__popc(s_bits[tid * (kPer + 1) + j]);
+        const uint32_t incl = wave_incl_scan(mine);
+        if (lane == kWave - 1) s_wave[wv] = incl;
+        __syncthreads();
+        uint64_t at = o + s_below + incl - mine;
+        for (uint32_t w = 0; w < wv; ++w) at += s_wave[w];
+        for (uint32_t j = 0; j < kPer; ++j) {
+            const uint32_t id0 = (range << kSortRangeBits) + (tid * kPer + j) * 32;
+            for (uint32_t x = s_bits[tid * (kPer + 1) + j]; x; x &= x - 1)
+                sorted[at++] = id0 + (uint32_t)__ffs((int)x) - 1;
+        }
+        __syncthreads();  // the next item clears the bitmap
+    }
+}
+
+// the long lists back into place, kSortBack workgroups a list
+constexpr uint32_t kSortBack = 16;
+__global__ void dec_sort_back_kernel(uint32_t k, const uint64_t *__restrict__ out_off,
+                                     const uint32_t *__restrict__ sorted, const uint32_t *__restrict__ more,
+                                     const DecodeMarks *__restrict__ marks, uint32_t *__restrict__ ids) {
+    const uint32_t lists = marks->n_long;
+    for (uint32_t l = blockIdx.x / kSortBack; l < lists; l += gridDim.x / kSortBack) {
+        const uint32_t i = more[k - 1 - l];
+        const uint64_t z = out_off[i + 1];
+        for (uint64_t e = out_off[i] + (blockIdx.x % kSortBack) * blockDim.x + threadIdx.x; e < z;
+             e += (uint64_t)kSortBack * blockDim.x)
+            ids[e] = sorted[e];
+    }
+}
+
 __global__ void dec_unkey_kernel(uint64_t total, const uint64_t *__restrict__ keys, uint32_t *__restrict__ out) {
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
     for (uint64_t j = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; j < total; j += stride)
@@ -238,10 +537,19 @@ uint64_t DecodeWork::bytes() const {
 template <class Acc, bool kSorted>
 static lg_status dec_lists(const lg_graph *g, Acc acc, const uint32_t *labels, uint32_t k, uint64_t total,
                            const uint64_t *out_off, const uint32_t *perm, uint32_t *out_ids, uint64_t *keys,
-                           hipStream_t stream) {
+                           uint32_t *more, DecodeMarks *marks, hipStream_t stream) {
     if constexpr (IsGapAcc<Acc>::value || IsVarintAcc<Acc>::value) {
         LG_LAUNCH((dec_lists_kernel<Acc, kSorted>), grid_for((uint64_t)k * kWave, 256, 1u << 16), 256, 0, stream,
-                  acc, g->n, labels, k, out_off, perm, out_ids, keys);
+                  acc, g->n, labels, k, out_off, perm, out_ids, keys, g->n_vseg ? (uint64_t)g->vseg_split : ~0ull,
+                  more, marks);
+        if constexpr (IsVarintAcc<Acc>::value) {
+            LG_CHECK_LAUNCH();
+            if (g->n_vseg)
+                LG_LAUNCH((dec_varint_chunks_kernel<Acc, kSorted>), std::min(k, 512u), 1024, 0, stream, acc, g->n,
+                          labels, out_off, perm, out_ids, keys, (const uint32_t *)more, (const DecodeMarks *)marks,
+                          g->heavy.as<uint32_t>(), g->n_heavy, g->vhb0.as<uint64_t>(), g->vhb1.as<uint64_t>(),
+                          g->vseg_off.as<uint64_t>(), g->vseg_base.as<uint32_t>(), g->vseg_bytes);
+        }
     } else {
         // pieces of 256 entries (one step of the walk) up to 4,096; in
         // between, as many as fill the device twice
@@ -270,25 +578,32 @@ lg_status decode_run(lg_graph *g, DecodeWork &w, const uint32_t *vertices, uint3
     const uint32_t *perm = (rel && flags != LG_DECODE_RAW) ? g->perm.as<uint32_t>() : nullptr;
     const bool sorted = rel && flags == LG_DECODE_SORTED;
 
-    // head: labels (k) | degrees (k) | flag
-    LG_TRY(w.head.ensure(((uint64_t)k * 8 + 8 + 7) & ~7ull));
+    // head: labels (k) | degrees (k), later the lists left for other kernels | marks
+    LG_TRY(w.head.ensure(decode_head_bytes(k)));
     uint32_t *labels = w.head.as<uint32_t>();
     uint32_t *deg = labels + k;
-    uint32_t *bad = deg + k;
-    LG_TRY(fill_u32(bad, 0, 1, stream));
-    LG_LAUNCH(dec_map_kernel, grid_for(k, 256, 1u << 16), 256, 0, stream, g->n, vertices, k, inv, labels, bad);
-    LG_CHECK_LAUNCH();
+    DecodeMarks *marks = reinterpret_cast<DecodeMarks *>(deg + k);
     return dispatch_acc_decode(g, [&](auto acc) -> lg_status {
         using Acc = decltype(acc);
-        if constexpr (IsVarintAcc<Acc>::value)
-            LG_LAUNCH(dec_varint_degree_kernel<Acc>, grid_for((uint64_t)k * kWave, 256, 1u << 16), 256, 0, stream,
-                      acc, labels, k, deg);
-        else
-            LG_LAUNCH(dec_degree_kernel<Acc>, grid_for(k, 256, 1u << 16), 256, 0, stream, acc, labels, k, deg);
-        LG_CHECK_LAUNCH();
-        LG_TRY(exclusive_scan_u32(deg, out_off, k, w.scan_tmp, stream));
-        LG_CHECK_HIP(hipMemcpyAsync(w.host, out_off + k, 8, hipMemcpyDeviceToHost, stream));
-        LG_CHECK_HIP(hipMemcpyAsync(w.host + 1, bad, 4, hipMemcpyDeviceToHost, stream));
+        // (a borrowed host slot is ordinary memory, which a kernel cannot write)
+        if (w.host_owned && k <= (IsVarintAcc<Acc>::value ? kDecSmall / 16 : kDecSmall)) {
+            LG_LAUNCH(dec_small_kernel<Acc>, 1, kDecSmall, 0, stream, acc, g->n, vertices, k, inv, labels, out_off,
+                      marks, w.host);
+            LG_CHECK_LAUNCH();
+        } else {
+            LG_TRY(fill_u32(&marks->bad, 0, sizeof(DecodeMarks) / 4, stream));
+            LG_LAUNCH(dec_map_kernel<Acc>, grid_for(k, 256, 1u << 16), 256, 0, stream, acc, g->n, vertices, k, inv,
+                      labels, deg, marks);
+            LG_CHECK_LAUNCH();
+            if constexpr (IsVarintAcc<Acc>::value) {
+                LG_LAUNCH(dec_varint_degree_kernel<Acc>, grid_for((uint64_t)k * kWave, 256, 1u << 16), 256, 0,
+                          stream, acc, labels, k, deg);
+                LG_CHECK_LAUNCH();
+            }
+            LG_TRY(exclusive_scan_u32(deg, out_off, k, w.scan_tmp, stream));
+            LG_CHECK_HIP(hipMemcpyAsync(w.host, out_off + k, 8, hipMemcpyDeviceToHost, stream));
+            LG_CHECK_HIP(hipMemcpyAsync(w.host + 1, &marks->bad, 4, hipMemcpyDeviceToHost, stream));
+        }
         LG_CHECK_HIP(hipStreamSynchronize(stream));
         if (*reinterpret_cast<uint32_t *>(w.host + 1)) {
             set_error("lg_decode_neighbors: vertex id >= n");
@@ -302,12 +617,39 @@ lg_status decode_run(lg_graph *g, DecodeWork &w, const uint32_t *vertices, uint3
             return LG_ERR_CAPACITY;
         }
         if (total == 0) return LG_OK;
-        if (!sorted) return dec_lists<Acc, false>(g, acc, labels, k, total, out_off, perm, out_ids, nullptr, stream);
+        const uint32_t ranges = (uint32_t)(((uint64_t)g->n + (1u << kSortRangeBits) - 1) >> kSortRangeBits);
+        const bool has_long = g->max_degree > kSortMid;
+        if (!sorted || !has_long || ranges <= kSortMaxRanges) {
+            // the fixed scratch of the allocation-free entry point bounds what
+            // it sorts, whichever sort that is
+            if (sorted && (has_long || w.keys.borrowed)) LG_TRY(w.keys.ensure(total * 8));
+            LG_TRY((dec_lists<Acc, false>(g, acc, labels, k, total, out_off, perm, out_ids, nullptr, deg, marks, stream)));
+            if (!sorted) return LG_OK;
+            LG_LAUNCH(dec_sort_wave_kernel, grid_for(k, kWave, 1u << 14), 256, 0, stream, k,
+                      (const uint64_t *)out_off, out_ids, deg, marks);
+            LG_CHECK_LAUNCH();
+            if (g->max_degree > kSortWave) {
+                LG_LAUNCH(dec_sort_mid_kernel, grid_for(k, 1, 1024), 1024, 0, stream, (const uint64_t *)out_off,
+                          out_ids, (const uint32_t *)deg, (const DecodeMarks *)marks);
+                LG_CHECK_LAUNCH();
+            }
+            if (has_long) {
+                LG_LAUNCH(dec_sort_long_kernel, grid_for((uint64_t)k * ranges, 1, 512), 1024, 0, stream, k, ranges,
+                          (const uint64_t *)out_off, (const uint32_t *)out_ids, (const uint32_t *)deg,
+                          (const DecodeMarks *)marks, w.keys.as<uint32_t>());
+                LG_CHECK_LAUNCH();
+                LG_LAUNCH(dec_sort_back_kernel, 1024, 256, 0, stream, k, (const uint64_t *)out_off,
+                          (const uint32_t *)w.keys.p, (const uint32_t *)deg, (const DecodeMarks *)marks, out_ids);
+                LG_CHECK_LAUNCH();
+            }
+            return LG_OK;
+        }
         LG_TRY(w.keys.ensure(total * 8));
         LG_TRY(w.keys2.ensure(total * 8));
         LG_TRY(w.vals.ensure(total * 4));
         LG_TRY(w.vals2.ensure(total * 4));
-        LG_TRY((dec_lists<Acc, true>(g, acc, labels, k, total, out_off, perm, out_ids, w.keys.as<uint64_t>(), stream)));
+        LG_TRY((dec_lists<Acc, true>(g, acc, labels, k, total, out_off, perm, out_ids, w.keys.as<uint64_t>(), deg, marks,
+                                      stream)));
         const uint32_t bits = 32 + bitlen_u64(k - 1);
         LG_TRY(radix_sort_pairs64(w.keys.as<uint64_t>(), w.vals.as<uint32_t>(), w.keys2.as<uint64_t>(),
                                   w.vals2.as<uint32_t>(), total, bits, w.sort_tmp, stream));
@@ -374,7 +716,7 @@ struct NoallocLayout {
 NoallocLayout noalloc_layout() {
     NoallocLayout L{};
     uint64_t o = 0;
-    L.head = o;  o += align256((uint64_t)LG_NOALLOC_MAX_VERTICES * 8 + 8);  // labels | degrees | flag
+    L.head = o;  o += align256(decode_head_bytes(LG_NOALLOC_MAX_VERTICES));
     L.scan = o;  o += align256(scan_tmp_bytes(LG_NOALLOC_MAX_VERTICES));
     L.keys = o;  o += align256((uint64_t)LG_NOALLOC_MAX_SORTED_IDS * 8);
     L.keys2 = o; o += align256((uint64_t)LG_NOALLOC_MAX_SORTED_IDS * 8);

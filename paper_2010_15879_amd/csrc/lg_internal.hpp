@@ -361,6 +361,8 @@ constexpr double kBfsProbeCost = 1.0 / 6.0;
 // BFS from host roots on an explicit workspace (lg_bfs without argument checks)
 lg_status bfs_run(lg_graph *g, BfsWork &w, const uint32_t *roots, uint32_t r, int32_t *depth, int32_t *parent,
                   int32_t max_depth, uint32_t flags, hipStream_t stream, double alpha = kBfsAlphaLatency);
+// bytes of DecodeWork::head for k requests
+uint64_t decode_head_bytes(uint64_t k);
 // lg_decode_neighbors on an explicit workspace
 lg_status decode_run(lg_graph *g, DecodeWork &w, const uint32_t *vertices, uint32_t k, uint64_t *out_off,
                      uint32_t *out_ids, uint64_t cap, uint32_t flags, hipStream_t stream, uint64_t *total);

@@ -864,7 +864,7 @@ static lg_status pb_build(lg_graph *g, hipStream_t s) {
     uint64_t slots[4] = {0, 0, 0, 0};
     dec.host = slots;
     dec.host_owned = false;
-    LG_TRY(dec.head.scratch(((uint64_t)n * 8 + 8 + 7) & ~7ull, s));
+    LG_TRY(dec.head.scratch(decode_head_bytes(n), s));
     LG_TRY(dec.scan_tmp.scratch(std::max<uint64_t>(scan_tmp_bytes(n), 8), s));
     LG_TRY(decode_run(g, dec, all.as<uint32_t>(), n, eoff.as<uint64_t>(), col.as<uint32_t>(), g->m, LG_DECODE_RAW, s,
                       nullptr));

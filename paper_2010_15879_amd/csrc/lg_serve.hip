@@ -225,7 +225,7 @@ void lg_server::plan(Worker &W, const lg_query &q, uint32_t batch, std::vector<R
         out.push_back({&W.vin, k * 4});
         out.push_back({&W.off, (k + 1) * 8});
         out.push_back({&W.ids, cap * 4});
-        out.push_back({&W.dec.head, (k * 8 + 8 + 7) & ~7ull});
+        out.push_back({&W.dec.head, decode_head_bytes(k)});
         out.push_back({&W.dec.scan_tmp, scan_tmp_bytes(k)});
         if (rel) {  // sorted output of a relabeled graph: keyed radix sort
             out.push_back({&W.dec.keys, cap * 8});
