@@ -188,12 +188,20 @@ class Graph:
         self._h = C.c_void_p(handle)
         self.n = n
         self.m = m
+        self._mean_list = None
 
     @property
     def handle(self) -> C.c_void_p:
         if not self._h:
             raise ValueError("graph already freed")
         return self._h
+
+    @property
+    def mean_list(self) -> float:
+        """Mean list length of the vertices with edges."""
+        if self._mean_list is None:
+            self._mean_list = self.m / max(1, self.n - self.info()["isolated"])
+        return self._mean_list
 
     def free(self):
         if self._h:
@@ -288,6 +296,9 @@ def sssp(g: Graph, root: int, delta: int = 0, stream=None) -> torch.Tensor:
     return dist
 
 
+_DECODE_GUESS_MAX = 1 << 24  # ids a decode without a capacity allocates ahead
+
+
 def decode_neighbors(g: Graph, vertices: torch.Tensor, flags="sorted", cap: Optional[int] = None, stream=None):
     """Returns (offsets int64[k+1], ids int32[total]) on the device."""
     k = vertices.numel()
@@ -296,8 +307,16 @@ def decode_neighbors(g: Graph, vertices: torch.Tensor, flags="sorted", cap: Opti
     vptr = _dev_ptr(vertices, torch.int32, "vertices") if k else None
     s = _stream(stream)
     if cap is None:
-        st = lib().lg_decode_neighbors(g.handle, vptr, k, off.data_ptr(), None, 0, DECODE_FLAGS[flags], s)
-        if st not in (LG_OK, LG_ERR_CAPACITY):
+        # room for a quarter more than k lists of the mean length: one call
+        # then serves most requests.  A request that needs more has its
+        # lengths counted by that call and is decoded by a second one (64
+        # lists of a 2^16-vertex graph: two calls 79 us, one 51 us).
+        cap = min(int(1.25 * k * g.mean_list) + 256, _DECODE_GUESS_MAX)
+        ids = torch.empty(cap, dtype=torch.int32, device=dev)
+        st = lib().lg_decode_neighbors(g.handle, vptr, k, off.data_ptr(), ids.data_ptr(), cap, DECODE_FLAGS[flags], s)
+        if st == LG_OK:
+            return off, ids[: int(off[-1].item())]
+        if st != LG_ERR_CAPACITY:
             _check(st)
         cap = int(off[-1].item())
     ids = torch.empty(max(cap, 1), dtype=torch.int32, device=dev)
