@@ -273,8 +273,8 @@ lg_status lg_encode_weighted(uint32_t n, uint64_t m, const uint64_t *row_offsets
  *   dist     dev, uint64[n]; UINT64_MAX for vertices the root does not reach
  *
  * Returns LG_ERR_UNSUPPORTED for an unweighted graph.  Synchronous: the
- * host reads each step's frontier size back to drive the buckets, and the
- * call returns once dist is written.  The workspace is kept with the graph
+ * device drives the buckets, the host queues a few steps at a time and looks
+ * whether they ended the search, and the call returns once dist is written.  The workspace is kept with the graph
  * until lg_free; calls on the same graph from several threads run one after
  * the other (each holds the graph's workspace for its whole duration).
  */

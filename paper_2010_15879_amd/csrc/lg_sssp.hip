@@ -14,11 +14,12 @@
 //            degrees, 64 consecutive edges per wave step: nd = dist(u) + w;
 //            an atomic minimum on dist(v), and v is marked when it lowered it
 // An empty frontier moves to the bucket of the smallest marked distance;
-// none marked ends the search.  Every vertex relaxed from a distance d
+// none marked ends the search.  The device takes these decisions itself
+// (SsspState), so that the host queues several steps before it looks.  Every vertex relaxed from a distance d
 // reaches the final distances of the paths through it, so the result is the
 // exact distances whatever delta and the order of the atomics.
 #include <algorithm>
-
+#include <cstring>
 #include <mutex>
 
 #include "lg_device.hpp"
@@ -103,14 +104,28 @@ lg_status dispatch_wacc(const lg_graph *g, Fn &&fn) {
 
 constexpr uint64_t kInfDist = ~0ull;
 
+// Where the search stands (device memory, read back by the host).
+struct SsspState {
+    unsigned long long hi;     // distances below it are collected
+    unsigned long long count;  // frontier vertices of this step
+    unsigned long long steps;
+    unsigned long long done;   // 1: no vertex is marked any more, 2: the step bound was hit
+};
+// What a collecting workgroup found in its words.
+struct SsspPart {
+    unsigned long long edges;  // entries of the vertices taken
+    unsigned long long left;   // the smallest distance staying marked
+    unsigned long long count;  // vertices taken
+};
+
 struct SsspWork {
     DevBuf upd;                         // bitmap, one bit per vertex
-    DevBuf qv, qw, qdeg;                // frontier: vertex, ID width, degree
-    DevBuf qstart, qdist, qoff;         // list start, distance, exclusive scan of qdeg
-    DevBuf ctr;                         // [0] frontier size, [1] smallest distance left marked
-    DevBuf tmask, wcnt, woff;           // per bitmap word: vertices taken, their count, queue position
+    DevBuf qv, qw;                      // frontier: vertex, ID width
+    DevBuf qstart, qdist, qoff;         // list start, distance, entries of the vertices before
+    DevBuf state;                       // SsspState
+    DevBuf tmask, wdeg;                 // per bitmap word: vertices taken, their degrees' sum
+    DevBuf parts;                       // SsspPart of every collecting workgroup
     DevBuf dl;                          // label-space distances (relabeled graphs)
-    DevBuf scan_tmp;
     uint64_t *host = nullptr;           // pinned readback slots
     SsspWork() = default;
     SsspWork(const SsspWork &) = delete;
@@ -119,8 +134,8 @@ struct SsspWork {
         if (host) (void)hipHostFree(host);
     }
     uint64_t bytes() const {
-        return upd.bytes + qv.bytes + qw.bytes + qdeg.bytes + qstart.bytes + qdist.bytes + qoff.bytes + ctr.bytes +
-               tmask.bytes + wcnt.bytes + woff.bytes + dl.bytes + scan_tmp.bytes;
+        return upd.bytes + qv.bytes + qw.bytes + qstart.bytes + qdist.bytes + qoff.bytes +
+               state.bytes + tmask.bytes + wdeg.bytes + parts.bytes + dl.bytes;
     }
 };
 
@@ -135,101 +150,226 @@ lg_status sssp_free(lg_graph *g) {
 // The root arrives as its original ID and is mapped to its label (inv,
 // when relabeled) here.
 __global__ void sssp_init_kernel(uint32_t n, uint64_t words, uint32_t root_id, const uint32_t *__restrict__ inv,
-                                 uint64_t *__restrict__ dist, uint64_t *__restrict__ upd) {
+                                 uint64_t first_hi, uint64_t *__restrict__ dist, uint64_t *__restrict__ upd,
+                                 SsspState *__restrict__ state) {
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
     const uint64_t total = n > words ? n : words;
     const uint32_t root = inv ? inv[root_id] : root_id;
+    if (blockIdx.x == 0 && threadIdx.x == 0) *state = SsspState{first_hi, 0, 0, 0};
     for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += stride) {
         if (i < n) dist[i] = i == root ? 0ull : kInfDist;
         if (i < words) upd[i] = i == (root >> 6) ? 1ull << (root & 63) : 0ull;
     }
 }
 
-// ctr[0] = 0 (frontier size), ctr[1] = no marked distance left
-__global__ void sssp_ctr_kernel(unsigned long long *__restrict__ ctr) {
-    if (threadIdx.x == 0) {
-        ctr[0] = 0ull;
-        ctr[1] = kInfDist;
-    }
-}
-
-// The frontier is compacted without a shared counter (one atomic add per
-// wave on a single address serializes the whole pass): a count pass takes
-// each word's marked vertices below the bound out of the bitmap and counts
-// them, an exclusive scan over the words gives every word its queue
-// position, and a write pass fills the queue.  Every marked vertex has edges
-// (it was reached over one) but the root, which may have none: it is then
-// alone in the first frontier, which holds no edges.
+// The frontier is compacted without a shared counter (single-address atomics
+// from thousands of workgroups took 20 us a step).  Every workgroup has a
+// fixed range of bitmap words.  The count pass takes each word's marked
+// vertices below the bound out of the bitmap and leaves the range's vertices,
+// entries and smallest distance left marked; the write pass sums the ranges
+// before its own (at most kCollectParts of them) and places its vertices with
+// the running entry count the relax pass walks by.  Two launches for what
+// were seven (a reset, the count, two scans of up to three launches), and no
+// read-back between them: Kronecker 2^20
+// vertices, 20 steps: 2.55 -> 1.66 ms.  Every
+// marked vertex has edges (it was reached over one) but the root, which may
+// have none: it is then alone in the first frontier, which holds no edges.
 constexpr int kCollectThreads = 256;
-constexpr uint32_t kCollectBlocks = 4096;
+constexpr uint32_t kCollectWaves = kCollectThreads / kWave;
+constexpr uint64_t kCollectParts = 1024;
 
+template <class Acc>
 __global__ __launch_bounds__(kCollectThreads) void sssp_count_kernel(
-    uint32_t n, uint64_t words, uint64_t hi, const uint64_t *__restrict__ dist, uint64_t *__restrict__ upd,
-    uint64_t *__restrict__ tmask, uint32_t *__restrict__ cnt, unsigned long long *__restrict__ ctr) {
-    __shared__ unsigned long long s_left[kCollectThreads / kWave];
-    const uint32_t lane = lane_id();
-    const uint64_t wave = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave;
-    const uint64_t nwaves = ((uint64_t)gridDim.x * blockDim.x) / kWave;
+    Acc acc, uint32_t n, uint64_t words, uint64_t per, const SsspState *__restrict__ state,
+    const uint64_t *__restrict__ dist, uint64_t *__restrict__ upd, uint64_t *__restrict__ tmask,
+    uint64_t *__restrict__ wdeg, SsspPart *__restrict__ parts) {
+    if (state->done) return;
+    __shared__ unsigned long long s_left[kCollectWaves], s_edges[kCollectWaves], s_count[kCollectWaves];
+    const uint64_t hi = state->hi;
+    const uint32_t lane = lane_id(), wv = threadIdx.x / kWave;
+    const uint64_t q0 = (uint64_t)blockIdx.x * per;
+    const uint64_t q1 = q0 + per < words ? q0 + per : words;
     uint64_t left = kInfDist;  // the smallest distance staying marked
-    for (uint64_t q = wave; q < words; q += nwaves) {
-        const uint64_t bits = upd[q];
-        uint64_t take_m = 0;
-        if (bits) {  // same for every lane
-            const uint64_t v = q * 64 + lane;
-            const bool set = ((bits >> lane) & 1ull) && v < n;
-            const uint64_t d = set ? dist[v] : kInfDist;
-            const bool take = set && d < hi;
-            take_m = __ballot(take);
-            if (set && !take && d < left) left = d;
-            if (lane == 0 && take_m) upd[q] = bits & ~take_m;
+    unsigned long long edges = 0, count = 0;
+    // a wave holds every fourth word of 256 (so that a range's marked words
+    // spread over the waves), then takes the marked ones two at a time, their
+    // vertices' distances and list lengths in flight together
+    constexpr int kWords = 2;
+    for (uint64_t b = q0; b < q1; b += kCollectThreads) {
+        const uint64_t q = b + lane * kCollectWaves + wv;
+        const uint64_t mine = q < q1 ? upd[q] : 0ull;
+        uint64_t my_take = 0, my_deg = 0;
+        for (uint64_t todo = __ballot(mine != 0ull); todo;) {
+            uint32_t t[kWords];
+            uint64_t d[kWords];
+            bool set[kWords], take[kWords];
+#pragma unroll
+            for (int k = 0; k < kWords; ++k) {
+                const bool any = todo != 0;
+                t[k] = any ? (uint32_t)__ffsll((long long)todo) - 1 : 0u;
+                todo &= todo - 1;
+                const uint64_t bits = __shfl(mine, t[k], kWave);
+                const uint64_t v = (b + t[k] * kCollectWaves + wv) * 64 + lane;
+                set[k] = any && ((bits >> lane) & 1ull) && v < n;
+                d[k] = set[k] ? dist[v] : kInfDist;
+            }
+            uint32_t deg[kWords];
+#pragma unroll
+            for (int k = 0; k < kWords; ++k) {
+                take[k] = set[k] && d[k] < hi;
+                if (set[k] && !take[k] && d[k] < left) left = d[k];
+                const uint64_t v = (b + t[k] * kCollectWaves + wv) * 64 + lane;
+                deg[k] = take[k] ? acc.info((uint32_t)v).deg : 0u;
+            }
+#pragma unroll
+            for (int k = 0; k < kWords; ++k) {
+                const uint64_t take_m = __ballot(take[k]);
+                const uint64_t sum = wave_sum((unsigned long long)deg[k]);
+                if (take_m && lane == t[k]) {
+                    my_take = take_m;
+                    my_deg = sum;
+                }
+            }
         }
-        if (lane == 0) {
-            tmask[q] = take_m;
-            cnt[q] = (uint32_t)__popcll(take_m);
+        if (q < q1) {
+            tmask[q] = my_take;
+            if (my_take) {
+                wdeg[q] = my_deg;
+                upd[q] = mine & ~my_take;
+            }
         }
+        edges += my_deg;
+        count += (unsigned long long)__popcll(my_take);
     }
 #pragma unroll
     for (int s = kWave / 2; s > 0; s >>= 1) {
         const uint64_t o = __shfl_xor(left, s, kWave);
         left = o < left ? o : left;
     }
-    if (lane == 0) s_left[threadIdx.x / kWave] = left;
+    edges = wave_sum(edges);
+    count = wave_sum(count);
+    if (lane == 0) {
+        s_left[wv] = left;
+        s_edges[wv] = edges;
+        s_count[wv] = count;
+    }
     __syncthreads();
     if (threadIdx.x == 0) {
-        unsigned long long m = s_left[0];
-        for (int i = 1; i < kCollectThreads / kWave; ++i) m = s_left[i] < m ? s_left[i] : m;
-        if (m != kInfDist) atomicMin(&ctr[1], m);
+        SsspPart p{0, kInfDist, 0};
+        for (uint32_t w = 0; w < kCollectWaves; ++w) {
+            p.edges += s_edges[w];
+            p.count += s_count[w];
+            p.left = s_left[w] < p.left ? s_left[w] : p.left;
+        }
+        parts[blockIdx.x] = p;
     }
+}
+
+// exclusive prefix over a workgroup's threads, and the total
+__device__ __forceinline__ uint64_t collect_scan(uint64_t x, uint64_t *s_wave, uint64_t &total) {
+    const uint32_t lane = lane_id(), wv = threadIdx.x / kWave;
+    const uint64_t incl = wave_incl_scan(x);
+    __syncthreads();  // the last use of s_wave is over
+    if (lane == kWave - 1) s_wave[wv] = incl;
+    __syncthreads();
+    uint64_t base = 0;
+    total = 0;
+    for (uint32_t w = 0; w < kCollectWaves; ++w) {
+        if (w < wv) base += s_wave[w];
+        total += s_wave[w];
+    }
+    return base + incl - x;
 }
 
 template <class Acc>
 __global__ __launch_bounds__(kCollectThreads) void sssp_write_kernel(
-    Acc acc, uint32_t n, uint64_t words, const uint64_t *__restrict__ dist, const uint64_t *__restrict__ tmask,
-    const uint64_t *__restrict__ woff, uint32_t *__restrict__ qv, uint64_t *__restrict__ qstart, uint32_t *__restrict__ qw,
-    uint32_t *__restrict__ qdeg, uint64_t *__restrict__ qdist, unsigned long long *__restrict__ ctr) {
-    const uint32_t lane = lane_id();
-    const uint64_t wave = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave;
-    const uint64_t nwaves = ((uint64_t)gridDim.x * blockDim.x) / kWave;
-    if (blockIdx.x == 0 && threadIdx.x == 0) ctr[0] = woff[words];  // frontier size
-    for (uint64_t q = wave; q < words; q += nwaves) {
-        const uint64_t m = tmask[q];
-        if (!m) continue;  // same for every lane
-        if ((m >> lane) & 1ull) {
-            const uint64_t v = q * 64 + lane;
-            const WInfo vi = acc.info((uint32_t)v);
-            const uint64_t pos = woff[q] + popc_below(m);
-            qv[pos] = (uint32_t)v;
-            qstart[pos] = vi.start;
-            qw[pos] = vi.w;
-            qdeg[pos] = vi.deg;
-            qdist[pos] = dist[v];
+    Acc acc, uint64_t words, uint64_t per, uint64_t delta, uint64_t max_steps, const uint64_t *__restrict__ dist,
+    const uint64_t *__restrict__ tmask, const uint64_t *__restrict__ wdeg, const SsspPart *__restrict__ parts,
+    uint32_t *__restrict__ qv, uint64_t *__restrict__ qstart, uint32_t *__restrict__ qw, uint64_t *__restrict__ qdist,
+    uint64_t *__restrict__ qoff, SsspState *__restrict__ state) {
+    __shared__ uint64_t s_wave[kCollectWaves];
+    __shared__ uint64_t s_pos[kCollectThreads], s_off[kCollectThreads], s_take[kCollectThreads];
+    __shared__ unsigned long long s_left;
+    // (a block that finds `done` set by block 0 below had nothing to write)
+    if (state->done) return;
+    const uint32_t lane = lane_id(), wv = threadIdx.x / kWave;
+    // the ranges before this one
+    uint64_t cnt = 0, edges = 0, all_cnt = 0, all_edges = 0, left = kInfDist;
+    for (uint32_t i = threadIdx.x; i < gridDim.x; i += kCollectThreads) {
+        const SsspPart p = parts[i];
+        if (i < blockIdx.x) {
+            cnt += p.count;
+            edges += p.edges;
         }
+        all_cnt += p.count;
+        all_edges += p.edges;
+        left = p.left < left ? p.left : left;
+    }
+    if (threadIdx.x == 0) s_left = kInfDist;
+    uint64_t pos0, off0, total_cnt, total_edges;
+    (void)collect_scan(cnt, s_wave, pos0);
+    (void)collect_scan(edges, s_wave, off0);
+    if (blockIdx.x == 0) {
+        (void)collect_scan(all_cnt, s_wave, total_cnt);
+        (void)collect_scan(all_edges, s_wave, total_edges);
+        if (left != kInfDist) atomicMin(&s_left, (unsigned long long)left);
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            const unsigned long long steps = state->steps + 1;
+            state->steps = steps;
+            qoff[total_cnt] = total_edges;
+            if (steps > max_steps) {  // the queue may be left unwritten: nothing is relaxed
+                state->count = 0;
+                state->done = 2;
+            } else {
+                state->count = total_cnt;
+                if (!total_cnt) {  // the next bucket with a marked vertex
+                    const uint64_t k = s_left / delta;
+                    if (s_left == kInfDist) state->done = 1;
+                    else state->hi = k + 1 > kInfDist / delta ? kInfDist : (k + 1) * delta;
+                }
+            }
+        }
+    }
+    const uint64_t q0 = (uint64_t)blockIdx.x * per;
+    const uint64_t q1 = q0 + per < words ? q0 + per : words;
+    for (uint64_t b = q0; b < q1; b += kCollectThreads) {
+        const uint64_t q = b + threadIdx.x;
+        const uint64_t take = q < q1 ? tmask[q] : 0ull;
+        const uint64_t deg = take ? wdeg[q] : 0ull;
+        uint64_t tile_cnt, tile_edges;
+        const uint64_t at = collect_scan((uint64_t)__popcll(take), s_wave, tile_cnt);
+        const uint64_t off = collect_scan(deg, s_wave, tile_edges);
+        s_take[threadIdx.x] = take;
+        s_pos[threadIdx.x] = pos0 + at;
+        s_off[threadIdx.x] = off0 + off;
+        __syncthreads();
+        const uint32_t tile = q1 - b < (uint64_t)kCollectThreads ? (uint32_t)(q1 - b) : (uint32_t)kCollectThreads;
+        for (uint32_t t = wv; t < tile; t += kCollectWaves) {
+            const uint64_t m = s_take[t];
+            if (!m) continue;  // same for every lane
+            const bool in = (m >> lane) & 1ull;
+            const uint64_t v = (b + t) * 64 + lane;
+            const WInfo vi = in ? acc.info((uint32_t)v) : WInfo{0, 0, 0};
+            const uint64_t incl = wave_incl_scan((uint64_t)vi.deg);
+            if (in) {
+                const uint64_t pos = s_pos[t] + popc_below(m);
+                qv[pos] = (uint32_t)v;
+                qstart[pos] = vi.start;
+                qw[pos] = vi.w;
+                qdist[pos] = dist[v];
+                qoff[pos] = s_off[t] + incl - vi.deg;
+            }
+        }
+        pos0 += tile_cnt;
+        off0 += tile_edges;
+        __syncthreads();  // the next tile rewrites the words' places
     }
 }
 
 // Edge t of the frontier belongs to slot s with qoff[s] <= t < qoff[s + 1];
 // every slot holds at least one edge.  Each wave takes a contiguous range
-// of edges, 64 per step, and finds its first slot by one binary search.  In
+// of edges, 64 per step, and finds its first slot by one search.  In
 // a step starting at edge t0 in slot s0, lane j loads the boundary
 // qoff[s0 + 1 + j]; the boundaries inside (t0, t0 + 64) form a bit mask
 // (a wave sum of distinct bits), so the slot of edge t0 + i is s0 plus the
@@ -237,7 +377,7 @@ __global__ __launch_bounds__(kCollectThreads) void sssp_write_kernel(
 // the number of boundaries at or below t0 + 64.  No lane runs a search per
 // edge.
 template <class Acc>
-__global__ void sssp_relax_kernel(Acc acc, uint32_t n, const uint64_t *__restrict__ count_p,
+__global__ void sssp_relax_kernel(Acc acc, uint32_t n, const SsspState *__restrict__ state,
                                   const uint64_t *__restrict__ qoff, const uint32_t *__restrict__ qv,
                                   const uint64_t *__restrict__ qstart,
                                   const uint32_t *__restrict__ qw, const uint64_t *__restrict__ qdist,
@@ -245,17 +385,20 @@ __global__ void sssp_relax_kernel(Acc acc, uint32_t n, const uint64_t *__restric
     const uint32_t lane = lane_id();
     const uint64_t wave = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave;
     const uint64_t nwaves = ((uint64_t)gridDim.x * blockDim.x) / kWave;
-    const uint64_t count = *count_p;
+    const uint64_t count = state->count;
+    if (!count) return;
     const uint64_t E = qoff[count];
     const uint64_t per = ((E + nwaves - 1) / nwaves + kWave - 1) / kWave * kWave;
     const uint64_t tb = wave * per;
     if (tb >= E) return;  // same for every lane
     const uint64_t te = tb + per < E ? tb + per : E;
-    uint64_t s0 = 0, hi = count;  // qoff[s0] <= tb < qoff[hi]
+    uint64_t s0 = 0, hi = count;  // qoff[s0] <= tb < qoff[hi], 64 probes a step
     while (hi - s0 > 1) {
-        const uint64_t mid = s0 + (hi - s0) / 2;
-        if (qoff[mid] <= tb) s0 = mid;
-        else hi = mid;
+        const uint64_t step = (hi - s0 + kWave - 1) / kWave;
+        const uint64_t at = s0 + lane * step;
+        const uint64_t le = __ballot(at < hi && qoff[at < hi ? at : s0] <= tb);
+        s0 += (uint64_t)(__popcll(le) - 1) * step;
+        hi = hi - s0 > step ? s0 + step : hi;
     }
     const uint64_t below = lane == kWave - 1 ? ~0ull : ((2ull << lane) - 1ull);  // bits 0..lane
     for (uint64_t t0 = tb; t0 < te; t0 += kWave) {
@@ -325,15 +468,14 @@ static lg_status lg_sssp_impl(const lg_graph *gc, uint32_t root, uint32_t delta,
     }
     LG_TRY(W.upd.ensure(words * 8));
     LG_TRY(W.tmask.ensure(words * 8));
-    LG_TRY(W.wcnt.ensure(words * 4));
-    LG_TRY(W.woff.ensure((words + 1) * 8));
+    LG_TRY(W.wdeg.ensure(words * 8));
+    LG_TRY(W.parts.ensure(kCollectParts * sizeof(SsspPart)));
     LG_TRY(W.qv.ensure((uint64_t)n * 4));
     LG_TRY(W.qw.ensure((uint64_t)n * 4));
-    LG_TRY(W.qdeg.ensure((uint64_t)n * 4));
     LG_TRY(W.qstart.ensure((uint64_t)n * 8));
     LG_TRY(W.qdist.ensure((uint64_t)n * 8));
     LG_TRY(W.qoff.ensure(((uint64_t)n + 1) * 8));
-    LG_TRY(W.ctr.ensure(16));
+    LG_TRY(W.state.ensure(sizeof(SsspState)));
     // a relabeled graph runs in label space, then maps back
     const bool rel = g->relabel != LG_RELABEL_NONE;
     uint64_t *const dist_out = dist;
@@ -341,53 +483,53 @@ static lg_status lg_sssp_impl(const lg_graph *gc, uint32_t root, uint32_t delta,
         LG_TRY(W.dl.ensure((uint64_t)n * 8));
         dist = W.dl.as<uint64_t>();
     }
+    SsspState *state = W.state.as<SsspState>();
     LG_LAUNCH(sssp_init_kernel, grid_for(std::max<uint64_t>(n, words), 256, 1u << 16), 256, 0, stream, n, words, root,
-              rel ? (const uint32_t *)g->inv.as<uint32_t>() : (const uint32_t *)nullptr, dist, W.upd.as<uint64_t>());
+              rel ? (const uint32_t *)g->inv.as<uint32_t>() : (const uint32_t *)nullptr, D, dist,
+              W.upd.as<uint64_t>(), state);
     LG_CHECK_LAUNCH();
     return dispatch_wacc(g, [&](auto acc) -> lg_status {
         using Acc = decltype(acc);
         int cus = 0;
         LG_CHECK_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, g->device));
-        const uint32_t collect_grid = grid_for(words * kWave, kCollectThreads, kCollectBlocks);
+        // words of a collecting workgroup: at least one per wave
+        const uint64_t per = std::max<uint64_t>(kCollectWaves, (words + kCollectParts - 1) / kCollectParts);
+        const uint32_t collect_grid = (uint32_t)((words + per - 1) / per);
         const uint32_t relax_grid = (uint32_t)std::max(1, cus) * 8;
-        uint64_t hi = D;
         // every step either relaxes a non-empty frontier (each entry of it
         // lowered a distance) or moves to a later bucket: bounded for
         // non-negative weights; the cap only guards against a corrupt graph
         const uint64_t cap = 64ull * n + 1024;
-        for (uint64_t step = 0;; ++step) {
-            if (step > cap) {
-                set_error("lg_sssp: no convergence after %llu steps", (unsigned long long)step);
-                return LG_ERR_DEVICE;
+        // steps queued between two looks at the state: the ones past the end
+        // find it done and return at once
+        constexpr int kAhead = 4;
+        SsspState now{};
+        while (!now.done) {
+            for (int i = 0; i < kAhead; ++i) {
+                LG_LAUNCH(sssp_count_kernel<Acc>, collect_grid, kCollectThreads, 0, stream, acc, n, words, per,
+                          (const SsspState *)state, (const uint64_t *)dist, W.upd.as<uint64_t>(),
+                          W.tmask.as<uint64_t>(), W.wdeg.as<uint64_t>(), W.parts.as<SsspPart>());
+                LG_CHECK_LAUNCH();
+                LG_LAUNCH(sssp_write_kernel<Acc>, collect_grid, kCollectThreads, 0, stream, acc, words, per, D, cap,
+                          (const uint64_t *)dist, (const uint64_t *)W.tmask.as<uint64_t>(),
+                          (const uint64_t *)W.wdeg.as<uint64_t>(), (const SsspPart *)W.parts.as<SsspPart>(),
+                          W.qv.as<uint32_t>(), W.qstart.as<uint64_t>(), W.qw.as<uint32_t>(), W.qdist.as<uint64_t>(),
+                          W.qoff.as<uint64_t>(), state);
+                LG_CHECK_LAUNCH();
+                LG_LAUNCH(sssp_relax_kernel<Acc>, relax_grid, 256, 0, stream, acc, n, (const SsspState *)state,
+                          (const uint64_t *)W.qoff.as<uint64_t>(), (const uint32_t *)W.qv.as<uint32_t>(),
+                          (const uint64_t *)W.qstart.as<uint64_t>(), (const uint32_t *)W.qw.as<uint32_t>(),
+                          (const uint64_t *)W.qdist.as<uint64_t>(), (unsigned long long *)dist,
+                          W.upd.as<unsigned long long>());
+                LG_CHECK_LAUNCH();
             }
-            LG_LAUNCH(sssp_ctr_kernel, 1, 64, 0, stream, W.ctr.as<unsigned long long>());
-            LG_CHECK_LAUNCH();
-            LG_LAUNCH(sssp_count_kernel, collect_grid, kCollectThreads, 0, stream, n, words, hi,
-                      (const uint64_t *)dist, W.upd.as<uint64_t>(), W.tmask.as<uint64_t>(), W.wcnt.as<uint32_t>(),
-                      W.ctr.as<unsigned long long>());
-            LG_CHECK_LAUNCH();
-            LG_TRY(exclusive_scan_u32(W.wcnt.as<uint32_t>(), W.woff.as<uint64_t>(), words, W.scan_tmp, stream));
-            LG_LAUNCH(sssp_write_kernel<Acc>, collect_grid, kCollectThreads, 0, stream, acc, n, words,
-                      (const uint64_t *)dist, (const uint64_t *)W.tmask.as<uint64_t>(),
-                      (const uint64_t *)W.woff.as<uint64_t>(), W.qv.as<uint32_t>(), W.qstart.as<uint64_t>(), W.qw.as<uint32_t>(),
-                      W.qdeg.as<uint32_t>(), W.qdist.as<uint64_t>(), W.ctr.as<unsigned long long>());
-            LG_CHECK_LAUNCH();
-            LG_CHECK_HIP(hipMemcpyAsync(W.host, W.ctr.p, 16, hipMemcpyDeviceToHost, stream));
+            LG_CHECK_HIP(hipMemcpyAsync(W.host, state, sizeof(SsspState), hipMemcpyDeviceToHost, stream));
             LG_CHECK_HIP(hipStreamSynchronize(stream));
-            const uint64_t count = W.host[0], left = W.host[1];
-            if (count == 0) {
-                if (left == kInfDist) break;
-                const uint64_t k = left / D;
-                hi = k + 1 > kInfDist / D ? kInfDist : (k + 1) * D;
-                continue;
-            }
-            LG_TRY(exclusive_scan_u32(W.qdeg.as<uint32_t>(), W.qoff.as<uint64_t>(), count, W.scan_tmp, stream));
-            LG_LAUNCH(sssp_relax_kernel<Acc>, relax_grid, 256, 0, stream, acc, n,
-                      (const uint64_t *)W.ctr.as<uint64_t>(), (const uint64_t *)W.qoff.as<uint64_t>(),
-                      (const uint32_t *)W.qv.as<uint32_t>(), (const uint64_t *)W.qstart.as<uint64_t>(), (const uint32_t *)W.qw.as<uint32_t>(),
-                      (const uint64_t *)W.qdist.as<uint64_t>(), (unsigned long long *)dist,
-                      W.upd.as<unsigned long long>());
-            LG_CHECK_LAUNCH();
+            std::memcpy(&now, W.host, sizeof(now));
+        }
+        if (now.done == 2) {
+            set_error("lg_sssp: no convergence after %llu steps", now.steps);
+            return LG_ERR_DEVICE;
         }
         if (rel) {
             LG_LAUNCH(sssp_unpermute_kernel, grid_for(n, 256, 1u << 16), 256, 0, stream, n, g->inv.as<uint32_t>(),
