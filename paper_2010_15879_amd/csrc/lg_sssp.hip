@@ -120,11 +120,13 @@ struct SsspPart {
 
 struct SsspWork {
     DevBuf upd;                         // bitmap, one bit per vertex
-    DevBuf qv, qw;                      // frontier: vertex, ID width
-    DevBuf qstart, qdist, qoff;         // list start, distance, entries of the vertices before
+    DevBuf qv;                          // frontier: vertex
+    DevBuf qstart, qdist, qoff;         // list start (as in vstart), distance, entries of the vertices before
     DevBuf state;                       // SsspState
     DevBuf tmask, wdeg;                 // per bitmap word: vertices taken, their degrees' sum
     DevBuf parts;                       // SsspPart of every collecting workgroup
+    DevBuf vstart, vdeg;                // per vertex, of the first call on: list start | ID width << 56, degree
+    bool lists = false;
     DevBuf dl;                          // label-space distances (relabeled graphs)
     uint64_t *host = nullptr;           // pinned readback slots
     SsspWork() = default;
@@ -134,8 +136,8 @@ struct SsspWork {
         if (host) (void)hipHostFree(host);
     }
     uint64_t bytes() const {
-        return upd.bytes + qv.bytes + qw.bytes + qstart.bytes + qdist.bytes + qoff.bytes +
-               state.bytes + tmask.bytes + wdeg.bytes + parts.bytes + dl.bytes;
+        return upd.bytes + qv.bytes + qstart.bytes + qdist.bytes + qoff.bytes +
+               state.bytes + tmask.bytes + wdeg.bytes + parts.bytes + vstart.bytes + vdeg.bytes + dl.bytes;
     }
 };
 
@@ -162,46 +164,61 @@ __global__ void sssp_init_kernel(uint32_t n, uint64_t words, uint32_t root_id, c
     }
 }
 
+// Every vertex's list, decoded once per graph: a search collects a vertex
+// about one and a half times, each time for its degree and again for its
+// start (Elias-Fano selects in every step: 4.3 of 11 ms on a relabeled
+// Kronecker graph of 2^23 vertices).
+template <class Acc>
+__global__ void sssp_lists_kernel(Acc acc, uint32_t n, uint64_t *__restrict__ vstart, uint32_t *__restrict__ vdeg) {
+    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
+    for (uint64_t v = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += stride) {
+        const WInfo vi = acc.info((uint32_t)v);
+        vstart[v] = vi.start | (uint64_t)vi.w << 56;  // streams stay far below 2^56 bits
+        vdeg[v] = vi.deg;
+    }
+}
+
 // The frontier is compacted without a shared counter (single-address atomics
-// from thousands of workgroups took 20 us a step).  Every workgroup has a
-// fixed range of bitmap words.  The count pass takes each word's marked
-// vertices below the bound out of the bitmap and leaves the range's vertices,
-// entries and smallest distance left marked; the write pass sums the ranges
-// before its own (at most kCollectParts of them) and places its vertices with
+// from thousands of workgroups took 20 us a step).  Every workgroup has its
+// fixed tiles of bitmap words, dealt in turn (a relabeled graph's marks crowd
+// in the first words).  The count pass takes each word's marked
+// vertices below the bound out of the bitmap and leaves the workgroup's
+// vertices, entries and smallest distance left marked; the write pass sums
+// the workgroups before its own (at most kCollectParts) and places its vertices with
 // the running entry count the relax pass walks by.  Two launches for what
 // were seven (a reset, the count, two scans of up to three launches), and no
 // read-back between them: Kronecker 2^20
-// vertices, 20 steps: 2.55 -> 1.66 ms.  Every
+// vertices, 20 steps: 2.65 -> 1.62 ms.  Every
 // marked vertex has edges (it was reached over one) but the root, which may
 // have none: it is then alone in the first frontier, which holds no edges.
 constexpr int kCollectThreads = 256;
 constexpr uint32_t kCollectWaves = kCollectThreads / kWave;
-constexpr uint64_t kCollectParts = 1024;
+constexpr uint64_t kCollectParts = 2048;
+constexpr uint64_t kCollectTile = 64;  // words of a tile, at most
 
-template <class Acc>
 __global__ __launch_bounds__(kCollectThreads) void sssp_count_kernel(
-    Acc acc, uint32_t n, uint64_t words, uint64_t per, const SsspState *__restrict__ state,
-    const uint64_t *__restrict__ dist, uint64_t *__restrict__ upd, uint64_t *__restrict__ tmask,
+    uint32_t n, uint64_t words, uint32_t tile, const SsspState *__restrict__ state,
+    const uint32_t *__restrict__ vdeg, const uint64_t *__restrict__ dist, uint64_t *__restrict__ upd, uint64_t *__restrict__ tmask,
     uint64_t *__restrict__ wdeg, SsspPart *__restrict__ parts) {
     if (state->done) return;
     __shared__ unsigned long long s_left[kCollectWaves], s_edges[kCollectWaves], s_count[kCollectWaves];
     const uint64_t hi = state->hi;
     const uint32_t lane = lane_id(), wv = threadIdx.x / kWave;
-    const uint64_t q0 = (uint64_t)blockIdx.x * per;
-    const uint64_t q1 = q0 + per < words ? q0 + per : words;
     uint64_t left = kInfDist;  // the smallest distance staying marked
     unsigned long long edges = 0, count = 0;
-    // a wave holds every fourth word of 256 (so that a range's marked words
+    // a wave holds every fourth word of a tile (so that its marked words
     // spread over the waves), then takes the marked ones two at a time, their
     // vertices' distances and list lengths in flight together
     constexpr int kWords = 2;
-    for (uint64_t b = q0; b < q1; b += kCollectThreads) {
+    for (uint64_t b = (uint64_t)blockIdx.x * tile; b < words; b += (uint64_t)gridDim.x * tile) {
         const uint64_t q = b + lane * kCollectWaves + wv;
-        const uint64_t mine = q < q1 ? upd[q] : 0ull;
+        const bool in = lane * kCollectWaves + wv < tile && q < words;
+        const uint64_t mine = in ? upd[q] : 0ull;
         uint64_t my_take = 0, my_deg = 0;
         for (uint64_t todo = __ballot(mine != 0ull); todo;) {
             uint32_t t[kWords];
             uint64_t d[kWords];
+            uint32_t deg[kWords];
             bool set[kWords], take[kWords];
 #pragma unroll
             for (int k = 0; k < kWords; ++k) {
@@ -212,26 +229,24 @@ __global__ __launch_bounds__(kCollectThreads) void sssp_count_kernel(
                 const uint64_t v = (b + t[k] * kCollectWaves + wv) * 64 + lane;
                 set[k] = any && ((bits >> lane) & 1ull) && v < n;
                 d[k] = set[k] ? dist[v] : kInfDist;
+                deg[k] = set[k] ? vdeg[v] : 0u;
             }
-            uint32_t deg[kWords];
 #pragma unroll
             for (int k = 0; k < kWords; ++k) {
                 take[k] = set[k] && d[k] < hi;
                 if (set[k] && !take[k] && d[k] < left) left = d[k];
-                const uint64_t v = (b + t[k] * kCollectWaves + wv) * 64 + lane;
-                deg[k] = take[k] ? acc.info((uint32_t)v).deg : 0u;
             }
 #pragma unroll
             for (int k = 0; k < kWords; ++k) {
                 const uint64_t take_m = __ballot(take[k]);
-                const uint64_t sum = wave_sum((unsigned long long)deg[k]);
+                const uint64_t sum = wave_sum((unsigned long long)(take[k] ? deg[k] : 0u));
                 if (take_m && lane == t[k]) {
                     my_take = take_m;
                     my_deg = sum;
                 }
             }
         }
-        if (q < q1) {
+        if (in) {
             tmask[q] = my_take;
             if (my_take) {
                 wdeg[q] = my_deg;
@@ -281,19 +296,18 @@ __device__ __forceinline__ uint64_t collect_scan(uint64_t x, uint64_t *s_wave, u
     return base + incl - x;
 }
 
-template <class Acc>
 __global__ __launch_bounds__(kCollectThreads) void sssp_write_kernel(
-    Acc acc, uint64_t words, uint64_t per, uint64_t delta, uint64_t max_steps, const uint64_t *__restrict__ dist,
+    const uint64_t *__restrict__ vstart, const uint32_t *__restrict__ vdeg, uint64_t words, uint32_t tile, uint64_t delta, uint64_t max_steps, const uint64_t *__restrict__ dist,
     const uint64_t *__restrict__ tmask, const uint64_t *__restrict__ wdeg, const SsspPart *__restrict__ parts,
-    uint32_t *__restrict__ qv, uint64_t *__restrict__ qstart, uint32_t *__restrict__ qw, uint64_t *__restrict__ qdist,
+    uint32_t *__restrict__ qv, uint64_t *__restrict__ qstart, uint64_t *__restrict__ qdist,
     uint64_t *__restrict__ qoff, SsspState *__restrict__ state) {
     __shared__ uint64_t s_wave[kCollectWaves];
-    __shared__ uint64_t s_pos[kCollectThreads], s_off[kCollectThreads], s_take[kCollectThreads];
+    __shared__ uint64_t s_pos[kCollectTile], s_off[kCollectTile], s_take[kCollectTile];
     __shared__ unsigned long long s_left;
     // (a block that finds `done` set by block 0 below had nothing to write)
     if (state->done) return;
     const uint32_t lane = lane_id(), wv = threadIdx.x / kWave;
-    // the ranges before this one
+    // the workgroups before this one
     uint64_t cnt = 0, edges = 0, all_cnt = 0, all_edges = 0, left = kInfDist;
     for (uint32_t i = threadIdx.x; i < gridDim.x; i += kCollectThreads) {
         const SsspPart p = parts[i];
@@ -331,34 +345,33 @@ __global__ __launch_bounds__(kCollectThreads) void sssp_write_kernel(
             }
         }
     }
-    const uint64_t q0 = (uint64_t)blockIdx.x * per;
-    const uint64_t q1 = q0 + per < words ? q0 + per : words;
-    for (uint64_t b = q0; b < q1; b += kCollectThreads) {
+    for (uint64_t b = (uint64_t)blockIdx.x * tile; b < words; b += (uint64_t)gridDim.x * tile) {
         const uint64_t q = b + threadIdx.x;
-        const uint64_t take = q < q1 ? tmask[q] : 0ull;
+        const uint64_t take = threadIdx.x < tile && q < words ? tmask[q] : 0ull;
         const uint64_t deg = take ? wdeg[q] : 0ull;
         uint64_t tile_cnt, tile_edges;
         const uint64_t at = collect_scan((uint64_t)__popcll(take), s_wave, tile_cnt);
         const uint64_t off = collect_scan(deg, s_wave, tile_edges);
-        s_take[threadIdx.x] = take;
-        s_pos[threadIdx.x] = pos0 + at;
-        s_off[threadIdx.x] = off0 + off;
+        if (threadIdx.x < tile) {
+            s_take[threadIdx.x] = take;
+            s_pos[threadIdx.x] = pos0 + at;
+            s_off[threadIdx.x] = off0 + off;
+        }
         __syncthreads();
-        const uint32_t tile = q1 - b < (uint64_t)kCollectThreads ? (uint32_t)(q1 - b) : (uint32_t)kCollectThreads;
         for (uint32_t t = wv; t < tile; t += kCollectWaves) {
             const uint64_t m = s_take[t];
             if (!m) continue;  // same for every lane
             const bool in = (m >> lane) & 1ull;
             const uint64_t v = (b + t) * 64 + lane;
-            const WInfo vi = in ? acc.info((uint32_t)v) : WInfo{0, 0, 0};
-            const uint64_t incl = wave_incl_scan((uint64_t)vi.deg);
+            const uint32_t deg = in ? vdeg[v] : 0u;
+            const uint64_t start = in ? vstart[v] : 0ull;
+            const uint64_t incl = wave_incl_scan((uint64_t)deg);
             if (in) {
                 const uint64_t pos = s_pos[t] + popc_below(m);
                 qv[pos] = (uint32_t)v;
-                qstart[pos] = vi.start;
-                qw[pos] = vi.w;
+                qstart[pos] = start;
                 qdist[pos] = dist[v];
-                qoff[pos] = s_off[t] + incl - vi.deg;
+                qoff[pos] = s_off[t] + incl - deg;
             }
         }
         pos0 += tile_cnt;
@@ -379,8 +392,7 @@ __global__ __launch_bounds__(kCollectThreads) void sssp_write_kernel(
 template <class Acc>
 __global__ void sssp_relax_kernel(Acc acc, uint32_t n, const SsspState *__restrict__ state,
                                   const uint64_t *__restrict__ qoff, const uint32_t *__restrict__ qv,
-                                  const uint64_t *__restrict__ qstart,
-                                  const uint32_t *__restrict__ qw, const uint64_t *__restrict__ qdist,
+                                  const uint64_t *__restrict__ qstart, const uint64_t *__restrict__ qdist,
                                   unsigned long long *__restrict__ dist, unsigned long long *__restrict__ upd) {
     const uint32_t lane = lane_id();
     const uint64_t wave = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave;
@@ -414,7 +426,8 @@ __global__ void sssp_relax_kernel(Acc acc, uint32_t n, const SsspState *__restri
         const uint64_t a = s0 + (uint64_t)__popcll(M & below);
         if (t < te && dist[qv[a]] >= qdist[a]) {
             uint32_t id, w;
-            acc.entry(qstart[a], qw[a], t - qoff[a], id, w);
+            const uint64_t st = qstart[a];
+            acc.entry(st & ((1ull << 56) - 1ull), (uint32_t)(st >> 56), t - qoff[a], id, w);
             if (id < n) {  // only a corrupt stream fails this
                 const unsigned long long nd = qdist[a] + (unsigned long long)w;
                 if (nd < dist[id]) {
@@ -471,7 +484,8 @@ static lg_status lg_sssp_impl(const lg_graph *gc, uint32_t root, uint32_t delta,
     LG_TRY(W.wdeg.ensure(words * 8));
     LG_TRY(W.parts.ensure(kCollectParts * sizeof(SsspPart)));
     LG_TRY(W.qv.ensure((uint64_t)n * 4));
-    LG_TRY(W.qw.ensure((uint64_t)n * 4));
+    LG_TRY(W.vstart.ensure((uint64_t)n * 8));
+    LG_TRY(W.vdeg.ensure((uint64_t)n * 4));
     LG_TRY(W.qstart.ensure((uint64_t)n * 8));
     LG_TRY(W.qdist.ensure((uint64_t)n * 8));
     LG_TRY(W.qoff.ensure(((uint64_t)n + 1) * 8));
@@ -492,10 +506,17 @@ static lg_status lg_sssp_impl(const lg_graph *gc, uint32_t root, uint32_t delta,
         using Acc = decltype(acc);
         int cus = 0;
         LG_CHECK_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, g->device));
-        // words of a collecting workgroup: at least one per wave
-        const uint64_t per = std::max<uint64_t>(kCollectWaves, (words + kCollectParts - 1) / kCollectParts);
-        const uint32_t collect_grid = (uint32_t)((words + per - 1) / per);
+        // tiles of one word per wave on small graphs, up to kCollectTile words
+        uint32_t tile = kCollectWaves;
+        while (tile < kCollectTile && words > tile * kCollectParts) tile *= 2;
+        const uint32_t collect_grid = (uint32_t)std::min<uint64_t>(kCollectParts, (words + tile - 1) / tile);
         const uint32_t relax_grid = (uint32_t)std::max(1, cus) * 8;
+        if (!W.lists) {
+            LG_LAUNCH(sssp_lists_kernel<Acc>, grid_for(n, 256, 1u << 16), 256, 0, stream, acc, n,
+                      W.vstart.as<uint64_t>(), W.vdeg.as<uint32_t>());
+            LG_CHECK_LAUNCH();
+            W.lists = true;
+        }
         // every step either relaxes a non-empty frontier (each entry of it
         // lowered a distance) or moves to a later bucket: bounded for
         // non-negative weights; the cap only guards against a corrupt graph
@@ -506,20 +527,20 @@ static lg_status lg_sssp_impl(const lg_graph *gc, uint32_t root, uint32_t delta,
         SsspState now{};
         while (!now.done) {
             for (int i = 0; i < kAhead; ++i) {
-                LG_LAUNCH(sssp_count_kernel<Acc>, collect_grid, kCollectThreads, 0, stream, acc, n, words, per,
-                          (const SsspState *)state, (const uint64_t *)dist, W.upd.as<uint64_t>(),
+                LG_LAUNCH(sssp_count_kernel, collect_grid, kCollectThreads, 0, stream, n, words, tile,
+                          (const SsspState *)state, (const uint32_t *)W.vdeg.as<uint32_t>(), (const uint64_t *)dist, W.upd.as<uint64_t>(),
                           W.tmask.as<uint64_t>(), W.wdeg.as<uint64_t>(), W.parts.as<SsspPart>());
                 LG_CHECK_LAUNCH();
-                LG_LAUNCH(sssp_write_kernel<Acc>, collect_grid, kCollectThreads, 0, stream, acc, words, per, D, cap,
-                          (const uint64_t *)dist, (const uint64_t *)W.tmask.as<uint64_t>(),
+                LG_LAUNCH(sssp_write_kernel, collect_grid, kCollectThreads, 0, stream,
+                          (const uint64_t *)W.vstart.as<uint64_t>(), (const uint32_t *)W.vdeg.as<uint32_t>(), words,
+                          tile, D, cap, (const uint64_t *)dist, (const uint64_t *)W.tmask.as<uint64_t>(),
                           (const uint64_t *)W.wdeg.as<uint64_t>(), (const SsspPart *)W.parts.as<SsspPart>(),
-                          W.qv.as<uint32_t>(), W.qstart.as<uint64_t>(), W.qw.as<uint32_t>(), W.qdist.as<uint64_t>(),
+                          W.qv.as<uint32_t>(), W.qstart.as<uint64_t>(), W.qdist.as<uint64_t>(),
                           W.qoff.as<uint64_t>(), state);
                 LG_CHECK_LAUNCH();
                 LG_LAUNCH(sssp_relax_kernel<Acc>, relax_grid, 256, 0, stream, acc, n, (const SsspState *)state,
                           (const uint64_t *)W.qoff.as<uint64_t>(), (const uint32_t *)W.qv.as<uint32_t>(),
-                          (const uint64_t *)W.qstart.as<uint64_t>(), (const uint32_t *)W.qw.as<uint32_t>(),
-                          (const uint64_t *)W.qdist.as<uint64_t>(), (unsigned long long *)dist,
+                          (const uint64_t *)W.qstart.as<uint64_t>(), (const uint64_t *)W.qdist.as<uint64_t>(), (unsigned long long *)dist,
                           W.upd.as<unsigned long long>());
                 LG_CHECK_LAUNCH();
             }
