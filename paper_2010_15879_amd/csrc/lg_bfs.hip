@@ -37,8 +37,9 @@ namespace lg {
 
 uint64_t BfsWork::bytes() const {
     return qa.bytes + qb.bytes + fstart.bytes + fdeg.bytes + fw.bytes + fscan.bytes + visited.bytes + curr.bytes +
-           next.bytes + counters.bytes + sample.bytes + depth_i.bytes + parent_i.bytes + scan_tmp.bytes + pv.bytes + pstart.bytes +
-           pdeg.bytes + pw.bytes + pseg_cnt.bytes + pseg_off.bytes;
+           next.bytes + counters.bytes + sample.bytes + depth_i.bytes + parent_i.bytes + scan_tmp.bytes + pv.bytes +
+           pstart.bytes +
+           pdeg.bytes + pw.bytes + pseg_cnt.bytes + pseg_off.bytes + claims.bytes;
 }
 
 BfsWork::~BfsWork() {
@@ -350,6 +351,223 @@ __global__ void td_finish_kernel(uint32_t n, uint64_t *__restrict__ visited, con
     }
 }
 
+// The same level where the parents outgrow the caches: the claims are binned
+// by vertex first, and a workgroup per bin takes the smallest in LDS and
+// finishes the bin's vertices, so that everything but the lists is streamed.
+// Uniform graph, 2^24 vertices, a level of 32 M edges: 1,263 us of atomics at
+// random places and 35 to finish became 244 + 111 us (bound by the lists'
+// scattered lines and 256 MB of claims each way).
+//
+// td_bin_kernel: a workgroup takes kTdBinTile edges of the frontier.  Marks
+// at the rows' first edges give every edge its row (a running maximum), the
+// claims are counting-sorted by bin in LDS, and each bin's run goes to room
+// reserved with one atomic.  Claims of visited vertices go along: testing the
+// bitmap here was 170 us of scattered reads, and the bin's workgroup reads
+// its own words of it anyway.  A bin has room for half more than its even
+// share; what does not fit claims its parent (or depth) directly, and the
+// bin's workgroup, which sees the count, reads those too.
+//
+// 1,024 threads and 8 edges each: two workgroups and 32 waves a CU; with 512
+// threads of 16 edges it took a seventh longer, with tiles or bins twice as
+// large as long.  The rows' starts are staged in LDS (a gather less per
+// edge: 3 %).
+constexpr uint32_t kTdBinThreads = 1024;
+constexpr uint32_t kTdBinSteps = 8;
+constexpr uint32_t kTdBinTile = kTdBinThreads * kTdBinSteps;
+constexpr uint32_t kTdBinWaves = kTdBinThreads / kWave;
+constexpr uint32_t kTdBinRows = 2048;  // rows of a tile held in LDS
+
+template <class Acc, bool kParent>
+__global__ __launch_bounds__(kTdBinThreads) void td_bin_kernel(
+    Acc acc, const uint32_t *__restrict__ queue, uint32_t qsize, const uint64_t *__restrict__ fstart,
+    const uint32_t *__restrict__ fw, const uint64_t *__restrict__ fscan, uint64_t edges,
+    int32_t *__restrict__ depth, uint32_t *__restrict__ parent, const uint64_t *__restrict__ visited,
+    int32_t next_depth, uint32_t shift, uint32_t bins, uint32_t cap, uint2 *__restrict__ claims,
+    uint32_t *__restrict__ fill) {
+    extern __shared__ uint32_t s_bin[];  // u32[bins] counts, then starts; u32[bins] first places
+    uint32_t *s_first = s_bin + bins;
+    __shared__ uint2 s_buf[kTdBinTile];  // row marks (u32), then the claims sorted by bin
+    __shared__ uint32_t s_wave[kTdBinWaves];
+    uint32_t *s_mark = reinterpret_cast<uint32_t *>(s_buf);
+    // of a row: where edge 0 of the frontier would lie were it in this list (56 bits), under its width
+    uint64_t *s_base = reinterpret_cast<uint64_t *>(s_buf + kTdBinTile / 2);
+    uint32_t *s_id = reinterpret_cast<uint32_t *>(s_base + kTdBinRows);
+    constexpr uint64_t kPlace = (1ull << 56) - 1;
+    const uint32_t tid = threadIdx.x, lane = lane_id(), wv = tid / kWave;
+    const uint32_t x0 = wv * (kWave * kTdBinSteps) + lane;
+    for (uint64_t t = blockIdx.x; t * kTdBinTile < edges; t += gridDim.x) {
+        const uint64_t e0 = t * kTdBinTile;
+        const uint64_t e1 = e0 + kTdBinTile < edges ? e0 + kTdBinTile : edges;
+        const uint32_t len = (uint32_t)(e1 - e0);
+        for (uint32_t i = tid; i < kTdBinTile / 2; i += kTdBinThreads) s_buf[i] = make_uint2(0, 0);
+        for (uint32_t b = tid; b < bins; b += kTdBinThreads) s_bin[b] = 0;
+        // the row of the tile's first edge, 64 probes a step (every wave for itself)
+        uint32_t i0 = 0, hi = qsize;
+        while (hi - i0 > 1) {
+            const uint32_t step = (hi - i0 + kWave - 1) / kWave;
+            const uint32_t at = i0 + lane * step;
+            const uint64_t le = __ballot(at < hi && fscan[at < hi ? at : i0] <= e0);
+            i0 += (uint32_t)(__popcll(le) - 1) * step;
+            hi = hi - i0 > step ? i0 + step : hi;
+        }
+        __syncthreads();
+        for (uint32_t k = i0 + tid; k < qsize; k += kTdBinThreads) {
+            const uint64_t a = fscan[k], z = fscan[k + 1];
+            if (a >= e1) break;
+            if (z > a && z > e0) s_mark[a > e0 ? (uint32_t)(a - e0) : 0u] = k - i0 + 1;
+            if (k - i0 < kTdBinRows) {
+                const uint32_t w = fw[k];
+                s_base[k - i0] = ((fstart[k] - a * Acc::step(w)) & kPlace) | ((uint64_t)w << 56);
+                if constexpr (kParent) s_id[k - i0] = queue[k];
+            }
+        }
+        __syncthreads();
+        uint32_t row[kTdBinSteps], top = 0;
+#pragma unroll
+        for (uint32_t q = 0; q < kTdBinSteps; ++q) {
+            row[q] = s_mark[x0 + q * kWave];
+            top = row[q] > top ? row[q] : top;
+        }
+        top = wave_max_scan_dpp(top);
+        if (lane == kWave - 1) s_wave[wv] = top;
+        __syncthreads();
+        uint32_t carry = 0;
+        for (uint32_t w = 0; w < wv; ++w) carry = s_wave[w] > carry ? s_wave[w] : carry;
+        carry = __builtin_amdgcn_readfirstlane(carry);
+#pragma unroll
+        for (uint32_t q = 0; q < kTdBinSteps; ++q) {
+            const uint32_t sc = wave_max_scan_dpp(row[q]);
+            row[q] = (sc > carry ? sc : carry) - 1;
+            const uint32_t last = (uint32_t)__builtin_amdgcn_readlane((int)sc, kWave - 1);
+            carry = last > carry ? last : carry;
+        }
+        // the edges, all of a thread's list and bitmap loads in flight together
+        // (slots past the end read the tile's last row, and the list's start)
+        constexpr uint32_t kIn = kTdBinSteps;
+        uint32_t v[kTdBinSteps], rank[kTdBinSteps];
+#pragma unroll
+        for (uint32_t q0 = 0; q0 < kTdBinSteps; q0 += kIn) {
+            uint64_t pos[kIn];
+            uint32_t w[kIn];
+#pragma unroll
+            for (uint32_t k = 0; k < kIn; ++k) {
+                const uint32_t x = x0 + (q0 + k) * kWave, r = row[q0 + k];
+                uint64_t base;
+                if (r < kTdBinRows) {
+                    base = s_base[r];
+                    w[k] = (uint32_t)(base >> 56);
+                    if constexpr (kParent) row[q0 + k] = s_id[r];
+                } else {
+                    w[k] = fw[i0 + r];
+                    base = fstart[i0 + r] - fscan[i0 + r] * Acc::step(w[k]);
+                    if constexpr (kParent) row[q0 + k] = queue[i0 + r];
+                }
+                pos[k] = x < len ? (base + (e0 + x) * Acc::step(w[k])) & kPlace : 0ull;
+            }
+#pragma unroll
+            for (uint32_t k = 0; k < kIn; ++k) v[q0 + k] = acc.get(pos[k], Acc::mask(w[k]));
+#pragma unroll
+            for (uint32_t k = 0; k < kIn; ++k) {
+                if (x0 + (q0 + k) * kWave >= len) v[q0 + k] = 0xFFFFFFFFu;
+                rank[q0 + k] = v[q0 + k] != 0xFFFFFFFFu ? atomicAdd(&s_bin[v[q0 + k] >> shift], 1u) : 0u;
+            }
+        }
+        __syncthreads();
+        // counts -> starts, and each bin's room
+        uint32_t total;
+        {
+            const uint32_t per = (bins + kTdBinThreads - 1) / kTdBinThreads;
+            const uint32_t b0 = tid * per;
+            uint32_t sum = 0;
+            for (uint32_t b = b0; b < b0 + per && b < bins; ++b) sum += s_bin[b];
+            const uint32_t incl = wave_scan_dpp(sum);
+            if (lane == kWave - 1) s_wave[wv] = incl;
+            __syncthreads();
+            uint32_t base = incl - sum;
+            total = 0;
+            for (uint32_t w = 0; w < kTdBinWaves; ++w) {
+                if (w < wv) base += s_wave[w];
+                total += s_wave[w];
+            }
+            for (uint32_t b = b0; b < b0 + per && b < bins; ++b) {
+                const uint32_t c = s_bin[b];
+                s_bin[b] = base;
+                // the place of the bin's run, less where it starts in the buffer
+                s_first[b] = (c ? atomicAdd(&fill[b], c) : 0u) - base;
+                base += c;
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (uint32_t q = 0; q < kTdBinSteps; ++q)
+            if (v[q] != 0xFFFFFFFFu)
+                s_buf[s_bin[v[q] >> shift] + rank[q]] = make_uint2(v[q], kParent ? row[q] : 0u);
+        __syncthreads();
+        for (uint32_t i = tid; i < total; i += kTdBinThreads) {
+            const uint2 c = s_buf[i];
+            const uint32_t b = c.x >> shift, at = s_first[b] + i;
+            if (at < cap) {
+                claims[(uint64_t)b * cap + at] = c;
+            } else if (!((visited[c.x >> 6] >> (c.x & 63)) & 1ull)) {
+                if constexpr (kParent) atomicMin(&parent[c.x], c.y);
+                else depth[c.x] = next_depth;
+            }
+        }
+        __syncthreads();  // the next tile clears the buffer
+    }
+}
+
+// A bin's claims: the smallest per vertex, then the vertices as
+// td_finish_kernel leaves them.
+template <bool kParent>
+__global__ __launch_bounds__(1024) void td_bin_finish_kernel(uint32_t n, uint32_t shift, uint32_t cap,
+                                                             const uint2 *__restrict__ claims,
+                                                             const uint32_t *__restrict__ fill,
+                                                             uint64_t *__restrict__ visited,
+                                                             uint32_t *__restrict__ parent, int32_t *__restrict__ depth,
+                                                             int32_t next_depth, uint64_t *__restrict__ frontier) {
+    extern __shared__ uint32_t s_min[];  // u32[1 << shift]
+    const uint32_t size = 1u << shift, lane = lane_id(), wv = threadIdx.x / kWave;
+    const uint64_t v0 = (uint64_t)blockIdx.x << shift;
+    const uint32_t all = fill[blockIdx.x], have = all < cap ? all : cap;
+    for (uint32_t i = threadIdx.x; i < size; i += 1024) s_min[i] = 0xFFFFFFFFu;
+    __syncthreads();
+    const uint2 *mine = claims + (uint64_t)blockIdx.x * cap;
+    constexpr uint32_t kIn = 4;
+    for (uint32_t i = threadIdx.x; i < have; i += 1024 * kIn) {
+        uint2 c[kIn];
+#pragma unroll
+        for (uint32_t k = 0; k < kIn; ++k) c[k] = mine[i + k * 1024 < have ? i + k * 1024 : have - 1];
+#pragma unroll
+        for (uint32_t k = 0; k < kIn; ++k) atomicMin(&s_min[c[k].x & (size - 1)], c[k].y);
+    }
+    __syncthreads();
+    for (uint32_t q = wv; q < size / kWave && v0 + (uint64_t)q * kWave < n; q += 1024 / kWave) {
+        const uint64_t v = v0 + (uint64_t)q * kWave + lane, w = v / kWave;
+        const uint64_t vis = visited[w];
+        const bool open = v < n && !((vis >> lane) & 1ull);
+        uint32_t p = s_min[q * kWave + lane];
+        if (all > cap) {  // some claims went past the bin
+            if constexpr (kParent) {
+                const uint32_t direct = open ? parent[v] : 0xFFFFFFFFu;
+                p = direct < p ? direct : p;
+            } else if (open && depth[v] == next_depth) {
+                p = 0;
+            }
+        }
+        const bool fresh = open && p != 0xFFFFFFFFu;
+        if (fresh) {
+            if constexpr (kParent) parent[v] = p;
+            depth[v] = next_depth;
+        }
+        const uint64_t m = __ballot(fresh);
+        if (lane == 0) {
+            frontier[w] = m;
+            if (m) visited[w] = vis | m;
+        }
+    }
+}
+
 // A small top-down level in one launch: a wave per frontier vertex decodes
 // its list and claims neighbors by the same rule as td_expand_kernel (skip
 // vertices visited before this level, CAS the depth, smallest parent label
@@ -591,27 +809,38 @@ __global__ void bu_pending_kernel(Acc acc, uint32_t threshold, uint64_t np, cons
     if (threadIdx.x == 0 && woke) atomicAdd(&counters[1], woke);
 }
 
-// frontier bitmap -> queue.  A wave takes 64 consecutive words (one per
-// lane), reserves their entries with one atomic and writes them in order,
+// frontier bitmap -> queue.  A workgroup takes as many consecutive words as
+// it has threads, one per lane, and reserves their entries with one atomic:
+// all reservations meet in one counter, some 18 ns each, which was this
+// kernel's time when every wave made its own (uniform graph, 2^24 vertices,
+// 4,096 reservations: 77 us a launch; 256 of them: 33).  A wave writes its 64 words' entries in order,
 // 64 consecutive queue slots per step: slot j's word is the one whose
 // prefix count range holds j (a binary search of the wave's inclusive
 // counts), its bit the (j - count before)-th one of that word.  One lane
 // writing its word's ones one after another scattered every store.
-__global__ void bitmap_to_queue_kernel(uint64_t words, const uint64_t *__restrict__ bits,
-                                       uint32_t *__restrict__ queue, unsigned long long *__restrict__ tail) {
-    const uint32_t lane = lane_id();
-    const uint64_t wave = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave;
-    const uint64_t nwaves = ((uint64_t)gridDim.x * blockDim.x) / kWave;
-    for (uint64_t w0 = wave * kWave; w0 < words; w0 += nwaves * kWave) {
-        const uint64_t q = w0 + lane;
+__global__ __launch_bounds__(1024) void bitmap_to_queue_kernel(uint64_t words, const uint64_t *__restrict__ bits,
+                                                               uint32_t *__restrict__ queue,
+                                                               unsigned long long *__restrict__ tail) {
+    __shared__ uint32_t s_count[1024 / kWave];
+    __shared__ unsigned long long s_off;
+    const uint32_t lane = lane_id(), wv = threadIdx.x / kWave;
+    for (uint64_t b0 = (uint64_t)blockIdx.x * blockDim.x; b0 < words; b0 += (uint64_t)gridDim.x * blockDim.x) {
+        const uint64_t w0 = b0 + (uint64_t)wv * kWave, q = w0 + lane;
         const uint64_t b = q < words ? bits[q] : 0ull;
         const uint32_t c = (uint32_t)__popcll(b);
-        const uint32_t incl = wave_incl_scan(c);
+        const uint32_t incl = wave_scan_dpp(c);
         const uint32_t total = __shfl(incl, kWave - 1, kWave);
-        if (total == 0) continue;  // wave-uniform
-        unsigned long long off = 0;
-        if (lane == 0) off = atomicAdd(tail, (unsigned long long)total);
-        off = __shfl(off, 0, kWave);
+        __syncthreads();  // the words before are through with the sums
+        if (lane == 0) s_count[wv] = total;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            uint32_t all = 0;
+            for (uint32_t i = 0; i < blockDim.x / kWave; ++i) all += s_count[i];
+            s_off = all ? atomicAdd(tail, (unsigned long long)all) : 0ull;
+        }
+        __syncthreads();
+        unsigned long long off = s_off;
+        for (uint32_t i = 0; i < wv; ++i) off += s_count[i];
         for (uint32_t j0 = 0; j0 < total; j0 += kWave) {
             const uint32_t j = j0 + lane;
             // the number of words whose inclusive count is <= j (at most 63:
@@ -626,6 +855,18 @@ __global__ void bitmap_to_queue_kernel(uint64_t words, const uint64_t *__restric
             if (j < total) queue[off + j] = (uint32_t)((w0 + k) * 64 + select_in_word(x, j - before));
         }
     }
+}
+
+// 1,024 threads a workgroup from 2^23 vertices, where the reservations are
+// the longer part (2^24: 33 us a launch, 41 with 256 threads); below, 256, so
+// that the queue is written from more CUs (2^20 vertices in 16 workgroups
+// cost a 64-root search 2 %).
+static lg_status bitmap_to_queue(uint64_t words, const uint64_t *bits, uint32_t *queue, unsigned long long *tail,
+                                 hipStream_t s) {
+    const uint32_t threads = words >= (1u << 17) ? 1024 : 256;
+    LG_LAUNCH(bitmap_to_queue_kernel, grid_for(words, threads, 1u << 16), threads, 0, s, words, bits, queue, tail);
+    LG_CHECK_LAUNCH();
+    return LG_OK;
 }
 
 // ---------------------------------------------------------------------------
@@ -1209,6 +1450,43 @@ __global__ void bfs_unpermute_kernel(uint32_t n, const uint32_t *__restrict__ in
 // bottom-up -> top-down when the frontier shrinks below n / kBfsBeta
 constexpr double kBfsBeta = 18.0;
 
+// A top-down level of `edges` edges by bins, when it pays: from 2^20
+// vertices (below, the parents stay in the caches), 2^20 edges (128 tiles; a
+// search of 2^20 vertices with a level of 343 K edges took 318 us against
+// 309 with direct claims, one with a level of 2.1 M edges 372 against 403)
+// and a quarter of the vertices (the bins' pass over the vertices costs 75
+// us more than td_finish at 2^24, as much as direct claims of 2 M edges).
+// At most 2^27 vertices, so that the bins' counts (4,096) and a bin's
+// vertices (2^15) stay in LDS, and 2 GiB of claims.  `done` says whether it
+// ran: without room for the claims the direct level takes over.
+constexpr uint64_t kTdBinMinVertices = 1u << 20, kTdBinMaxVertices = 1u << 27, kTdBinMinEdges = 1u << 20;
+constexpr uint64_t kTdBinMaxBytes = 2ull << 30;
+
+template <class Acc, bool kParent>
+static lg_status td_binned(BfsWork &w, Acc acc, uint32_t n, const uint32_t *queue, uint32_t qsize, uint64_t edges,
+                           uint64_t *visited, int32_t *depth, uint32_t *parent, int32_t next_depth,
+                           uint64_t *frontier, hipStream_t s, bool &done) {
+    done = false;
+    if (n < kTdBinMinVertices || n > kTdBinMaxVertices || edges < n / 4 || edges < kTdBinMinEdges) return LG_OK;
+    const uint32_t shift = n > (1u << 26) ? 15 : 14;
+    const uint32_t bins = (uint32_t)(((uint64_t)n + (1u << shift) - 1) >> shift);
+    const uint64_t cap = (edges / bins + edges / bins / 2 + 1024 + 63) & ~63ull;
+    const uint64_t bytes = cap * bins * 8 + (uint64_t)bins * 4;
+    if (bytes > kTdBinMaxBytes) return LG_OK;
+    if (w.claims.bytes < bytes && w.claims.ensure(bytes + bytes / 8) != LG_OK) return LG_OK;
+    uint32_t *fill = reinterpret_cast<uint32_t *>(w.claims.as<char>() + cap * bins * 8);
+    LG_TRY(fill_u32(fill, 0, bins, s));
+    LG_LAUNCH((td_bin_kernel<Acc, kParent>), grid_for(edges, kTdBinTile, 1u << 20), kTdBinThreads, bins * 8, s, acc,
+              queue, qsize, w.fstart.as<uint64_t>(), w.fw.as<uint32_t>(), w.fscan.as<uint64_t>(), edges, depth,
+              parent, visited, next_depth, shift, bins, (uint32_t)cap, w.claims.as<uint2>(), fill);
+    LG_CHECK_LAUNCH();
+    LG_LAUNCH(td_bin_finish_kernel<kParent>, bins, 1024, 4u << shift, s, n, shift, (uint32_t)cap,
+              (const uint2 *)w.claims.p, (const uint32_t *)fill, visited, parent, depth, next_depth, frontier);
+    LG_CHECK_LAUNCH();
+    done = true;
+    return LG_OK;
+}
+
 template <class Acc>
 static lg_status bfs_one(lg_graph *g, BfsWork &w, Acc acc, uint32_t root_id, const uint32_t *inv, int32_t *depth,
                          uint32_t *parent, int32_t max_depth, uint32_t flags, double alpha, hipStream_t s) {
@@ -1355,7 +1633,16 @@ static lg_status bfs_one(lg_graph *g, BfsWork &w, Acc acc, uint32_t root_id, con
             // a level of more than n/16 edges claims without CAS or queue
             // appends; a pass over the vertices then finds the new ones
             const bool claim_min = fedges > (uint64_t)n / 16;
-            if (fedges) {
+            bool binned = false;
+            if (claim_min && banded) {
+                auto bin = [&](auto kpar) -> lg_status {
+                    return td_binned<Acc, decltype(kpar)::value>(w, acc, n, qin, (uint32_t)qsize, fedges, visited,
+                                                                 depth, parent, level + 1, curr, s, binned);
+                };
+                if (parent) LG_TRY(bin(std::true_type{}));
+                else LG_TRY(bin(std::false_type{}));
+            }
+            if (fedges && !binned) {
                 const uint32_t tiles = grid_for(fedges, kTdTile, 1u << 20);
                 if (claim_min) {
                     if (parent)
@@ -1380,15 +1667,15 @@ static lg_status bfs_one(lg_graph *g, BfsWork &w, Acc acc, uint32_t root_id, con
             if (claim_min) {
                 // the next frontier's bitmap and the visited one from the pass,
                 // its queue from the bitmap (the queue counter is zero here)
-                if (parent)
+                // (a binned level has written both bitmaps)
+                if (!binned && parent)
                     LG_LAUNCH(td_finish_kernel<true>, wgrid, 256, 0, s, n, visited, (const uint32_t *)parent, depth,
                               level + 1, curr);
-                else
+                else if (!binned)
                     LG_LAUNCH(td_finish_kernel<false>, wgrid, 256, 0, s, n, visited, (const uint32_t *)parent, depth,
                               level + 1, curr);
                 LG_CHECK_LAUNCH();
-                LG_LAUNCH(bitmap_to_queue_kernel, grid_for(words, 256, 1u << 16), 256, 0, s, words, curr, qout, ctr);
-                LG_CHECK_LAUNCH();
+                LG_TRY(bitmap_to_queue(words, curr, qout, ctr, s));
                 LG_CHECK_HIP(hipMemcpyAsync(w.host, ctr, 8, hipMemcpyDeviceToHost, s));
                 LG_CHECK_HIP(hipStreamSynchronize(s));
                 qsize = w.host[0];
@@ -1463,9 +1750,7 @@ static lg_status bfs_one(lg_graph *g, BfsWork &w, Acc acc, uint32_t root_id, con
             if (back) {
                 bu_done = true;
                 LG_TRY(fill_u64((uint64_t *)ctr + 5, 0, 1, s));
-                LG_LAUNCH(bitmap_to_queue_kernel, grid_for(words, 256, 1u << 16), 256, 0, s, words, curr, qin,
-                          ctr + 5);
-                LG_CHECK_LAUNCH();
+                LG_TRY(bitmap_to_queue(words, curr, qin, ctr + 5, s));
                 qsize = now;
                 topdown = true;
             }
@@ -1677,9 +1962,7 @@ static lg_status bfs_one_inorder(lg_graph *g, BfsWork &w, Acc acc, uint32_t root
             awake = now;
             if (back) {
                 LG_TRY(fill_u64((uint64_t *)ctr + 5, 0, 1, s));
-                LG_LAUNCH(bitmap_to_queue_kernel, grid_for(words, 256, 1u << 16), 256, 0, s, words, curr, qin,
-                          ctr + 5);
-                LG_CHECK_LAUNCH();
+                LG_TRY(bitmap_to_queue(words, curr, qin, ctr + 5, s));
                 qsize = now;
                 topdown = true;
             }
@@ -2300,8 +2583,7 @@ static lg_status ms_begin(MsBatch &b, const uint32_t *roots, Out out) {
     LG_LAUNCH(ms_bits_kernel, grid_for(words * kWave, 256, kStrideBlocks), 256, 0, s, n,
               (const unsigned long long *)b.fr, b.bits);
     LG_CHECK_LAUNCH();
-    LG_LAUNCH(bitmap_to_queue_kernel, grid_for(words, 256, 1u << 16), 256, 0, s, words, b.bits, b.queue, b.ctr);
-    LG_CHECK_LAUNCH();
+    LG_TRY(bitmap_to_queue(words, b.bits, b.queue, b.ctr, s));
     LG_CHECK_HIP(hipMemcpyAsync(b.w.host, b.ctr, 8, hipMemcpyDeviceToHost, s));
     LG_CHECK_HIP(hipStreamSynchronize(s));
     b.fsize = b.w.host[0];
@@ -2373,8 +2655,7 @@ static lg_status ms_level(MsBatch &b, Acc acc, Out out) {
         if (td) LG_TRY(resolve(std::false_type{}, std::true_type{}));
         else LG_TRY(resolve(std::false_type{}, std::false_type{}));
     }
-    LG_LAUNCH(bitmap_to_queue_kernel, grid_for(words, 256, 1u << 16), 256, 0, s, words, b.bits, b.queue, b.ctr);
-    LG_CHECK_LAUNCH();
+    LG_TRY(bitmap_to_queue(words, b.bits, b.queue, b.ctr, s));
     LG_CHECK_HIP(hipMemcpyAsync(w.host, b.ctr, 24, hipMemcpyDeviceToHost, s));
     LG_CHECK_HIP(hipStreamSynchronize(s));
     b.fsize = w.host[0];

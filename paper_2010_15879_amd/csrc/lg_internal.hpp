@@ -110,6 +110,7 @@ struct BfsWork {
     DevBuf pv, pstart, pdeg, pw; // bottom-up: heavy vertices left for the segment pass
     DevBuf pseg_cnt, pseg_off;
     DevBuf depth_i, parent_i;    // label-space results when relabeled
+    DevBuf claims;               // binned top-down levels: the bins' claims, then their counts
     DevBuf scan_tmp;
     uint64_t *host = nullptr;    // pinned readback slots
     BfsWork() = default;

@@ -155,38 +155,6 @@ bool pb_applies(const lg_graph *g, uint32_t iters) {
     return iters >= (g->id_mode == LG_IDS_LOCAL || g->id_mode == LG_IDS_LOCAL_GAP ? 6u : 10u);
 }
 
-// Workgroup barrier that orders LDS only (no wait for global stores in
-// flight, which __syncthreads() adds).
-__device__ __forceinline__ void lds_barrier() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
-// Inclusive scans over the 64 lanes of a wave with DPP moves (shifts by 1,
-// 2, 4 and 8 lanes inside each row of 16, then the last lane of a row
-// broadcast into the rows after it): no LDS, no lane-address registers.
-__device__ __forceinline__ uint32_t wave_scan_dpp(uint32_t x) {
-    // dpp_ctrl: row_shr:n = 0x110 + n, row_bcast:15 = 0x142, row_bcast:31 = 0x143
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xF, 0xF, true);
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xF, 0xF, true);
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xF, 0xF, true);
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xF, 0xF, true);
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xA, 0xF, false);  // rows 1, 3 += end of rows 0, 2
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xC, 0xF, false);  // rows 2, 3 += end of row 1
-    return x;
-}
-__device__ __forceinline__ uint32_t wave_max_scan_dpp(uint32_t x) {
-    auto mx = [](uint32_t a, uint32_t b) { return a > b ? a : b; };
-    x = mx(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xF, 0xF, true));
-    x = mx(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xF, 0xF, true));
-    x = mx(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xF, 0xF, true));
-    x = mx(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xF, 0xF, true));
-    x = mx(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xA, 0xF, false));
-    x = mx(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xC, 0xF, false));
-    return x;
-}
-
 // ---------------------------------------------------------------------------
 // the build: once per graph
 // ---------------------------------------------------------------------------
