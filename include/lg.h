@@ -217,7 +217,11 @@ lg_status lg_decode_neighbors_noalloc(const lg_graph *g, const uint32_t *vertice
  * Results are independent of the flags and of the direction switching.
  * With r > 1 every row equals the result of a call with that root alone;
  * work queued on `stream` before the call completes first, and work queued
- * on `stream` after it waits for every root.  Two ways of running them:
+ * on `stream` after it waits for every root.  With LG_BFS_DIRECTION_OPT, up
+ * to 15 roots on a graph of at most 2^14 vertices and 2^19 entries (one root:
+ * 2^18) run as one launch on `stream`, with 8 bytes of device workspace per
+ * vertex and root (16 relabeled); the call returns once it is enqueued.
+ * Otherwise there are two ways of running them:
  *   - with LG_BFS_DIRECTION_OPT on a graph whose lists are not gap or Varint
  *     coded, not weighted and without bvIL offsets, the first roots go in
  *     batches of up to 64 while at least 16 are left, each batch one
@@ -228,7 +232,10 @@ lg_status lg_decode_neighbors_noalloc(const lg_graph *g, const uint32_t *vertice
  *     stays within 16 GiB); the host reads a few
  *     counters per level, so the call returns when these batches are done;
  *   - the other roots run a few at a time, each on its own internal stream
- *     with its own workspace; the call returns once each is enqueued.
+ *     with its own workspace (32 bytes per vertex, 40 relabeled, and on graphs
+ *     of at least 2^20 vertices up to 14 bytes per edge of the largest
+ *     top-down level, at most 2.25 GiB, done without when it cannot be had);
+ *     the call returns once each is enqueued.
  * These streams and workspaces belong to the device, not to the graph: they
  * grow to the largest graph searched and stay until lg_trim; multi-root
  * calls on one device run one after the other.
@@ -274,8 +281,8 @@ lg_status lg_encode_weighted(uint32_t n, uint64_t m, const uint64_t *row_offsets
  *
  * Returns LG_ERR_UNSUPPORTED for an unweighted graph.  Synchronous: the
  * device drives the buckets, the host queues a few steps at a time and looks
- * whether they ended the search, and the call returns once dist is written.  The workspace is kept with the graph
- * until lg_free; calls on the same graph from several threads run one after
+ * whether they ended the search, and the call returns once dist is written.
+ * The workspace is kept with the graph until lg_free; calls on the same graph from several threads run one after
  * the other (each holds the graph's workspace for its whole duration).
  */
 lg_status lg_sssp(const lg_graph *g, uint32_t root, uint32_t delta, uint64_t *dist, hipStream_t stream);

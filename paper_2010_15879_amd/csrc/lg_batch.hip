@@ -361,179 +361,234 @@ __device__ __forceinline__ uint32_t batch_len(const ulonglong2 &i) { return (uin
 // top-down over depths in memory, 1.2 ms; 256 over 16 graphs of 2^14 to 2^18:
 // 50.0 and 3.5 ms.
 template <class Acc, int kThreads>
-__global__ __launch_bounds__(kThreads) void bfs_batch_kernel(
-    const BatchGraph<Acc> *__restrict__ graphs, const BatchJob *__restrict__ jobs, uint32_t num_jobs,
-    uint32_t *__restrict__ job_counter, int32_t *__restrict__ depth, int32_t *__restrict__ parent,
-    int32_t max_depth, uint32_t *__restrict__ queues, uint64_t qcap, uint32_t chunk, uint32_t wave_threshold) {
+__device__ __forceinline__ void batch_search(const BatchGraph<Acc> &G, uint32_t root, int32_t *__restrict__ D,
+                                             uint32_t *__restrict__ P, int32_t max_depth, uint32_t *qa, uint32_t *qb,
+                                             uint32_t chunk, uint32_t wave_threshold) {
     extern __shared__ uint32_t s_bits[];
-    __shared__ uint32_t s_job, s_tail, s_nheavy;
+    __shared__ uint32_t s_tail, s_nheavy;
     __shared__ unsigned long long s_edges;
     __shared__ uint32_t s_heavy[kMaxChunk];
     const uint32_t tid = threadIdx.x;
     const uint32_t lane = lane_id();
     const uint32_t wv = tid / kWave;
     constexpr uint32_t kWaves = kThreads / kWave;
+    const uint32_t n = G.n, words = (n + 63) / 64 * 2;
+    const BatchBits B{s_bits, s_bits + words, s_bits + 2 * words};
+    for (uint32_t i = tid; i < 3 * words; i += kThreads) s_bits[i] = 0;
+    if (P)
+        for (uint32_t v = tid; v < n; v += kThreads) P[v] = v == root ? root : 0xFFFFFFFFu;
+    __syncthreads();
+    if (tid == 0) {
+        qa[0] = root;
+        D[root] = 0;
+        B.vis[root >> 5] = B.fr[root >> 5] = 1u << (root & 31);
+        s_edges = 0;
+    }
+    __syncthreads();
+    uint32_t *qin = qa, *qout = qb;
+    uint32_t F = 1;                  // frontier vertices (the same in every thread, as all below)
+    uint64_t unexplored = G.m;       // entries of the lists not on a frontier yet (Varint: bytes count for entries)
+    bool bottom = false;
+    for (int32_t level = 0; F && !(max_depth >= 0 && level >= max_depth); ++level) {
+        const int32_t nd = level + 1;
+        // the frontier's entries: summed here for a queue, by the level before for a bitmap
+        if (!bottom) {
+            unsigned long long mine = 0;
+            for (uint32_t i = tid; i < F; i += kThreads) mine += batch_len(batch_list(G.acc, qin[i]));
+            mine = wave_sum(mine);
+            if (lane == 0 && mine) atomicAdd(&s_edges, mine);
+            __syncthreads();
+        }
+        const uint64_t edges = s_edges;
+        if (!bottom) bottom = edges > unexplored / kBatchAlpha;
+        else if (F < n / kBatchBeta) {
+            bottom = false;
+            if (tid == 0) s_tail = 0;
+            __syncthreads();
+            for (uint32_t w = tid; w < words; w += kThreads) {
+                uint32_t x = B.fr[w];
+                uint32_t at = x ? atomicAdd(&s_tail, (uint32_t)__popc(x)) : 0u;
+                for (; x; x &= x - 1) qin[at++] = w * 32 + (uint32_t)__ffs((int)x) - 1;
+            }
+        }
+        unexplored = unexplored > edges ? unexplored - edges : 0;
+        __syncthreads();  // s_edges read, the queue written
+        if (tid == 0) {
+            s_tail = 0;
+            s_nheavy = 0;
+            s_edges = 0;
+        }
+        __syncthreads();
+        if (bottom) {
+            // a lane per unvisited vertex; the first frontier neighbour in its
+            // list is the smallest.  Long lists wait for a wave.
+            uint32_t found = 0;
+            unsigned long long sum = 0;
+            for (uint32_t v0 = wv * kWave; v0 < n; v0 += kWaves * kWave) {
+                const uint32_t v = v0 + lane;
+                const bool open = v < n && !B.in(B.vis, v);
+                if (!__ballot(open)) continue;
+                auto li = [&]() {
+                    if constexpr (IsGapAcc<Acc>::value || IsVarintAcc<Acc>::value)
+                        return batch_list(G.acc, v < n ? v : n - 1);
+                    else
+                        return wave_info(G.acc, v0, n);
+                }();
+                if (!open) continue;
+                const uint32_t len = batch_len(li);
+                if (len >= wave_threshold) {
+                    qout[atomicAdd(&s_nheavy, 1u)] = v;
+                    continue;
+                }
+                batch_lane_list(G.acc, n, li, [&](uint32_t u) {
+                    if (!B.in(B.fr, u)) return true;
+                    B.mark(v);
+                    D[v] = nd;
+                    if (P) P[v] = u;
+                    ++found;
+                    sum += len;
+                    return false;
+                });
+            }
+            __syncthreads();
+            const uint32_t nh = s_nheavy;
+            for (uint32_t h = wv; h < nh; h += kWaves) {
+                const uint32_t v = __builtin_amdgcn_readfirstlane(qout[h]);
+                const auto li = batch_list(G.acc, v);
+                batch_wave_list(G.acc, n, li, [&](bool valid, uint32_t u) {
+                    const uint64_t hit = __ballot(valid && B.in(B.fr, u));
+                    if (!hit) return true;
+                    if (lane == (uint32_t)__ffsll((long long)hit) - 1) {
+                        B.mark(v);
+                        D[v] = nd;
+                        if (P) P[v] = u;
+                        ++found;
+                        sum += batch_len(li);
+                    }
+                    return false;
+                });
+            }
+            found = wave_sum(found);
+            sum = wave_sum(sum);
+            if (lane == 0 && found) {
+                atomicAdd(&s_tail, found);
+                atomicAdd(&s_edges, sum);
+            }
+        } else {
+            for (uint32_t c0 = 0; c0 < F; c0 += chunk) {
+                const uint32_t c1 = c0 + chunk < F ? c0 + chunk : F;
+                for (uint32_t i = c0 + tid; i < c1; i += kThreads) {
+                    const uint32_t v = qin[i];
+                    const auto li = batch_list(G.acc, v);
+                    if (batch_len(li) >= wave_threshold) {
+                        s_heavy[atomicAdd(&s_nheavy, 1u)] = v;
+                    } else {
+                        batch_lane_list(G.acc, n, li, [&](uint32_t u) {
+                            batch_claim(B, u, v, nd, D, P, qout, &s_tail);
+                            return true;
+                        });
+                    }
+                }
+                __syncthreads();
+                const uint32_t nh = s_nheavy;
+                for (uint32_t h = wv; h < nh; h += kWaves) {
+                    const uint32_t v = __builtin_amdgcn_readfirstlane(s_heavy[h]);
+                    batch_wave_list(G.acc, n, batch_list(G.acc, v), [&](bool valid, uint32_t u) {
+                        if (valid) batch_claim(B, u, v, nd, D, P, qout, &s_tail);
+                        return true;
+                    });
+                }
+                __syncthreads();
+                if (tid == 0) s_nheavy = 0;
+                __syncthreads();
+            }
+            uint32_t *t = qin; qin = qout; qout = t;
+        }
+        __syncthreads();
+        F = s_tail;
+        for (uint32_t w = tid; w < words; w += kThreads) {
+            const uint32_t x = B.nx[w];
+            B.vis[w] |= x;
+            B.fr[w] = x;
+            B.nx[w] = 0;
+        }
+        __syncthreads();
+    }
+    for (uint32_t v = tid; v < n; v += kThreads)
+        if (!B.in(B.vis, v)) D[v] = -1;
+}
+
+template <class Acc, int kThreads>
+__global__ __launch_bounds__(kThreads) void bfs_batch_kernel(
+    const BatchGraph<Acc> *__restrict__ graphs, const BatchJob *__restrict__ jobs, uint32_t num_jobs,
+    uint32_t *__restrict__ job_counter, int32_t *__restrict__ depth, int32_t *__restrict__ parent,
+    int32_t max_depth, uint32_t *__restrict__ queues, uint64_t qcap, uint32_t chunk, uint32_t wave_threshold) {
+    __shared__ uint32_t s_job;
     uint32_t *qa = queues + (uint64_t)blockIdx.x * 2 * qcap;
-    uint32_t *qb = qa + qcap;
     for (;;) {
-        if (tid == 0) s_job = atomicAdd(job_counter, 1u);
+        if (threadIdx.x == 0) s_job = atomicAdd(job_counter, 1u);
         __syncthreads();
         const uint32_t job = s_job;
         if (job >= num_jobs) break;
         const BatchJob jb = jobs[job];
         const BatchGraph<Acc> G = graphs[jb.graph];
-        const uint32_t n = G.n, words = (n + 63) / 64 * 2;
-        const BatchBits B{s_bits, s_bits + words, s_bits + 2 * words};
-        int32_t *D = depth + jb.out_offset;
-        uint32_t *P = parent ? reinterpret_cast<uint32_t *>(parent + jb.out_offset) : nullptr;
-        for (uint32_t i = tid; i < 3 * words; i += kThreads) s_bits[i] = 0;
-        if (P)
-            for (uint32_t v = tid; v < n; v += kThreads) P[v] = v == jb.root ? jb.root : 0xFFFFFFFFu;
-        __syncthreads();
-        if (tid == 0) {
-            qa[0] = jb.root;
-            D[jb.root] = 0;
-            B.vis[jb.root >> 5] = B.fr[jb.root >> 5] = 1u << (jb.root & 31);
-            s_edges = 0;
-        }
-        __syncthreads();
-        uint32_t *qin = qa, *qout = qb;
-        uint32_t F = 1;                  // frontier vertices (the same in every thread, as all below)
-        uint64_t unexplored = G.m;       // entries of the lists not on a frontier yet (Varint: bytes count for entries)
-        bool bottom = false;
-        for (int32_t level = 0; F && !(max_depth >= 0 && level >= max_depth); ++level) {
-            const int32_t nd = level + 1;
-            // the frontier's entries: summed here for a queue, by the level before for a bitmap
-            if (!bottom) {
-                unsigned long long mine = 0;
-                for (uint32_t i = tid; i < F; i += kThreads) mine += batch_len(batch_list(G.acc, qin[i]));
-                mine = wave_sum(mine);
-                if (lane == 0 && mine) atomicAdd(&s_edges, mine);
-                __syncthreads();
-            }
-            const uint64_t edges = s_edges;
-            if (!bottom) bottom = edges > unexplored / kBatchAlpha;
-            else if (F < n / kBatchBeta) {
-                bottom = false;
-                if (tid == 0) s_tail = 0;
-                __syncthreads();
-                for (uint32_t w = tid; w < words; w += kThreads) {
-                    uint32_t x = B.fr[w];
-                    uint32_t at = x ? atomicAdd(&s_tail, (uint32_t)__popc(x)) : 0u;
-                    for (; x; x &= x - 1) qin[at++] = w * 32 + (uint32_t)__ffs((int)x) - 1;
-                }
-            }
-            unexplored = unexplored > edges ? unexplored - edges : 0;
-            __syncthreads();  // s_edges read, the queue written
-            if (tid == 0) {
-                s_tail = 0;
-                s_nheavy = 0;
-                s_edges = 0;
-            }
-            __syncthreads();
-            if (bottom) {
-                // a lane per unvisited vertex; the first frontier neighbour in its
-                // list is the smallest.  Long lists wait for a wave.
-                uint32_t found = 0;
-                unsigned long long sum = 0;
-                for (uint32_t v0 = wv * kWave; v0 < n; v0 += kWaves * kWave) {
-                    const uint32_t v = v0 + lane;
-                    const bool open = v < n && !B.in(B.vis, v);
-                    if (!__ballot(open)) continue;
-                    auto li = [&]() {
-                        if constexpr (IsGapAcc<Acc>::value || IsVarintAcc<Acc>::value)
-                            return batch_list(G.acc, v < n ? v : n - 1);
-                        else
-                            return wave_info(G.acc, v0, n);
-                    }();
-                    if (!open) continue;
-                    const uint32_t len = batch_len(li);
-                    if (len >= wave_threshold) {
-                        qout[atomicAdd(&s_nheavy, 1u)] = v;
-                        continue;
-                    }
-                    batch_lane_list(G.acc, n, li, [&](uint32_t u) {
-                        if (!B.in(B.fr, u)) return true;
-                        B.mark(v);
-                        D[v] = nd;
-                        if (P) P[v] = u;
-                        ++found;
-                        sum += len;
-                        return false;
-                    });
-                }
-                __syncthreads();
-                const uint32_t nh = s_nheavy;
-                for (uint32_t h = wv; h < nh; h += kWaves) {
-                    const uint32_t v = __builtin_amdgcn_readfirstlane(qout[h]);
-                    const auto li = batch_list(G.acc, v);
-                    batch_wave_list(G.acc, n, li, [&](bool valid, uint32_t u) {
-                        const uint64_t hit = __ballot(valid && B.in(B.fr, u));
-                        if (!hit) return true;
-                        if (lane == (uint32_t)__ffsll((long long)hit) - 1) {
-                            B.mark(v);
-                            D[v] = nd;
-                            if (P) P[v] = u;
-                            ++found;
-                            sum += batch_len(li);
-                        }
-                        return false;
-                    });
-                }
-                found = wave_sum(found);
-                sum = wave_sum(sum);
-                if (lane == 0 && found) {
-                    atomicAdd(&s_tail, found);
-                    atomicAdd(&s_edges, sum);
-                }
-            } else {
-                for (uint32_t c0 = 0; c0 < F; c0 += chunk) {
-                    const uint32_t c1 = c0 + chunk < F ? c0 + chunk : F;
-                    for (uint32_t i = c0 + tid; i < c1; i += kThreads) {
-                        const uint32_t v = qin[i];
-                        const auto li = batch_list(G.acc, v);
-                        if (batch_len(li) >= wave_threshold) {
-                            s_heavy[atomicAdd(&s_nheavy, 1u)] = v;
-                        } else {
-                            batch_lane_list(G.acc, n, li, [&](uint32_t u) {
-                                batch_claim(B, u, v, nd, D, P, qout, &s_tail);
-                                return true;
-                            });
-                        }
-                    }
-                    __syncthreads();
-                    const uint32_t nh = s_nheavy;
-                    for (uint32_t h = wv; h < nh; h += kWaves) {
-                        const uint32_t v = __builtin_amdgcn_readfirstlane(s_heavy[h]);
-                        batch_wave_list(G.acc, n, batch_list(G.acc, v), [&](bool valid, uint32_t u) {
-                            if (valid) batch_claim(B, u, v, nd, D, P, qout, &s_tail);
-                            return true;
-                        });
-                    }
-                    __syncthreads();
-                    if (tid == 0) s_nheavy = 0;
-                    __syncthreads();
-                }
-                uint32_t *t = qin; qin = qout; qout = t;
-            }
-            __syncthreads();
-            F = s_tail;
-            for (uint32_t w = tid; w < words; w += kThreads) {
-                const uint32_t x = B.nx[w];
-                B.vis[w] |= x;
-                B.fr[w] = x;
-                B.nx[w] = 0;
-            }
-            __syncthreads();
-        }
-        for (uint32_t v = tid; v < n; v += kThreads)
-            if (!B.in(B.vis, v)) D[v] = -1;
+        batch_search<Acc, kThreads>(G, jb.root, depth + jb.out_offset,
+                                    parent ? reinterpret_cast<uint32_t *>(parent + jb.out_offset) : nullptr, max_depth,
+                                    qa, qa + qcap, chunk, wave_threshold);
         __syncthreads();  // s_job and the bitmaps are rewritten next
     }
 }
 
+// The searches of one call on a small graph: a workgroup per root, one launch
+// and no read-back, where a wide search's levels cost three launches and a
+// read-back or two each.  Bound by the chain of levels within a workgroup
+// (Kronecker 2^12: 181 -> 61 us for one root, 960 -> 86 for 15; uniform 2^13:
+// 175 -> 114 and 801 -> 118).  Lists from 128 entries go to a wave (from 32:
+// uniform 2^13 282 us).
+constexpr uint32_t kSmallThreads = 1024, kSmallWaveList = 128;
+struct SmallRoots {
+    uint32_t v[kBfsSmallRoots];
+};
+
+template <class Acc>
+__global__ __launch_bounds__(kSmallThreads) void bfs_small_kernel(BatchGraph<Acc> G, SmallRoots roots,
+                                                                  const uint32_t *__restrict__ inv,
+                                                                  int32_t *__restrict__ depth,
+                                                                  uint32_t *__restrict__ parent, int32_t max_depth,
+                                                                  uint32_t *__restrict__ queues) {
+    const uint64_t row = (uint64_t)blockIdx.x * G.n;
+    const uint32_t root = roots.v[blockIdx.x];
+    uint32_t *qa = queues + 2 * row;
+    batch_search<Acc, kSmallThreads>(G, inv ? inv[root] : root, depth + row, parent ? parent + row : nullptr,
+                                     max_depth, qa, qa + G.n, kMaxChunk, kSmallWaveList);
+}
+
 __global__ void batch_reset_kernel(uint32_t *__restrict__ counter) {
     if (threadIdx.x == 0 && blockIdx.x == 0) *counter = 0;
+}
+
+lg_status bfs_small(lg_graph *g, const uint32_t *roots, uint32_t r, int32_t *depth, int32_t *parent,
+                    int32_t max_depth, hipStream_t s) {
+    const uint32_t n = g->n;
+    const bool rel = g->relabel != LG_RELABEL_NONE;
+    const uint64_t rows = (uint64_t)r * n;
+    DevBuf work;  // two queues a root; relabeled: rows in label space
+    LG_TRY(work.scratch(rows * 4 * (rel ? 4 : 2), s));
+    uint32_t *queues = work.as<uint32_t>();
+    int32_t *d = rel ? (int32_t *)(queues + 2 * rows) : depth;
+    uint32_t *p = !parent ? nullptr : rel ? queues + 3 * rows : reinterpret_cast<uint32_t *>(parent);
+    SmallRoots ids{};
+    for (uint32_t i = 0; i < r; ++i) ids.v[i] = roots[i];
+    LG_TRY(dispatch_acc_dec(g, [&](auto acc) -> lg_status {
+        using Acc = decltype(acc);
+        const BatchGraph<Acc> G{acc, n, IsVarintAcc<Acc>::value ? g->U / 8 : g->m};
+        LG_LAUNCH(bfs_small_kernel<Acc>, r, kSmallThreads, (uint32_t)batch_bitmap_bytes(n), s, G, ids,
+                  rel ? g->inv.as<const uint32_t>() : nullptr, d, p, max_depth, queues);
+        LG_CHECK_LAUNCH();
+        return LG_OK;
+    }));
+    if (!rel) return LG_OK;
+    return bfs_unpermute(g, d, p, r, depth, parent, s);
 }
 
 }  // namespace lg

@@ -1434,13 +1434,24 @@ __global__ void bu_varint_pending_kernel(Acc acc, uint32_t n, uint64_t np, const
 __global__ void bfs_unpermute_kernel(uint32_t n, const uint32_t *__restrict__ inv, const uint32_t *__restrict__ perm,
                                      const int32_t *__restrict__ depth_i, const uint32_t *__restrict__ parent_i,
                                      int32_t *__restrict__ depth, int32_t *__restrict__ parent) {
-    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
+    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x, row = (uint64_t)blockIdx.y * n;
+    depth_i += row;
+    depth += row;
+    if (parent) parent_i += row, parent += row;
     for (uint64_t o = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; o < n; o += stride) {
         const uint32_t x = inv[o];
         const int32_t d = depth_i[x];
         depth[o] = d;
         if (parent) parent[o] = d < 0 ? -1 : (int32_t)perm[parent_i[x]];
     }
+}
+
+lg_status bfs_unpermute(lg_graph *g, const int32_t *depth_i, const uint32_t *parent_i, uint32_t rows, int32_t *depth,
+                        int32_t *parent, hipStream_t s) {
+    LG_LAUNCH(bfs_unpermute_kernel, dim3(grid_for(g->n, 256, 1u << 16), rows), 256, 0, s, g->n,
+              g->inv.as<uint32_t>(), g->perm.as<uint32_t>(), depth_i, parent_i, depth, parent);
+    LG_CHECK_LAUNCH();
+    return LG_OK;
 }
 
 // ---------------------------------------------------------------------------
@@ -2908,6 +2919,20 @@ static lg_status bfs_run_ms(lg_graph *g, const uint32_t *roots, uint32_t r, int3
 
 }  // namespace lg
 
+namespace lg {
+// Is the stream being captured?  A captured one-launch search would replay on
+// scratch that the pool has given to others since; the other paths read back
+// and so fail in a capture.
+static bool stream_capturing(hipStream_t s) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &st) != hipSuccess) {
+        (void)hipGetLastError();
+        return true;
+    }
+    return st != hipStreamCaptureStatusNone;
+}
+}  // namespace lg
+
 extern "C" lg_status lg_bfs(const lg_graph *gc, const uint32_t *roots, uint32_t r, int32_t *depth, int32_t *parent,
                             int32_t max_depth, uint32_t flags, hipStream_t stream) {
     using namespace lg;
@@ -2917,6 +2942,11 @@ extern "C" lg_status lg_bfs(const lg_graph *gc, const uint32_t *roots, uint32_t 
     for (uint32_t i = 0; i < r; ++i)
         if (roots[i] >= g->n) { set_error("lg_bfs: root %u out of range", roots[i]); return LG_ERR_INVALID; }
     if (r == 0) return LG_OK;
+    if (flags == LG_BFS_DIRECTION_OPT && r <= kBfsSmallRoots && g->n <= kBfsSmallVertices &&
+        g->m <= (r == 1 ? kBfsSmallEntriesOne : kBfsSmallEntries) && !stream_capturing(stream)) {
+        LG_TRY(bfs_small(g, roots, r, depth, parent, max_depth, stream));
+        return mark_use(g, stream);
+    }
     const uint32_t r_ms = bfs_ms_graph(g, flags) ? bfs_ms_roots(r) : 0;
     if (r_ms) {
         LG_TRY(bfs_run_ms(g, roots, r_ms, depth, parent, max_depth, stream));

@@ -80,8 +80,9 @@ __global__ void dec_varint_degree_kernel(Acc acc, const uint32_t *__restrict__ l
 // A small request in one launch: labels, degrees, their prefix, and the two
 // values the host waits for straight into its pinned memory.  (Clearing the
 // mark, labels, degrees, scan and two copies were six launches, each longer
-// than its work: 64 lists 138 us in two calls, 77 so.)  Up to kDecSmall requests, a thread each; of Varint lists,
-// which a wave counts, up to a sixteenth of that.
+// than its work: 64 lists 138 us in two calls, 77 so.)  Up to kDecSmall
+// requests, a thread each; of Varint lists, which a wave counts, up to a
+// sixteenth of that.
 constexpr uint32_t kDecSmall = 1024;
 
 template <class Acc>

@@ -360,6 +360,21 @@ constexpr double kBfsAlphaLate = 15.0;
 constexpr double kBfsProbeCost = 1.0 / 6.0;
 
 // BFS from host roots on an explicit workspace (lg_bfs without argument checks)
+// Calls of up to 15 roots (from 16 a batch shares the traversal) on a small
+// graph run in one launch, a workgroup per root (lg_batch.hip).  A workgroup's
+// time grows with the entries, the other paths' hardly does: one root up to
+// 2^18 entries (uniform: 114 us against 175; 2^19 188 against 199, Kronecker
+// 2^20 300 against 204), several up to 2^19 (two roots 161 against 306 us,
+// relabeled 233 against 304, gap lists 249 against 353).  Sweeps over the
+// vertices are one workgroup's too: at most 2^14 (degree 8: 127 us against
+// 315).
+constexpr uint32_t kBfsSmallRoots = 15, kBfsSmallVertices = 1u << 14;
+constexpr uint64_t kBfsSmallEntriesOne = 1ull << 18, kBfsSmallEntries = 1ull << 19;
+lg_status bfs_small(lg_graph *g, const uint32_t *roots, uint32_t r, int32_t *depth, int32_t *parent,
+                    int32_t max_depth, hipStream_t stream);
+// `rows` searches' results in label space to rows by original ID
+lg_status bfs_unpermute(lg_graph *g, const int32_t *depth_i, const uint32_t *parent_i, uint32_t rows, int32_t *depth,
+                        int32_t *parent, hipStream_t stream);
 lg_status bfs_run(lg_graph *g, BfsWork &w, const uint32_t *roots, uint32_t r, int32_t *depth, int32_t *parent,
                   int32_t max_depth, uint32_t flags, hipStream_t stream, double alpha = kBfsAlphaLatency);
 // bytes of DecodeWork::head for k requests

@@ -1,6 +1,8 @@
 // lg_pagerank: pull PageRank without atomics on global memory (PR of
 // section "Considered Algorithms"), FP32 storage, decoding every list inside
-// the pull kernels.
+// the pull kernels.  It serves what propagation blocking does not
+// (pb_applies in lg_pagerank_pb.hip): fewer than 2^10 vertices, and calls of
+// few iterations on lists that are not one stream of fixed-width entries.
 //
 //   PR_0 = 1/n
 //   PR_{t+1}(v) = (1-a)/n + a (sum_{u in N_v} PR_t(u)/d_u + D_t/n)

@@ -181,16 +181,16 @@ __global__ void sssp_lists_kernel(Acc acc, uint32_t n, uint64_t *__restrict__ vs
 // The frontier is compacted without a shared counter (single-address atomics
 // from thousands of workgroups took 20 us a step).  Every workgroup has its
 // fixed tiles of bitmap words, dealt in turn (a relabeled graph's marks crowd
-// in the first words).  The count pass takes each word's marked
-// vertices below the bound out of the bitmap and leaves the workgroup's
-// vertices, entries and smallest distance left marked; the write pass sums
-// the workgroups before its own (at most kCollectParts) and places its vertices with
-// the running entry count the relax pass walks by.  Two launches for what
-// were seven (a reset, the count, two scans of up to three launches), and no
-// read-back between them: Kronecker 2^20
-// vertices, 20 steps: 2.65 -> 1.62 ms.  Every
-// marked vertex has edges (it was reached over one) but the root, which may
-// have none: it is then alone in the first frontier, which holds no edges.
+// in the first words).  The count pass takes each word's marked vertices
+// below the bound out of the bitmap and leaves the workgroup's vertices,
+// entries and smallest distance left marked; the write pass sums the
+// workgroups before its own (at most kCollectParts) and places its vertices
+// with the running entry count the relax pass walks by.  Two launches for
+// what were seven (a reset, the count, two scans of up to three launches),
+// and no read-back between them: Kronecker 2^20 vertices, 20 steps, 2.65 ->
+// 1.62 ms.  Every marked vertex has edges (it was reached over one) but the
+// root, which may have none: it is then alone in the first frontier, which
+// holds no edges.
 constexpr int kCollectThreads = 256;
 constexpr uint32_t kCollectWaves = kCollectThreads / kWave;
 constexpr uint64_t kCollectParts = 2048;
