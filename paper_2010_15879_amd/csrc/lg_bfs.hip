@@ -128,7 +128,8 @@ __global__ void bfs_init_kernel(uint32_t n, int32_t *__restrict__ depth, uint32_
     }
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         queue[0] = root;
-        for (int i = 0; i < 5; ++i) counters[i] = 0;  // queue count and both bottom-up pairs
+        // queue count, both bottom-up pairs, count of the queue built after them
+        for (int i = 0; i < 6; ++i) counters[i] = 0;
     }
 }
 
@@ -860,10 +861,11 @@ __global__ __launch_bounds__(1024) void bitmap_to_queue_kernel(uint64_t words, c
 // 1,024 threads a workgroup from 2^23 vertices, where the reservations are
 // the longer part (2^24: 33 us a launch, 41 with 256 threads); below, 256, so
 // that the queue is written from more CUs (2^20 vertices in 16 workgroups
-// cost a 64-root search 2 %).
+// cost a 64-root search 2 %), and up to 2^18 vertices a wave, at most 64
+// reservations and no barrier to wait at.
 static lg_status bitmap_to_queue(uint64_t words, const uint64_t *bits, uint32_t *queue, unsigned long long *tail,
                                  hipStream_t s) {
-    const uint32_t threads = words >= (1u << 17) ? 1024 : 256;
+    const uint32_t threads = words >= (1u << 17) ? 1024 : words > (1u << 12) ? 256 : kWave;
     LG_LAUNCH(bitmap_to_queue_kernel, grid_for(words, threads, 1u << 16), threads, 0, s, words, bits, queue, tail);
     LG_CHECK_LAUNCH();
     return LG_OK;
@@ -1759,8 +1761,8 @@ static lg_status bfs_one(lg_graph *g, BfsWork &w, Acc acc, uint32_t root_id, con
             const bool back = flags == LG_BFS_DIRECTION_OPT && now < awake && (double)now <= (double)n / kBfsBeta;
             awake = now;
             if (back) {
+                if (bu_done) LG_TRY(fill_u64((uint64_t *)ctr + 5, 0, 1, s));  // used before
                 bu_done = true;
-                LG_TRY(fill_u64((uint64_t *)ctr + 5, 0, 1, s));
                 LG_TRY(bitmap_to_queue(words, curr, qin, ctr + 5, s));
                 qsize = now;
                 topdown = true;
@@ -1792,6 +1794,7 @@ static lg_status bfs_one_inorder(lg_graph *g, BfsWork &w, Acc acc, uint32_t root
     int32_t level = 0;
     bool topdown = true;
     uint32_t bu_pair = 0;
+    bool bu_done = false;  // a bottom-up phase is over
     for (;;) {
         if (max_depth >= 0 && level >= max_depth) break;
         if (topdown) {
@@ -1972,7 +1975,8 @@ static lg_status bfs_one_inorder(lg_graph *g, BfsWork &w, Acc acc, uint32_t root
             const bool back = flags == LG_BFS_DIRECTION_OPT && now < awake && (double)now <= (double)n / kBfsBeta;
             awake = now;
             if (back) {
-                LG_TRY(fill_u64((uint64_t *)ctr + 5, 0, 1, s));
+                if (bu_done) LG_TRY(fill_u64((uint64_t *)ctr + 5, 0, 1, s));  // used before
+                bu_done = true;
                 LG_TRY(bitmap_to_queue(words, curr, qin, ctr + 5, s));
                 qsize = now;
                 topdown = true;
