@@ -385,7 +385,7 @@ lg_status decode_run(lg_graph *g, DecodeWork &w, const uint32_t *vertices, uint3
 lg_status pr_free(lg_graph *g);
 // PageRank by propagation blocking: the calls it serves, its driver, its
 // workspace (lg_pagerank_pb.hip)
-bool pb_applies(const lg_graph *g, uint32_t iters);
+bool pb_applies(const lg_graph *g, float damping, uint32_t iters);
 lg_status pagerank_pb(lg_graph *g, float damping, uint32_t iters, float *scores, hipStream_t s);
 uint64_t pb_bytes(const lg_graph *g);
 void pb_free(lg_graph *g);

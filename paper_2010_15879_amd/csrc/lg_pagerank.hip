@@ -392,7 +392,7 @@ static lg_status lg_pagerank_impl(const lg_graph *gc, float damping, uint32_t it
         LG_CHECK_LAUNCH();
         return LG_OK;
     }
-    if (pb_applies(g, iters)) return pagerank_pb(g, damping, iters, scores, stream);
+    if (pb_applies(g, damping, iters)) return pagerank_pb(g, damping, iters, scores, stream);
     if (g->layout == LG_LAYOUT_PACKED && (g->id_mode == LG_IDS_VARINT_FULL || g->id_mode == LG_IDS_VARINT_DIFF))
         return pagerank_varint(g, damping, iters, scores, stream);
     if (!g->pr) {

@@ -40,6 +40,7 @@ constexpr uint32_t kMinSrcShift = 13, kMaxSrcShift = 15;   // source block: at m
 constexpr uint32_t kMinFineShift = 8, kMaxFineShift = 14;  // bin: at most 128 KB of sums
 constexpr double kFixScale = 1152921504606846976.0;  // 2^60
 constexpr double kFixUnit = 1.0 / 1152921504606846976.0;
+constexpr double kFixMinBase = 1.0 / 34359738368.0;  // 2^-35
 constexpr uint32_t kXcdCount = 8;
 
 // below this many vertices one workgroup does most of either
@@ -149,17 +150,26 @@ static lg_status pb_take_buffers(lg_graph *g, uint64_t bytes) {
 // vertices: 5 iterations 1.27 ms by the pull, 1.34 with the build, 20
 // iterations 4.5 against 2.5; Varint differences, 2^10 vertices: 20
 // iterations 0.49 ms either way, 2^16: 5 iterations 0.68 against 0.58).
-bool pb_applies(const lg_graph *g, uint32_t iters) {
+static bool pb_always(const lg_graph *g) {
+    // Large unrelabeled local IDs among them: the pull's FP32 sums are less
+    // accurate (uniform graph, 2^22 vertices, one iteration: largest error
+    // 5.5 against 1.7 units of 2^-24; a star of 12 M vertices 441 against 1)
+    // and its gathers slower (2^24 vertices: 9.5 ms an iteration against 1.3).
+    if (g->relabel != LG_RELABEL_NONE || g->weighted || g->n < kPbAlwaysVertices) return false;
+    return g->layout == LG_LAYOUT_PLAIN || g->id_mode == LG_IDS_GLOBAL || g->id_mode == LG_IDS_LOCAL;
+}
+
+bool pb_applies(const lg_graph *g, float damping, uint32_t iters) {
     if (g->n < kPbMinVertices || g->n > kPbMaxVertices || g->m >= kPbMaxEntries) return false;
-    if (g->layout == LG_LAYOUT_PLAIN) return true;
-    if (g->weighted || g->offset_mode == LG_OFFS_INTERLEAVED_BV) return false;
-    if (g->id_mode == LG_IDS_GLOBAL) return true;
-    // Large unrelabeled local IDs are served from the first iteration: the
-    // pull's FP32 sums are less accurate (uniform graph, 2^22 vertices, one
-    // iteration: largest error 5.5 against 1.7 units of 2^-24; a star of 12 M
-    // vertices 441 against 1) and its gathers slower (2^24 vertices: 9.5 ms an
-    // iteration against 1.3).
-    if (g->id_mode == LG_IDS_LOCAL && g->relabel == LG_RELABEL_NONE && g->n >= kPbAlwaysVertices) return true;
+    const bool plain = g->layout == LG_LAYOUT_PLAIN;
+    if (!plain && (g->weighted || g->offset_mode == LG_OFFS_INTERLEAVED_BV)) return false;
+    if (pb_always(g)) return true;
+    // A score is at least the base term (1 - damping) / n.  Below 2^-35 the
+    // fixed-point unit, 2^-60, is no longer small beside an FP32 rounding of
+    // it (relabeled star of 12 M vertices, damping 1, one iteration: mean
+    // error 791 units of 2^-24, by the pull 0.3).
+    if (1.0 - (double)damping < (double)g->n * kFixMinBase) return false;
+    if (plain || g->id_mode == LG_IDS_GLOBAL) return true;
     return iters >= (g->id_mode == LG_IDS_LOCAL || g->id_mode == LG_IDS_LOCAL_GAP ? 6u : 10u);
 }
 
