@@ -219,9 +219,10 @@ lg_status lg_decode_neighbors_noalloc(const lg_graph *g, const uint32_t *vertice
  * work queued on `stream` before the call completes first, and work queued
  * on `stream` after it waits for every root.  With LG_BFS_DIRECTION_OPT, up
  * to 15 roots on a graph of at most 2^14 vertices and 2^19 entries (one root:
- * 2^18) run as one launch on `stream`, with 8 bytes of device workspace per
- * vertex and root (16 relabeled); the call returns once it is enqueued.
- * Otherwise there are two ways of running them:
+ * 2^18) run as one launch on `stream`, in one of up to 8 workspaces of 3.75
+ * MiB that belong to the device; the call returns once it is enqueued (not on
+ * hipStreamPerThread or a capturing stream).  Otherwise there are two ways of
+ * running them:
  *   - with LG_BFS_DIRECTION_OPT on a graph whose lists are not gap or Varint
  *     coded, not weighted and without bvIL offsets, the first roots go in
  *     batches of up to 64 while at least 16 are left, each batch one
@@ -505,7 +506,8 @@ const char *lg_last_error(void);
  * propagation blocking (4 bytes per stored entry each) are kept apart from
  * it: lg_free parks the pair of one graph per device for the next graph of
  * about the same size.  lg_trim frees the cache, that pair, and the
- * per-device workspaces of multi-root lg_bfs calls.  Call it when no library
+ * per-device workspaces of lg_bfs calls with several roots or on small
+ * graphs.  Call it when no library
  * call is running. */
 void lg_trim(void);
 

@@ -20,6 +20,9 @@
 // graph, replayed by lg_bfs_batch_run.
 #include <algorithm>
 #include <cstring>
+#include <map>
+#include <memory>
+#include <mutex>
 #include <vector>
 
 #include "lg_device.hpp"
@@ -567,14 +570,70 @@ __global__ void batch_reset_kernel(uint32_t *__restrict__ counter) {
     if (threadIdx.x == 0 && blockIdx.x == 0) *counter = 0;
 }
 
-lg_status bfs_small(lg_graph *g, const uint32_t *roots, uint32_t r, int32_t *depth, int32_t *parent,
-                    int32_t max_depth, hipStream_t s) {
+// Workspaces of these searches.  A call returns with its kernels still queued,
+// so what it used may only be written again after them, also when the next
+// call comes on another stream (a handle can be a new stream's, once the one
+// it named is destroyed).  A workspace therefore carries an event, and whoever
+// takes it waits for that on the device.  The lock is held while a call queues
+// its work.
+constexpr uint64_t kSmallBytes = (uint64_t)kBfsSmallRoots * kBfsSmallVertices * 16;
+constexpr size_t kSmallSlots = 8;  // per device: calls that can be in flight side by side
+struct SmallSlot {
+    DevBuf mem;  // two queues a root; relabeled: rows in label space behind them
+    hipEvent_t done = nullptr;
+    hipStream_t last = nullptr;
+    ~SmallSlot() {
+        if (done) {
+            (void)hipEventSynchronize(done);
+            (void)hipEventDestroy(done);
+        }
+    }
+};
+struct SmallSlots {
+    std::mutex mu;
+    std::map<int, std::vector<std::unique_ptr<SmallSlot>>> of;  // by device, least recently used first
+};
+static SmallSlots &small_slots() {
+    static SmallSlots *s = new SmallSlots();  // never destroyed: no frees during static teardown
+    return *s;
+}
+
+void bfs_small_trim() {
+    SmallSlots &all = small_slots();
+    std::lock_guard<std::mutex> hold(all.mu);
+    all.of.clear();
+}
+
+// the workspace that this stream used last, else an idle or a new one, else
+// the least recently used; moved to the end of `slots`
+static lg_status small_take(std::vector<std::unique_ptr<SmallSlot>> &slots, hipStream_t s) {
+    size_t at = 0;
+    while (at < slots.size() && slots[at]->last != s) ++at;
+    if (at == slots.size()) {
+        at = 0;
+        while (at < slots.size() && hipEventQuery(slots[at]->done) != hipSuccess) ++at;
+        (void)hipGetLastError();  // "not ready" is no failure
+    }
+    if (at == slots.size() && at == kSmallSlots) at = 0;
+    if (at == slots.size()) {
+        auto slot = std::make_unique<SmallSlot>();
+        LG_TRY(slot->mem.alloc(kSmallBytes));
+        LG_CHECK_HIP(hipEventCreateWithFlags(&slot->done, hipEventDisableTiming));
+        slots.push_back(std::move(slot));
+    } else {
+        LG_CHECK_HIP(hipStreamWaitEvent(s, slots[at]->done, 0));
+        std::rotate(slots.begin() + at, slots.begin() + at + 1, slots.end());
+    }
+    slots.back()->last = s;
+    return LG_OK;
+}
+
+static lg_status small_launch(lg_graph *g, SmallSlot &slot, const uint32_t *roots, uint32_t r, int32_t *depth,
+                              int32_t *parent, int32_t max_depth, hipStream_t s) {
     const uint32_t n = g->n;
     const bool rel = g->relabel != LG_RELABEL_NONE;
     const uint64_t rows = (uint64_t)r * n;
-    DevBuf work;  // two queues a root; relabeled: rows in label space
-    LG_TRY(work.scratch(rows * 4 * (rel ? 4 : 2), s));
-    uint32_t *queues = work.as<uint32_t>();
+    uint32_t *queues = slot.mem.as<uint32_t>();
     int32_t *d = rel ? (int32_t *)(queues + 2 * rows) : depth;
     uint32_t *p = !parent ? nullptr : rel ? queues + 3 * rows : reinterpret_cast<uint32_t *>(parent);
     SmallRoots ids{};
@@ -589,6 +648,22 @@ lg_status bfs_small(lg_graph *g, const uint32_t *roots, uint32_t r, int32_t *dep
     }));
     if (!rel) return LG_OK;
     return bfs_unpermute(g, d, p, r, depth, parent, s);
+}
+
+lg_status bfs_small(lg_graph *g, const uint32_t *roots, uint32_t r, int32_t *depth, int32_t *parent,
+                    int32_t max_depth, hipStream_t s) {
+    SmallSlots &all = small_slots();
+    std::lock_guard<std::mutex> hold(all.mu);
+    try {
+        auto &slots = all.of[g->device];
+        LG_TRY(small_take(slots, s));
+        const lg_status st = small_launch(g, *slots.back(), roots, r, depth, parent, max_depth, s);
+        LG_CHECK_HIP(hipEventRecord(slots.back()->done, s));
+        return st;
+    } catch (const std::bad_alloc &) {
+        set_error("lg_bfs: host allocation failed");
+        return LG_ERR_OOM;
+    }
 }
 
 }  // namespace lg

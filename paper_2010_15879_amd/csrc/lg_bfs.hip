@@ -2924,16 +2924,19 @@ static lg_status bfs_run_ms(lg_graph *g, const uint32_t *roots, uint32_t r, int3
 }  // namespace lg
 
 namespace lg {
-// Is the stream being captured?  A captured one-launch search would replay on
-// scratch that the pool has given to others since; the other paths read back
-// and so fail in a capture.
-static bool stream_capturing(hipStream_t s) {
+// May a search be left queued on this stream in one launch?  Not in a capture:
+// the launch would replay on a workspace that others have taken since (the
+// other paths read back and so fail there).  Not on hipStreamPerThread: the
+// stream is gone with its thread, and with it the order that the next user of
+// the workspace relies on.
+static bool one_launch_stream(hipStream_t s) {
+    if (s == hipStreamPerThread) return false;
     hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(s, &st) != hipSuccess) {
         (void)hipGetLastError();
-        return true;
+        return false;
     }
-    return st != hipStreamCaptureStatusNone;
+    return st == hipStreamCaptureStatusNone;
 }
 }  // namespace lg
 
@@ -2947,7 +2950,7 @@ extern "C" lg_status lg_bfs(const lg_graph *gc, const uint32_t *roots, uint32_t 
         if (roots[i] >= g->n) { set_error("lg_bfs: root %u out of range", roots[i]); return LG_ERR_INVALID; }
     if (r == 0) return LG_OK;
     if (flags == LG_BFS_DIRECTION_OPT && r <= kBfsSmallRoots && g->n <= kBfsSmallVertices &&
-        g->m <= (r == 1 ? kBfsSmallEntriesOne : kBfsSmallEntries) && !stream_capturing(stream)) {
+        g->m <= (r == 1 ? kBfsSmallEntriesOne : kBfsSmallEntries) && one_launch_stream(stream)) {
         LG_TRY(bfs_small(g, roots, r, depth, parent, max_depth, stream));
         return mark_use(g, stream);
     }

@@ -330,6 +330,7 @@ lg_status mark_use(lg_graph *g, hipStream_t stream);
 
 lg_status bfs_free(lg_graph *g);
 void bfs_pools_trim();
+void bfs_small_trim();  // frees the workspaces of bfs_small
 lg_status bfs_workspace_ensure(BfsWork &w, uint64_t n, uint64_t n_heavy, bool relabel, bool need_parent);
 // Direction switch of the direction-optimizing BFS: top-down -> bottom-up
 // when the frontier's edges exceed the unexplored edges / alpha.
