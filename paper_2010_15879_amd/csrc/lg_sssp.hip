@@ -304,8 +304,7 @@ __global__ __launch_bounds__(kCollectThreads) void sssp_write_kernel(
     __shared__ uint64_t s_wave[kCollectWaves];
     __shared__ uint64_t s_pos[kCollectTile], s_off[kCollectTile], s_take[kCollectTile];
     __shared__ unsigned long long s_left;
-    // (a block that finds `done` set by block 0 below had nothing to write)
-    if (state->done) return;
+    __shared__ bool s_done;
     const uint32_t lane = lane_id(), wv = threadIdx.x / kWave;
     // the workgroups before this one
     uint64_t cnt = 0, edges = 0, all_cnt = 0, all_edges = 0, left = kInfDist;
@@ -319,9 +318,17 @@ __global__ __launch_bounds__(kCollectThreads) void sssp_write_kernel(
         all_edges += p.edges;
         left = p.left < left ? p.left : left;
     }
-    if (threadIdx.x == 0) s_left = kInfDist;
+    // Block 0 sets `done` below while others start: one thread looks, so that a
+    // workgroup goes on or ends as a whole.  (One that sees it set in this
+    // launch had nothing to write, or the step bound was hit and nothing is
+    // relaxed.)
+    if (threadIdx.x == 0) {
+        s_left = kInfDist;
+        s_done = state->done != 0;
+    }
     uint64_t pos0, off0, total_cnt, total_edges;
     (void)collect_scan(cnt, s_wave, pos0);
+    if (s_done) return;
     (void)collect_scan(edges, s_wave, off0);
     if (blockIdx.x == 0) {
         (void)collect_scan(all_cnt, s_wave, total_cnt);
