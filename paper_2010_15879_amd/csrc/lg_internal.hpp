@@ -241,6 +241,7 @@ struct lg_graph {
     lg::BfsWork *bfs = nullptr;
     lg::PrWork *pr = nullptr;
     lg::PbWork *pb = nullptr;  // PageRank by propagation blocking (lg_pagerank_pb.hip)
+    bool pb_short = false;     // its tables did not fit into memory
     lg::DecodeWork *dec = nullptr;
     lg::SsspWork *sssp = nullptr;
     std::mutex sssp_mu;  // lg_sssp calls on this graph share `sssp`: one at a time

@@ -1,8 +1,9 @@
 // lg_pagerank: pull PageRank without atomics on global memory (PR of
 // section "Considered Algorithms"), FP32 storage, decoding every list inside
 // the pull kernels.  It serves what propagation blocking does not
-// (pb_applies in lg_pagerank_pb.hip): fewer than 2^10 vertices, and calls of
-// few iterations on lists that are not one stream of fixed-width entries.
+// (pb_applies in lg_pagerank_pb.hip): fewer than 2^10 vertices, calls of
+// few iterations on lists that are not one stream of fixed-width entries, and
+// graphs for whose tables there is no memory.
 //
 //   PR_0 = 1/n
 //   PR_{t+1}(v) = (1-a)/n + a (sum_{u in N_v} PR_t(u)/d_u + D_t/n)
@@ -392,7 +393,11 @@ static lg_status lg_pagerank_impl(const lg_graph *gc, float damping, uint32_t it
         LG_CHECK_LAUNCH();
         return LG_OK;
     }
-    if (pb_applies(g, damping, iters)) return pagerank_pb(g, damping, iters, scores, stream);
+    if (pb_applies(g, damping, iters)) {
+        // without memory for its tables (nothing has run then) the kernels below serve the call
+        const lg_status st = pagerank_pb(g, damping, iters, scores, stream);
+        if (st != LG_ERR_OOM) return st;
+    }
     if (g->layout == LG_LAYOUT_PACKED && (g->id_mode == LG_IDS_VARINT_FULL || g->id_mode == LG_IDS_VARINT_DIFF))
         return pagerank_varint(g, damping, iters, scores, stream);
     if (!g->pr) {

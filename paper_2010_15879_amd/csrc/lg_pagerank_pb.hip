@@ -160,7 +160,9 @@ static bool pb_always(const lg_graph *g) {
 }
 
 bool pb_applies(const lg_graph *g, float damping, uint32_t iters) {
-    if (g->n < kPbMinVertices || g->n > kPbMaxVertices || g->m >= kPbMaxEntries) return false;
+    // (a graph that its tables did not fit once keeps to the pull, so that its
+    // calls agree whatever else comes and goes in memory)
+    if (g->pb_short || g->n < kPbMinVertices || g->n > kPbMaxVertices || g->m >= kPbMaxEntries) return false;
     const bool plain = g->layout == LG_LAYOUT_PLAIN;
     if (!plain && (g->weighted || g->offset_mode == LG_OFFS_INTERLEAVED_BV)) return false;
     if (pb_always(g)) return true;
@@ -812,6 +814,8 @@ static lg_status pb_build_tiles(lg_graph *g, PbEntries<kPacked> ent, const uint6
                                     hipMemcpyHostToDevice, s));
         LG_TRY(W.gsum.scratch(((uint64_t)W.n_multi << W.fs) * 8, s));
     }
+    LG_TRY(W.ca.alloc((uint64_t)n * 4));
+    LG_TRY(W.cb.alloc((uint64_t)n * 4));
     LG_CHECK_HIP(hipStreamSynchronize(s));  // the host's items are copied
     W.built = true;
     return LG_OK;
@@ -873,18 +877,24 @@ lg_status pagerank_pb(lg_graph *g, float damping, uint32_t iters, float *scores,
         g->pb = new (std::nothrow) PbWork();
         if (!g->pb) { set_error("lg_pagerank: host allocation failed"); return LG_ERR_OOM; }
     }
-    PbWork &W = *g->pb;
-    const uint32_t n = g->n;
-    if (!W.built) {
+    if (!g->pb->built) {
+        lg_status st;
         try {
-            LG_TRY(pb_build(g, s));
+            st = pb_build(g, s);
         } catch (const std::bad_alloc &) {
             set_error("lg_pagerank: host allocation failed");
-            return LG_ERR_OOM;
+            st = LG_ERR_OOM;
+        }
+        if (st != LG_OK) {  // nothing is kept of a build that did not end
+            (void)hipStreamSynchronize(s);
+            g->pb_short = st == LG_ERR_OOM;
+            delete g->pb;
+            g->pb = nullptr;
+            return st;
         }
     }
-    if (W.ca.bytes < (uint64_t)n * 4) LG_TRY(W.ca.alloc((uint64_t)n * 4));
-    if (W.cb.bytes < (uint64_t)n * 4) LG_TRY(W.cb.alloc((uint64_t)n * 4));
+    PbWork &W = *g->pb;
+    const uint32_t n = g->n;
     const uint32_t *perm = g->relabel != LG_RELABEL_NONE ? g->perm.as<uint32_t>() : nullptr;
     const double nd = (double)n, a = damping, z = g->isolated;
     const uint64_t cells = (uint64_t)W.ns * W.nf;
