@@ -139,17 +139,9 @@ static lg_status pb_take_buffers(lg_graph *g, uint64_t bytes) {
     return LG_OK;
 }
 
-// Is propagation blocking the PageRank of this call?  A rule of the graph and
-// the iterations alone (never of timing or of earlier calls), so that results
-// do not depend on the run.  It beats the pull per iteration on every graph
-// measured (2 to 5 times, 2^10 to 2^25 vertices).  The line is drawn by the
-// first call on a graph, which pays for the build: lists that are one stream
-// of fixed-width entries cost about what the pull's tables cost (2^10
-// vertices, one iteration: 160 us either way); the others are decoded first,
-// which takes the pull's time for some iterations (relabeled local IDs, 2^20
-// vertices: 5 iterations 1.27 ms by the pull, 1.34 with the build, 20
-// iterations 4.5 against 2.5; Varint differences, 2^10 vertices: 20
-// iterations 0.49 ms either way, 2^16: 5 iterations 0.68 against 0.58).
+// Is propagation blocking the PageRank of this call?  A rule of the graph, the
+// damping and the iterations (never of timing), so that results do not depend
+// on the run.
 static bool pb_always(const lg_graph *g) {
     // Large unrelabeled local IDs among them: the pull's FP32 sums are less
     // accurate (uniform graph, 2^22 vertices, one iteration: largest error
@@ -171,8 +163,38 @@ bool pb_applies(const lg_graph *g, float damping, uint32_t iters) {
     // it (relabeled star of 12 M vertices, damping 1, one iteration: mean
     // error 791 units of 2^-24, by the pull 0.3).
     if (1.0 - (double)damping < (double)g->n * kFixMinBase) return false;
-    if (plain || g->id_mode == LG_IDS_GLOBAL) return true;
-    return iters >= (g->id_mode == LG_IDS_LOCAL || g->id_mode == LG_IDS_LOCAL_GAP ? 6u : 10u);
+    if (!g->m) return false;
+    // The iterations from which a graph's first call, build included, is no
+    // slower than the pull's.  12 families of lists, 2^10 to 2^23 vertices, 1
+    // to 24 edges a vertex, uniform and Kronecker, gave where the two meet.
+    // Uniform graphs: the more the shorter the lists, at a mean of 2, 4, 8, 16
+    // and 32 entries at most 25, 17, 9, 6 and 4 iterations (one stream of
+    // entries), 38, 26, 16, 11 and 7 (gap: the pull reads short lists fast,
+    // the build decodes them first; local up to 29, 22, 12, 8 and 6, under the
+    // same line, so that the two sum alike).  Skewed graphs, an eighth of the
+    // entries or more in lists above the heavy threshold, whose pull waits for
+    // its hubs: at most 5, 12.5 and 7 iterations; one stream of up to 2^16
+    // vertices wins from the first.
+    const uint64_t n = g->n, m = g->m;
+    const bool hub = (uint64_t)g->max_degree * 16 >= m, dense = m >= 64 * n;
+    const bool skewed = hub || dense || (uint64_t)g->n_heavy * g->heavy_threshold * 8 >= m;
+    if (plain || g->id_mode == LG_IDS_GLOBAL) {
+        // (hubs and long lists are also summed more exactly)
+        const uint32_t least = hub || dense || (skewed && n <= 1u << 16) ? 1 : 6;
+        return iters >= least && (skewed || iters * m >= 80 * n);
+    }
+    // A long list read in order that holds a sixteenth of the entries is the
+    // build's whole time (gap star, 2^17 vertices, 12 iterations: 0.53 ms by
+    // the pull, 1.1 with the build; 2^20.5: 1.3 and 8.8).  (Local widths, which
+    // it would not hold up, follow the same line.)
+    if (hub && g->max_degree > 1u << 14) return false;
+    if (g->id_mode == LG_IDS_LOCAL || g->id_mode == LG_IDS_LOCAL_GAP)
+        return iters >= 12 && (skewed || iters * m >= 140 * n);
+    // Varint lists: between 2^13 and 2^22 vertices skewed graphs meet at 3 to
+    // 17 iterations; uniform ones from 2^20 vertices and 16 entries a list at
+    // 2 to 15, others at 20 to hundreds or never (their lists are a few bytes,
+    // which a lane reads faster than an entry's 12 bytes stream)
+    return iters >= 16 && ((skewed && n >= 1u << 13 && n <= 1u << 22) || (n >= 1u << 20 && m >= 16 * n));
 }
 
 // ---------------------------------------------------------------------------

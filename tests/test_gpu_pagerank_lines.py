@@ -1,0 +1,67 @@
+"""Which calls build the tables of propagation blocking (8 bytes an entry that
+stay with the graph): those of enough iterations for the mean list and the
+encoding, on uniform and on skewed graphs.  Scores on both sides of a line
+within L1 1e-5 of the oracle's."""
+
+import numpy as np
+import pytest
+import torch
+
+import oracle as orc
+from paper_2010_15879_amd import graphgen as gg
+from paper_2010_15879_amd import lg
+
+pytestmark = pytest.mark.gpu
+
+
+def _uniform(n, degree):
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    return gg.canonical_csr(n, torch.randint(0, n, (degree * n,), generator=gen, device="cuda"),
+                            torch.randint(0, n, (degree * n,), generator=gen, device="cuda"))
+
+
+GRAPHS = {
+    "uniform4": lambda: _uniform((1 << 17) + 5, 4),
+    "uniform16": lambda: _uniform((1 << 14) + 5, 16),
+    "kron14": lambda: gg.kronecker(14, 16, seed=3, device="cuda"),
+    "kron17": lambda: gg.kronecker(17, 16, seed=3, device="cuda"),
+    "star": lambda: gg.canonical_csr(16000, torch.zeros(15999, dtype=torch.int64, device="cuda"),
+                                     torch.arange(1, 16000, device="cuda")),
+    "star17": lambda: gg.canonical_csr(1 << 17, torch.zeros((1 << 17) - 1, dtype=torch.int64, device="cuda"),
+                                       torch.arange(1, 1 << 17, device="cuda")),
+}
+# graph, encoding, the fewest iterations that build (None: none do)
+LINES = [
+    ("uniform4", dict(), 11), ("uniform4", dict(layout="plain", relabel=True), 11),
+    ("uniform4", dict(ids="local", offsets="ef"), 18), ("uniform4", dict(ids="local-gap"), 18),
+    ("uniform4", dict(ids="varint-diff"), None),
+    ("uniform16", dict(relabel="greedy"), 6), ("uniform16", dict(ids="local", relabel=True), 12),
+    ("uniform16", dict(ids="local-gap", offsets="ef"), 12), ("uniform16", dict(ids="varint-full"), None),
+    ("kron14", dict(), 1), ("kron14", dict(ids="varint-diff", relabel=True), 16),
+    ("kron17", dict(relabel=True), 6), ("kron17", dict(ids="local-gap"), 12),
+    ("star", dict(layout="plain"), 1), ("star", dict(ids="local", offsets="ef"), 12),
+    ("star", dict(ids="varint-full"), 16),
+    ("star17", dict(ids="local", offsets="ef"), None), ("star17", dict(ids="local-gap", relabel=True), None),
+]
+
+
+@pytest.fixture(scope="module")
+def graphs():
+    return {k: f() for k, f in GRAPHS.items()}
+
+
+@pytest.mark.parametrize("name,enc,line", LINES, ids=lambda v: v if isinstance(v, str) else
+                         "-".join(map(str, v.values())) or "global" if isinstance(v, dict) else str(v))
+def test_line(graphs, name, enc, line):
+    g = graphs[name]
+    off, col = g.numpy()
+    off, col = off.astype(np.uint64), col.view(np.uint32)
+    for iters in ([line - 1, line] if line else [30]):
+        lg.lib().lg_trim()  # buffers from the cache may be larger than asked for
+        h = lg.encode(g.row_offsets, g.col, g.n, **enc)
+        before = h.info()["device_bytes"]
+        pr = lg.pagerank(h, 0.85, iters).cpu().numpy().astype(np.float64)
+        if iters:
+            assert (h.info()["device_bytes"] - before >= 8 * g.m) == (iters == line), iters
+        assert np.abs(pr - orc.pagerank_par(off, col, 0.85, iters)).sum() <= 1e-5, iters
+        h.free()
