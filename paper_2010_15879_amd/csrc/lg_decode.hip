@@ -256,13 +256,16 @@ __global__ void dec_lists_kernel(Acc acc, uint32_t n, const uint32_t *__restrict
 }
 
 // Fixed-width and plain lists: the output is one range of entries (out_off is
-// the prefix of the list lengths), cut into equal pieces of `per` entries, a
-// wave each, whatever the list lengths.  (A wave per list left half its lanes
-// idle at degree 32 and put a dependent chain label -> offset -> list in
-// front of every list: 537 M entries in 16.7 M lists took 5.26 ms, a sixth of
-// the copy rate; a hub's list was one wave's.)  The wave finds the list of
-// its first entry with 64 probes per step, then takes 64 lists at a time: a
-// lane each decodes its list's offsets, and the lists' first entries, held
+// the prefix of the list lengths), cut into equal pieces, a wave each, whatever
+// the list lengths.  A piece is `per` units, a list counting for one beside its
+// entries, so that empty lists are shared out too (pieces of entries alone
+// left a wave millions of empty lists to step over: 1,000 entries in 2^24
+// lists 68.7 ms, now 0.33).  (A wave per list left half its lanes idle at
+// degree 32 and put a dependent chain label -> offset -> list in front of
+// every list: 537 M entries in 16.7 M lists took 5.26 ms, a sixth of the copy
+// rate; a hub's list was one wave's.)  The wave finds the lists of its ends
+// with 64 probes per step, then takes 64 lists at a time: a lane each decodes
+// its list's offsets, and the lists' first entries, held
 // across the lanes, tell every entry its list by a search with cross-lane
 // reads.  kDecSteps steps of 64 entries have their loads in flight together.
 // Same decode: 5.26 -> 1.25 ms (26-bit IDs, 4.0 GB read and written, 3.2
@@ -280,19 +283,36 @@ __global__ __launch_bounds__(256) void dec_walk_kernel(Acc acc, const uint32_t *
                                                        uint32_t *__restrict__ out_ids, uint64_t *__restrict__ keys) {
     const uint32_t lane = lane_id();
     const uint64_t wave = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave;
-    uint64_t e = wave * per;
-    if (e >= total) return;
-    const uint64_t e_end = e + per < total ? e + per : total;
-    // out_off[lo] <= e < out_off[hi]
-    uint32_t lo = 0, hi = k;
-    while (hi - lo > 1) {
-        const uint32_t step = (hi - lo + kWave - 1) / kWave;
-        const uint64_t at = (uint64_t)lo + (uint64_t)lane * step;
-        const uint64_t le = __ballot(at < hi && out_off[at < hi ? at : lo] <= e);
-        lo += (uint32_t)(__popcll(le) - 1) * step;
-        hi = hi - lo > step ? lo + step : hi;
+    // the piece's units and, for its two ends, the last list whose own unit is
+    // not after them (both searches' loads in flight together)
+    const uint64_t units = total + k;
+    const uint64_t d[2] = {wave * per, wave * per + per < units ? wave * per + per : units};
+    if (d[0] >= units) return;
+    uint32_t lo[2] = {0, 0}, hi[2] = {k, k};
+    while (hi[0] - lo[0] > 1 || hi[1] - lo[1] > 1) {
+        uint32_t step[2];
+        bool le[2];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            step[q] = (hi[q] - lo[q] + kWave - 1) / kWave;
+            const uint64_t at = (uint64_t)lo[q] + (uint64_t)lane * step[q];
+            const uint64_t i = at < hi[q] ? at : lo[q];
+            le[q] = at < hi[q] && out_off[i] + i <= d[q];
+        }
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            lo[q] += (uint32_t)(__popcll(__ballot(le[q])) - 1) * step[q];
+            hi[q] = hi[q] - lo[q] > step[q] ? lo[q] + step[q] : hi[q];
+        }
     }
-    for (uint64_t r = lo; e < e_end; r += kWave) {
+    // the entries before a unit: it less the lists begun by then
+    auto before = [&](int q) {
+        const uint64_t o = out_off[lo[q]];
+        return o + lo[q] == d[q] ? o : d[q] - lo[q] - 1;
+    };
+    uint64_t e = before(0);
+    const uint64_t e_end = before(1);
+    for (uint64_t r = lo[0]; e < e_end; r += kWave) {
         // lane's list: its first entry relative to e, and where its entry
         // number x of the whole output would lie, less x elements
         const uint64_t i = r + lane;
@@ -552,11 +572,12 @@ static lg_status dec_lists(const lg_graph *g, Acc acc, const uint32_t *labels, u
                           g->vseg_off.as<uint64_t>(), g->vseg_base.as<uint32_t>(), g->vseg_bytes);
         }
     } else {
-        // pieces of 256 entries (one step of the walk) up to 4,096; in
+        // pieces of 256 units (one step of the walk) up to 4,096; in
         // between, as many as fill the device twice
-        uint64_t per = (total / (2 * kDecWaves) + 255) & ~255ull;
+        const uint64_t units = total + k;
+        uint64_t per = (units / (2 * kDecWaves) + 255) & ~255ull;
         per = per < 256 ? 256 : (per > 4096 ? 4096 : per);
-        LG_LAUNCH((dec_walk_kernel<Acc, kSorted>), grid_for((total + per - 1) / per * kWave, 256), 256, 0, stream,
+        LG_LAUNCH((dec_walk_kernel<Acc, kSorted>), grid_for((units + per - 1) / per * kWave, 256), 256, 0, stream,
                   acc, labels, k, total, (uint32_t)per, out_off, perm, out_ids, keys);
     }
     LG_CHECK_LAUNCH();
