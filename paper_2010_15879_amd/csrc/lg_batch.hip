@@ -38,7 +38,8 @@ template <class Acc>
 struct BatchGraph {
     Acc acc;
     uint32_t n;
-    uint64_t m;
+    uint64_t m;        // entries (Varint: bytes)
+    uint64_t longest;  // no list is longer (Varint: in bytes, five a value)
 };
 
 struct BatchJob {
@@ -363,13 +364,27 @@ __device__ __forceinline__ uint32_t batch_len(const ulonglong2 &i) { return (uin
 // searches over 64 Kronecker graphs of 2^12 to 2^16 vertices: 24.1 ms
 // top-down over depths in memory, 1.2 ms; 256 over 16 graphs of 2^14 to 2^18:
 // 50.0 and 3.5 ms.
+//
+// Long chains are levels of a few vertices, each the chain of loads once and
+// its barriers.  A level therefore sums its frontier's entries ahead only
+// where that many could turn it bottom-up, settles the bitmaps by the queue
+// while that is the shorter, and has its counters doubled instead of cleared
+// between two barriers: two barriers a level, where no list is long (path of
+// 2^16 vertices: 155 ms with five and a pass over the bitmaps, 114 ms so; over
+// depths in memory 117).
+struct BatchCounters {
+    uint32_t tail;              // vertices found
+    unsigned long long edges;   // entries of the frontier (top-down) or of the vertices found (bottom-up)
+    unsigned long long ahead;   // entries of the frontier summed ahead, or the places taken of a queue
+};
+
 template <class Acc, int kThreads>
 __device__ __forceinline__ void batch_search(const BatchGraph<Acc> &G, uint32_t root, int32_t *__restrict__ D,
                                              uint32_t *__restrict__ P, int32_t max_depth, uint32_t *qa, uint32_t *qb,
                                              uint32_t chunk, uint32_t wave_threshold) {
     extern __shared__ uint32_t s_bits[];
-    __shared__ uint32_t s_tail, s_nheavy;
-    __shared__ unsigned long long s_edges;
+    __shared__ BatchCounters s_ctr[2];  // of odd and even levels
+    __shared__ uint32_t s_nheavy;
     __shared__ uint32_t s_heavy[kMaxChunk];
     const uint32_t tid = threadIdx.x;
     const uint32_t lane = lane_id();
@@ -384,44 +399,59 @@ __device__ __forceinline__ void batch_search(const BatchGraph<Acc> &G, uint32_t 
     if (tid == 0) {
         qa[0] = root;
         D[root] = 0;
-        B.vis[root >> 5] = B.fr[root >> 5] = 1u << (root & 31);
-        s_edges = 0;
+        B.vis[root >> 5] = 1u << (root & 31);
+        s_ctr[0] = s_ctr[1] = BatchCounters{0, 0, 0};
+        s_nheavy = 0;
     }
     __syncthreads();
+    const bool long_lists = G.longest >= wave_threshold;
     uint32_t *qin = qa, *qout = qb;
     uint32_t F = 1;                  // frontier vertices (the same in every thread, as all below)
     uint64_t unexplored = G.m;       // entries of the lists not on a frontier yet (Varint: bytes count for entries)
-    bool bottom = false;
+    uint64_t edges = 0;              // entries of the frontier, where known
+    bool bottom = false;             // the frontier is the bitmap fr, else the queue qin
+    bool marked = false;             // fr holds an earlier frontier
     for (int32_t level = 0; F && !(max_depth >= 0 && level >= max_depth); ++level) {
         const int32_t nd = level + 1;
-        // the frontier's entries: summed here for a queue, by the level before for a bitmap
-        if (!bottom) {
+        BatchCounters &ctr = s_ctr[level & 1];
+        // the other level's were last read before the barrier that ended it
+        if (tid == 0) s_ctr[(level & 1) ^ 1] = BatchCounters{0, 0, 0};
+        bool counted = true;
+        if (bottom) {
+            if (F < n / kBatchBeta) {
+                bottom = false;
+                for (uint32_t w = tid; w < words; w += kThreads) {
+                    uint32_t x = B.fr[w];
+                    uint32_t at = x ? (uint32_t)atomicAdd(&ctr.ahead, (unsigned long long)__popc(x)) : 0u;
+                    for (; x; x &= x - 1) qin[at++] = w * 32 + (uint32_t)__ffs((int)x) - 1;
+                }
+                __syncthreads();
+            }
+        } else if (F * G.longest > unexplored / kBatchAlpha) {
             unsigned long long mine = 0;
             for (uint32_t i = tid; i < F; i += kThreads) mine += batch_len(batch_list(G.acc, qin[i]));
             mine = wave_sum(mine);
-            if (lane == 0 && mine) atomicAdd(&s_edges, mine);
+            if (lane == 0 && mine) atomicAdd(&ctr.ahead, mine);
             __syncthreads();
-        }
-        const uint64_t edges = s_edges;
-        if (!bottom) bottom = edges > unexplored / kBatchAlpha;
-        else if (F < n / kBatchBeta) {
-            bottom = false;
-            if (tid == 0) s_tail = 0;
-            __syncthreads();
-            for (uint32_t w = tid; w < words; w += kThreads) {
-                uint32_t x = B.fr[w];
-                uint32_t at = x ? atomicAdd(&s_tail, (uint32_t)__popc(x)) : 0u;
-                for (; x; x &= x - 1) qin[at++] = w * 32 + (uint32_t)__ffs((int)x) - 1;
+            edges = ctr.ahead;
+            bottom = edges > unexplored / kBatchAlpha;
+            if (bottom) {
+                if (marked) {
+                    for (uint32_t w = tid; w < words; w += kThreads) B.fr[w] = 0;
+                    __syncthreads();
+                }
+                marked = true;
+                for (uint32_t i = tid; i < F; i += kThreads) {
+                    const uint32_t u = qin[i];
+                    atomicOr(&B.fr[u >> 5], 1u << (u & 31));
+                }
+                __syncthreads();
             }
+        } else {
+            counted = false;  // by the level itself
+            edges = 0;
         }
         unexplored = unexplored > edges ? unexplored - edges : 0;
-        __syncthreads();  // s_edges read, the queue written
-        if (tid == 0) {
-            s_tail = 0;
-            s_nheavy = 0;
-            s_edges = 0;
-        }
-        __syncthreads();
         if (bottom) {
             // a lane per unvisited vertex; the first frontier neighbour in its
             // list is the smallest.  Long lists wait for a wave.
@@ -474,46 +504,73 @@ __device__ __forceinline__ void batch_search(const BatchGraph<Acc> &G, uint32_t 
             found = wave_sum(found);
             sum = wave_sum(sum);
             if (lane == 0 && found) {
-                atomicAdd(&s_tail, found);
-                atomicAdd(&s_edges, sum);
+                atomicAdd(&ctr.tail, found);
+                atomicAdd(&ctr.edges, sum);
             }
         } else {
+            unsigned long long mine = 0;
             for (uint32_t c0 = 0; c0 < F; c0 += chunk) {
                 const uint32_t c1 = c0 + chunk < F ? c0 + chunk : F;
                 for (uint32_t i = c0 + tid; i < c1; i += kThreads) {
                     const uint32_t v = qin[i];
                     const auto li = batch_list(G.acc, v);
-                    if (batch_len(li) >= wave_threshold) {
+                    const uint32_t len = batch_len(li);
+                    mine += len;
+                    if (len >= wave_threshold) {
                         s_heavy[atomicAdd(&s_nheavy, 1u)] = v;
                     } else {
                         batch_lane_list(G.acc, n, li, [&](uint32_t u) {
-                            batch_claim(B, u, v, nd, D, P, qout, &s_tail);
+                            batch_claim(B, u, v, nd, D, P, qout, &ctr.tail);
                             return true;
                         });
                     }
                 }
+                if (!long_lists) continue;  // nothing is left for the waves
                 __syncthreads();
                 const uint32_t nh = s_nheavy;
                 for (uint32_t h = wv; h < nh; h += kWaves) {
                     const uint32_t v = __builtin_amdgcn_readfirstlane(s_heavy[h]);
                     batch_wave_list(G.acc, n, batch_list(G.acc, v), [&](bool valid, uint32_t u) {
-                        if (valid) batch_claim(B, u, v, nd, D, P, qout, &s_tail);
+                        if (valid) batch_claim(B, u, v, nd, D, P, qout, &ctr.tail);
                         return true;
                     });
                 }
+                if (c1 == F) break;
                 __syncthreads();
                 if (tid == 0) s_nheavy = 0;
                 __syncthreads();
             }
+            if (!counted) {
+                mine = wave_sum(mine);
+                if (lane == 0 && mine) atomicAdd(&ctr.edges, mine);
+            }
             uint32_t *t = qin; qin = qout; qout = t;
         }
         __syncthreads();
-        F = s_tail;
-        for (uint32_t w = tid; w < words; w += kThreads) {
-            const uint32_t x = B.nx[w];
-            B.vis[w] |= x;
-            B.fr[w] = x;
-            B.nx[w] = 0;
+        F = ctr.tail;
+        if (tid == 0) s_nheavy = 0;
+        if (bottom) {
+            edges = ctr.edges;
+            for (uint32_t w = tid; w < words; w += kThreads) {
+                const uint32_t x = B.nx[w];
+                B.vis[w] |= x;
+                B.fr[w] = x;
+                B.nx[w] = 0;
+            }
+        } else {
+            if (!counted) unexplored = unexplored > ctr.edges ? unexplored - ctr.edges : 0;
+            if (F < words) {
+                for (uint32_t i = tid; i < F; i += kThreads) {
+                    const uint32_t u = qin[i];
+                    atomicOr(&B.vis[u >> 5], 1u << (u & 31));
+                    B.nx[u >> 5] = 0;  // (all its bits are in the queue)
+                }
+            } else {
+                for (uint32_t w = tid; w < words; w += kThreads) {
+                    B.vis[w] |= B.nx[w];
+                    B.nx[w] = 0;
+                }
+            }
         }
         __syncthreads();
     }
@@ -640,7 +697,8 @@ static lg_status small_launch(lg_graph *g, SmallSlot &slot, const uint32_t *root
     for (uint32_t i = 0; i < r; ++i) ids.v[i] = roots[i];
     LG_TRY(dispatch_acc_dec(g, [&](auto acc) -> lg_status {
         using Acc = decltype(acc);
-        const BatchGraph<Acc> G{acc, n, IsVarintAcc<Acc>::value ? g->U / 8 : g->m};
+        const BatchGraph<Acc> G{acc, n, IsVarintAcc<Acc>::value ? g->U / 8 : g->m,
+                                (uint64_t)g->max_degree * (IsVarintAcc<Acc>::value ? 5 : 1)};
         LG_LAUNCH(bfs_small_kernel<Acc>, r, kSmallThreads, (uint32_t)batch_bitmap_bytes(n), s, G, ids,
                   rel ? g->inv.as<const uint32_t>() : nullptr, d, p, max_depth, queues);
         LG_CHECK_LAUNCH();
@@ -744,6 +802,7 @@ static lg_status batch_build(lg_batch_plan *p, const lg_graph *const *gs, bool a
         else hg[i].acc = Acc{g->plain_view()};
         hg[i].n = g->n;
         hg[i].m = IsVarintAcc<Acc>::value ? g->U / 8 : g->m;
+        hg[i].longest = (uint64_t)g->max_degree * (IsVarintAcc<Acc>::value ? 5 : 1);
     }
     LG_TRY(p->graphs.alloc(sizeof(BatchGraph<Acc>) * hg.size()));
     LG_CHECK_HIP(hipMemcpy(p->graphs.p, hg.data(), sizeof(BatchGraph<Acc>) * hg.size(), hipMemcpyHostToDevice));
