@@ -297,6 +297,7 @@ def sssp(g: Graph, root: int, delta: int = 0, stream=None) -> torch.Tensor:
 
 
 _DECODE_GUESS_MAX = 1 << 24  # ids a decode without a capacity allocates ahead
+_DECODE_SPARE = 1 << 16      # ids a result may hold unused beside as many as its own
 
 
 def decode_neighbors(g: Graph, vertices: torch.Tensor, flags="sorted", cap: Optional[int] = None, stream=None):
@@ -308,17 +309,24 @@ def decode_neighbors(g: Graph, vertices: torch.Tensor, flags="sorted", cap: Opti
     s = _stream(stream)
     if cap is None:
         # room for a quarter more than k lists of the mean length: one call
-        # then serves most requests.  A request that needs more has its
-        # lengths counted by that call and is decoded by a second one (64
-        # lists of a 2^16-vertex graph: two calls 79 us, one 51 us).
-        cap = min(int(1.25 * k * g.mean_list) + 256, _DECODE_GUESS_MAX)
-        ids = torch.empty(cap, dtype=torch.int32, device=dev)
-        st = lib().lg_decode_neighbors(g.handle, vptr, k, off.data_ptr(), ids.data_ptr(), cap, DECODE_FLAGS[flags], s)
-        if st == LG_OK:
-            return off, ids[: int(off[-1].item())]
-        if st != LG_ERR_CAPACITY:
+        # then serves most requests.  A request that needs more, or for which
+        # there is no such room, has its lengths counted by that call and is
+        # decoded by a second one (64 lists of a 2^16-vertex graph: two calls
+        # 79 us, one 51 us).
+        guess = min(int(1.25 * k * g.mean_list) + 256, _DECODE_GUESS_MAX)
+        try:
+            ids = torch.empty(guess, dtype=torch.int32, device=dev)
+        except torch.OutOfMemoryError:
+            guess, ids = 0, None
+        st = lib().lg_decode_neighbors(g.handle, vptr, k, off.data_ptr(), ids.data_ptr() if guess else None, guess,
+                                       DECODE_FLAGS[flags], s)
+        if st not in (LG_OK, LG_ERR_CAPACITY):
             _check(st)
         cap = int(off[-1].item())
+        if st == LG_OK and ids is not None:
+            # a result much smaller than the guess does not hold on to it
+            return off, ids[:cap] if guess <= 2 * cap + _DECODE_SPARE else ids[:cap].clone()
+        ids = None
     ids = torch.empty(max(cap, 1), dtype=torch.int32, device=dev)
     _check(lib().lg_decode_neighbors(g.handle, vptr, k, off.data_ptr(), ids.data_ptr(), cap, DECODE_FLAGS[flags], s))
     return off, ids[: int(off[-1].item())]
