@@ -233,10 +233,11 @@ lg_status lg_decode_neighbors_noalloc(const lg_graph *g, const uint32_t *vertice
  *     stays within 16 GiB); the host reads a few
  *     counters per level, so the call returns when these batches are done;
  *   - the other roots run a few at a time, each on its own internal stream
- *     with its own workspace (32 bytes per vertex, 40 relabeled, and on graphs
- *     of at least 2^20 vertices up to 14 bytes per edge of the largest
- *     top-down level, at most 2.25 GiB, done without when it cannot be had);
- *     the call returns once each is enqueued.
+ *     with its own workspace (32 bytes per vertex, 40 relabeled); the call
+ *     returns once each is enqueued.
+ * Searches of one root at a time on graphs of at least 2^20 vertices borrow a
+ * buffer of the device for their large top-down levels (14 bytes per edge of
+ * the level, at most 2.25 GiB, done without when it cannot be had).
  * These streams and workspaces belong to the device, not to the graph: they
  * grow to the largest graph searched and stay until lg_trim; multi-root
  * calls on one device run one after the other.
@@ -513,7 +514,7 @@ const char *lg_last_error(void);
  * it: lg_free parks the pair of one graph per device for the next graph of
  * about the same size.  lg_trim frees the cache, that pair, and the
  * per-device workspaces of lg_bfs calls with several roots or on small
- * graphs.  Call it when no library
+ * graphs, and the buffers of large top-down levels.  Call it when no library
  * call is running. */
 void lg_trim(void);
 

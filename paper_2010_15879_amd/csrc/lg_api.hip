@@ -133,6 +133,9 @@ lg_status DevBuf::alloc(uint64_t nbytes) {
     if (e != hipSuccess) {  // the scratch cache may hold the memory: give it back, try once more
         (void)hipGetLastError();
         pool_drop_device();
+        int dev = 0;
+        (void)hipGetDevice(&dev);
+        bfs_claims_trim(dev);
         e = hipMalloc(&p, nbytes);
     }
     if (e != hipSuccess) {
@@ -441,6 +444,7 @@ extern "C" const char *lg_last_error(void) { return lg::t_err; }
 extern "C" void lg_trim(void) {
     lg::bfs_pools_trim();
     lg::bfs_small_trim();
+    lg::bfs_claims_trim();
     lg::pb_trim();
     lg::Pool &pl = lg::pool();
     std::lock_guard<std::mutex> g(pl.mu);

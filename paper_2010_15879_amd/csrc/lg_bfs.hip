@@ -38,8 +38,7 @@ namespace lg {
 uint64_t BfsWork::bytes() const {
     return qa.bytes + qb.bytes + fstart.bytes + fdeg.bytes + fw.bytes + fscan.bytes + visited.bytes + curr.bytes +
            next.bytes + counters.bytes + sample.bytes + depth_i.bytes + parent_i.bytes + scan_tmp.bytes + pv.bytes +
-           pstart.bytes +
-           pdeg.bytes + pw.bytes + pseg_cnt.bytes + pseg_off.bytes + claims.bytes;
+           pstart.bytes + pdeg.bytes + pw.bytes + pseg_cnt.bytes + pseg_off.bytes;
 }
 
 BfsWork::~BfsWork() {
@@ -1463,6 +1462,72 @@ lg_status bfs_unpermute(lg_graph *g, const int32_t *depth_i, const uint32_t *par
 // bottom-up -> top-down when the frontier shrinks below n / kBfsBeta
 constexpr double kBfsBeta = 18.0;
 
+// Buffers for the claims of binned levels: a level borrows one and gives it
+// back when the host has seen the level end.  They belong to the device, so
+// that it holds as many as levels ever ran at once (at 14 bytes per edge of
+// the largest, a multiple of a search's other workspace), not one a graph.
+namespace {
+struct ClaimBuffers {
+    std::mutex mu;
+    std::vector<std::pair<int, DevBuf>> idle;  // by device
+};
+ClaimBuffers &claim_buffers() {
+    static ClaimBuffers *c = new ClaimBuffers();  // never destroyed: no frees during static teardown
+    return *c;
+}
+struct Claims {
+    DevBuf mem;
+    int device;
+    hipStream_t s;
+    Claims(int dev, hipStream_t stream) : device(dev), s(stream) {}
+    ~Claims() {
+        if (!mem.p) return;
+        (void)hipStreamSynchronize(s);  // the level failed: its kernels may still run
+        give_back();
+    }
+    // the smallest idle buffer of `bytes`, else a new one in place of the largest
+    lg_status take(uint64_t bytes) {
+        ClaimBuffers &all = claim_buffers();
+        {
+            std::lock_guard<std::mutex> hold(all.mu);
+            size_t best = all.idle.size();
+            for (size_t i = 0; i < all.idle.size(); ++i) {
+                if (all.idle[i].first != device) continue;
+                if (best < all.idle.size()) {
+                    const uint64_t a = all.idle[i].second.bytes, b = all.idle[best].second.bytes;
+                    if (b >= bytes ? a < bytes || a >= b : a <= b) continue;
+                }
+                best = i;
+            }
+            if (best < all.idle.size()) {
+                mem = std::move(all.idle[best].second);
+                all.idle.erase(all.idle.begin() + (long)best);
+            }
+        }
+        return mem.bytes >= bytes && mem.p ? LG_OK : mem.alloc(bytes + bytes / 8);
+    }
+    void give_back() {
+        if (!mem.p) return;
+        ClaimBuffers &all = claim_buffers();
+        std::lock_guard<std::mutex> hold(all.mu);
+        try {
+            all.idle.emplace_back(device, std::move(mem));
+        } catch (const std::bad_alloc &) {
+            mem.release();
+        }
+    }
+};
+}  // namespace
+
+void bfs_claims_trim(int device) {
+    ClaimBuffers &all = claim_buffers();
+    std::lock_guard<std::mutex> hold(all.mu);
+    for (size_t i = 0; i < all.idle.size();) {
+        if (device >= 0 && all.idle[i].first != device) ++i;
+        else all.idle.erase(all.idle.begin() + (long)i);
+    }
+}
+
 // A top-down level of `edges` edges by bins, when it pays: from 2^20
 // vertices (below, the parents stay in the caches), 2^20 edges (128 tiles; a
 // search of 2^20 vertices with a level of 343 K edges took 318 us against
@@ -1478,7 +1543,7 @@ constexpr uint64_t kTdBinMaxBytes = 2ull << 30;
 template <class Acc, bool kParent>
 static lg_status td_binned(BfsWork &w, Acc acc, uint32_t n, const uint32_t *queue, uint32_t qsize, uint64_t edges,
                            uint64_t *visited, int32_t *depth, uint32_t *parent, int32_t next_depth,
-                           uint64_t *frontier, hipStream_t s, bool &done) {
+                           uint64_t *frontier, hipStream_t s, Claims &claims, bool &done) {
     done = false;
     if (n < kTdBinMinVertices || n > kTdBinMaxVertices || edges < n / 4 || edges < kTdBinMinEdges) return LG_OK;
     const uint32_t shift = n > (1u << 26) ? 15 : 14;
@@ -1486,15 +1551,15 @@ static lg_status td_binned(BfsWork &w, Acc acc, uint32_t n, const uint32_t *queu
     const uint64_t cap = (edges / bins + edges / bins / 2 + 1024 + 63) & ~63ull;
     const uint64_t bytes = cap * bins * 8 + (uint64_t)bins * 4;
     if (bytes > kTdBinMaxBytes) return LG_OK;
-    if (w.claims.bytes < bytes && w.claims.ensure(bytes + bytes / 8) != LG_OK) return LG_OK;
-    uint32_t *fill = reinterpret_cast<uint32_t *>(w.claims.as<char>() + cap * bins * 8);
+    if (claims.take(bytes) != LG_OK) return LG_OK;
+    uint32_t *fill = reinterpret_cast<uint32_t *>(claims.mem.as<char>() + cap * bins * 8);
     LG_TRY(fill_u32(fill, 0, bins, s));
     LG_LAUNCH((td_bin_kernel<Acc, kParent>), grid_for(edges, kTdBinTile, 1u << 20), kTdBinThreads, bins * 8, s, acc,
               queue, qsize, w.fstart.as<uint64_t>(), w.fw.as<uint32_t>(), w.fscan.as<uint64_t>(), edges, depth,
-              parent, visited, next_depth, shift, bins, (uint32_t)cap, w.claims.as<uint2>(), fill);
+              parent, visited, next_depth, shift, bins, (uint32_t)cap, claims.mem.as<uint2>(), fill);
     LG_CHECK_LAUNCH();
     LG_LAUNCH(td_bin_finish_kernel<kParent>, bins, 1024, 4u << shift, s, n, shift, (uint32_t)cap,
-              (const uint2 *)w.claims.p, (const uint32_t *)fill, visited, parent, depth, next_depth, frontier);
+              (const uint2 *)claims.mem.p, (const uint32_t *)fill, visited, parent, depth, next_depth, frontier);
     LG_CHECK_LAUNCH();
     done = true;
     return LG_OK;
@@ -1647,10 +1712,11 @@ static lg_status bfs_one(lg_graph *g, BfsWork &w, Acc acc, uint32_t root_id, con
             // appends; a pass over the vertices then finds the new ones
             const bool claim_min = fedges > (uint64_t)n / 16;
             bool binned = false;
+            Claims claims(g->device, s);
             if (claim_min && banded) {
                 auto bin = [&](auto kpar) -> lg_status {
                     return td_binned<Acc, decltype(kpar)::value>(w, acc, n, qin, (uint32_t)qsize, fedges, visited,
-                                                                 depth, parent, level + 1, curr, s, binned);
+                                                                 depth, parent, level + 1, curr, s, claims, binned);
                 };
                 if (parent) LG_TRY(bin(std::true_type{}));
                 else LG_TRY(bin(std::false_type{}));
@@ -1691,6 +1757,7 @@ static lg_status bfs_one(lg_graph *g, BfsWork &w, Acc acc, uint32_t root_id, con
                 LG_TRY(bitmap_to_queue(words, curr, qout, ctr, s));
                 LG_CHECK_HIP(hipMemcpyAsync(w.host, ctr, 8, hipMemcpyDeviceToHost, s));
                 LG_CHECK_HIP(hipStreamSynchronize(s));
+                claims.give_back();
                 qsize = w.host[0];
                 LG_TRY(fill_u64((uint64_t *)ctr, 0, 1, s));  // the next level's queue counter
                 curr_level = level + 1;

@@ -110,7 +110,6 @@ struct BfsWork {
     DevBuf pv, pstart, pdeg, pw; // bottom-up: heavy vertices left for the segment pass
     DevBuf pseg_cnt, pseg_off;
     DevBuf depth_i, parent_i;    // label-space results when relabeled
-    DevBuf claims;               // binned top-down levels: the bins' claims, then their counts
     DevBuf scan_tmp;
     uint64_t *host = nullptr;    // pinned readback slots
     BfsWork() = default;
@@ -332,6 +331,7 @@ lg_status mark_use(lg_graph *g, hipStream_t stream);
 lg_status bfs_free(lg_graph *g);
 void bfs_pools_trim();
 void bfs_small_trim();  // frees the workspaces of bfs_small
+void bfs_claims_trim(int device = -1);  // frees the claim buffers that no level uses (of one device, or all)
 lg_status bfs_workspace_ensure(BfsWork &w, uint64_t n, uint64_t n_heavy, bool relabel, bool need_parent);
 // Direction switch of the direction-optimizing BFS: top-down -> bottom-up
 // when the frontier's edges exceed the unexplored edges / alpha.
