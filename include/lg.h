@@ -230,7 +230,7 @@ lg_status lg_decode_neighbors_noalloc(const lg_graph *g, const uint32_t *vertice
  *     per vertex, 36 bytes per vertex of device workspace; on a relabeled
  *     graph also the batch's results in label space, 5 bytes per vertex and
  *     root, roots rounded up to 16, 32 or 64, 9 past 254 levels, when that
- *     stays within 16 GiB); the host reads a few
+ *     stays within 16 GiB and there is room); the host reads a few
  *     counters per level, so the call returns when these batches are done;
  *   - the other roots run a few at a time, each on its own internal stream
  *     with its own workspace (32 bytes per vertex, 40 relabeled); the call

@@ -2784,13 +2784,15 @@ static lg_status bfs_ms_batch(lg_graph *g, BfsWork &w, MsWork &ms, Acc acc, cons
         if (!b.running()) return rows(bytes);
         // deeper than a byte: the cells widen once
         const uint64_t all = (uint64_t)n * stride;
-        LG_TRY(ms.cell_wide.ensure(all * 4));
-        LG_LAUNCH(ms_widen_kernel, grid_for(all, 256 * 8, 1u << 16), 256, 0, s, all,
-                  (const uint8_t *)ms.cell_depth.p, ms.cell_wide.as<int32_t>());
-        LG_CHECK_LAUNCH();
-        const MsCells<int32_t> wide{ms.cell_wide.as<int32_t>(), parent, stride};
-        while (b.running()) LG_TRY(ms_level(b, acc, wide));
-        return rows(wide);
+        if (ms.cell_wide.ensure(all * 4) == LG_OK) {
+            LG_LAUNCH(ms_widen_kernel, grid_for(all, 256 * 8, 1u << 16), 256, 0, s, all,
+                      (const uint8_t *)ms.cell_depth.p, ms.cell_wide.as<int32_t>());
+            LG_CHECK_LAUNCH();
+            const MsCells<int32_t> wide{ms.cell_wide.as<int32_t>(), parent, stride};
+            while (b.running()) LG_TRY(ms_level(b, acc, wide));
+            return rows(wide);
+        }
+        b.level = 0;  // no memory to widen into: from the start, in rows
     }
     const MsRows out{depth_out, parent_out, n};
     LG_TRY(ms_begin(b, roots, out));
@@ -2963,14 +2965,16 @@ static lg_status bfs_run_ms(lg_graph *g, const uint32_t *roots, uint32_t r, int3
     LG_TRY(ms.pend_m.ensure(n * 8));
     LG_TRY(ms.roots.ensure(kMsRoots * 4));
     // relabeled graphs: a batch's label-space cells in a workspace when they
-    // stay within kMsCellsCap (else rows are copied aside one by one)
+    // stay within kMsCellsCap and fit into memory (else rows are copied aside
+    // one by one)
     bool cells = false;
     if (g->relabel != LG_RELABEL_NONE) {
         const uint64_t all = n * ms_stride(std::min<uint32_t>(r, kMsRoots));
         cells = all * (parent ? 8 : 4) <= kMsCellsCap;
-        if (cells) {
-            LG_TRY(ms.cell_depth.ensure(all));
-            if (parent) LG_TRY(ms.cell_parent.ensure(all * 4));
+        if (cells && (ms.cell_depth.ensure(all) != LG_OK || (parent && ms.cell_parent.ensure(all * 4) != LG_OK))) {
+            ms.cell_depth.release();
+            ms.cell_parent.release();
+            cells = false;
         }
     }
     // lane 0's stream is not used: everything runs on the caller's stream
