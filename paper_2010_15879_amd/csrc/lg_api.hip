@@ -226,6 +226,12 @@ static bool prof_match(const char *filter, const char *name) {
 ProfMark prof_begin(const char *name, hipStream_t stream) {
     ProfState &st = prof();
     if (st.filter[0] && !prof_match(st.filter, name)) return ProfMark{};
+    // a captured launch does not run now, and its events could never be read
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone) {
+        (void)hipGetLastError();
+        return ProfMark{};
+    }
     std::lock_guard<std::mutex> g(st.mu);
     ProfMark m;
     if (st.pending.size() > 4096) drain(st, false);
