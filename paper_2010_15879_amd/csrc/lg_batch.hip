@@ -765,12 +765,24 @@ static lg_status batch_launch(lg_batch_plan *p, hipStream_t s) {
     LG_CHECK_LAUNCH();
     const auto *G = p->graphs.as<const BatchGraph<Acc>>();
     const auto *J = p->jobs.as<const BatchJob>();
-    return batch_kernel<Acc>(p, [&](auto bfs_batch_kernel) -> lg_status {
-        LG_LAUNCH(bfs_batch_kernel, p->workgroups, p->threads, (uint32_t)p->lds, s, G, J, p->num_jobs,
-                  p->counter.as<uint32_t>(), p->depth, p->parent, p->max_depth, p->queues.as<uint32_t>(), p->qcap,
-                  p->chunk, p->wave_threshold);
-        LG_CHECK_LAUNCH();
-        return LG_OK;
+    return batch_kernel<Acc>(p, [&](auto kernel) -> lg_status {
+        // (the launch's name in the profile is the variable's)
+        auto launch = [&](auto &&go) -> lg_status {
+            go(p->workgroups, p->threads, (uint32_t)p->lds, s, G, J, p->num_jobs, p->counter.as<uint32_t>(), p->depth,
+               p->parent, p->max_depth, p->queues.as<uint32_t>(), p->qcap, p->chunk, p->wave_threshold);
+            LG_CHECK_LAUNCH();
+            return LG_OK;
+        };
+        if (p->lds) {
+            const auto bfs_batch_kernel = kernel;
+            return launch([&](uint32_t grid, uint32_t block, uint32_t lds, hipStream_t st, auto... args) {
+                LG_LAUNCH(bfs_batch_kernel, grid, block, lds, st, args...);
+            });
+        }
+        const auto bfs_batch_large_kernel = kernel;
+        return launch([&](uint32_t grid, uint32_t block, uint32_t lds, hipStream_t st, auto... args) {
+            LG_LAUNCH(bfs_batch_large_kernel, grid, block, lds, st, args...);
+        });
     });
 }
 
