@@ -546,6 +546,22 @@ __global__ void dec_unkey_kernel(uint64_t total, const uint64_t *__restrict__ ke
         out[j] = (uint32_t)keys[j];
 }
 
+// How the lists of a sorted request on a relabeled graph are sorted, and the
+// temporaries of `total` IDs.
+enum class DecodeSort { kLists, kLong, kRadix };  // one by one; with bitmaps for the long ones; all pairs at once
+static DecodeSort decode_sort(const lg_graph *g) {
+    if (g->max_degree <= kSortMid) return DecodeSort::kLists;
+    const uint64_t ranges = ((uint64_t)g->n + (1u << kSortRangeBits) - 1) >> kSortRangeBits;
+    return ranges <= kSortMaxRanges ? DecodeSort::kLong : DecodeSort::kRadix;
+}
+DecodeSortBytes decode_sort_bytes(const lg_graph *g, uint64_t total) {
+    switch (decode_sort(g)) {
+        case DecodeSort::kLists: return {0, 0, 0, 0, 0};
+        case DecodeSort::kLong: return {total * 4, 0, 0, 0, 0};
+        default: return {total * 8, total * 8, total * 4, total * 4, radix_sort_tmp_bytes(total)};
+    }
+}
+
 DecodeWork::~DecodeWork() {
     if (host && host_owned) (void)hipHostFree(host);
 }
@@ -639,12 +655,14 @@ lg_status decode_run(lg_graph *g, DecodeWork &w, const uint32_t *vertices, uint3
             return LG_ERR_CAPACITY;
         }
         if (total == 0) return LG_OK;
-        const uint32_t ranges = (uint32_t)(((uint64_t)g->n + (1u << kSortRangeBits) - 1) >> kSortRangeBits);
-        const bool has_long = g->max_degree > kSortMid;
-        if (!sorted || !has_long || ranges <= kSortMaxRanges) {
+        const DecodeSortBytes tmp = sorted ? decode_sort_bytes(g, total) : DecodeSortBytes{};
+        if (!sorted || decode_sort(g) != DecodeSort::kRadix) {
+            const uint32_t ranges = (uint32_t)(((uint64_t)g->n + (1u << kSortRangeBits) - 1) >> kSortRangeBits);
+            const bool has_long = tmp.keys > 0;
             // the fixed scratch of the allocation-free entry point bounds what
             // it sorts, whichever sort that is
-            if (sorted && (has_long || w.keys.borrowed)) LG_TRY(w.keys.ensure(total * 8));
+            if (sorted && w.keys.borrowed) LG_TRY(w.keys.ensure(total * 8));
+            else if (has_long) LG_TRY(w.keys.ensure(tmp.keys));
             LG_TRY((dec_lists<Acc, false>(g, acc, labels, k, total, out_off, perm, out_ids, nullptr, deg, marks, stream)));
             if (!sorted) return LG_OK;
             LG_LAUNCH(dec_sort_wave_kernel, grid_for(k, kWave, 1u << 14), 256, 0, stream, k,
@@ -666,10 +684,10 @@ lg_status decode_run(lg_graph *g, DecodeWork &w, const uint32_t *vertices, uint3
             }
             return LG_OK;
         }
-        LG_TRY(w.keys.ensure(total * 8));
-        LG_TRY(w.keys2.ensure(total * 8));
-        LG_TRY(w.vals.ensure(total * 4));
-        LG_TRY(w.vals2.ensure(total * 4));
+        LG_TRY(w.keys.ensure(tmp.keys));
+        LG_TRY(w.keys2.ensure(tmp.keys2));
+        LG_TRY(w.vals.ensure(tmp.vals));
+        LG_TRY(w.vals2.ensure(tmp.vals2));
         LG_TRY((dec_lists<Acc, true>(g, acc, labels, k, total, out_off, perm, out_ids, w.keys.as<uint64_t>(), deg, marks,
                                       stream)));
         const uint32_t bits = 32 + bitlen_u64(k - 1);

@@ -381,6 +381,12 @@ lg_status bfs_run(lg_graph *g, BfsWork &w, const uint32_t *roots, uint32_t r, in
                   int32_t max_depth, uint32_t flags, hipStream_t stream, double alpha = kBfsAlphaLatency);
 // bytes of DecodeWork::head for k requests
 uint64_t decode_head_bytes(uint64_t k);
+// bytes of the other DecodeWork buffers that a sorted request of `total` IDs
+// on a relabeled graph takes
+struct DecodeSortBytes {
+    uint64_t keys, keys2, vals, vals2, sort_tmp;
+};
+DecodeSortBytes decode_sort_bytes(const lg_graph *g, uint64_t total);
 // lg_decode_neighbors on an explicit workspace
 lg_status decode_run(lg_graph *g, DecodeWork &w, const uint32_t *vertices, uint32_t k, uint64_t *out_off,
                      uint32_t *out_ids, uint64_t cap, uint32_t flags, hipStream_t stream, uint64_t *total);

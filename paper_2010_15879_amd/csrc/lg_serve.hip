@@ -227,12 +227,12 @@ void lg_server::plan(Worker &W, const lg_query &q, uint32_t batch, std::vector<R
         out.push_back({&W.ids, cap * 4});
         out.push_back({&W.dec.head, decode_head_bytes(k)});
         out.push_back({&W.dec.scan_tmp, scan_tmp_bytes(k)});
-        if (rel) {  // sorted output of a relabeled graph: keyed radix sort
-            out.push_back({&W.dec.keys, cap * 8});
-            out.push_back({&W.dec.keys2, cap * 8});
-            out.push_back({&W.dec.vals, cap * 4});
-            out.push_back({&W.dec.vals2, cap * 4});
-            out.push_back({&W.dec.sort_tmp, radix_sort_tmp_bytes(cap)});
+        if (rel) {  // sorted output of a relabeled graph
+            const DecodeSortBytes b = decode_sort_bytes(g, cap);
+            const Reserve sort[] = {{&W.dec.keys, b.keys}, {&W.dec.keys2, b.keys2}, {&W.dec.vals, b.vals},
+                                    {&W.dec.vals2, b.vals2}, {&W.dec.sort_tmp, b.sort_tmp}};
+            for (const Reserve &r : sort)
+                if (r.bytes) out.push_back(r);  // (an empty buffer would still be allocated)
         }
         return;
     }
