@@ -284,14 +284,16 @@ lg_status lg_encode_weighted(uint32_t n, uint64_t m, const uint64_t *row_offsets
  * Returns LG_ERR_UNSUPPORTED for an unweighted graph.  Synchronous: the
  * device drives the buckets, the host queues a few steps at a time and looks
  * whether they ended the search, and the call returns once dist is written.
- * The workspace is kept with the graph until lg_free; calls on the same graph from several threads run one after
- * the other (each holds the graph's workspace for its whole duration).
+ * The workspace is kept with the graph until lg_free; calls on the same graph
+ * from several threads run one after the other (each holds the graph's
+ * workspace for its whole duration).
  */
 lg_status lg_sssp(const lg_graph *g, uint32_t root, uint32_t delta, uint64_t *dist, hipStream_t stream);
 
 /*
- * lg_pagerank -- pull PageRank without atomics (section "Considered
- * Algorithms"), FP32 storage:
+ * lg_pagerank -- PageRank (section "Considered Algorithms"), FP32 storage: a
+ * pull without atomics on global memory, or propagation blocking, whose sums
+ * are exact in whatever order they are taken:
  *   PR_0 = 1/n;  PR_{t+1}(v) = (1-a)/n + a (sum_{u in N_v} PR_t(u)/d_u + D_t/n)
  * where D_t is the rank held by vertices without edges, spread uniformly.
  *
@@ -299,7 +301,8 @@ lg_status lg_sssp(const lg_graph *g, uint32_t root, uint32_t delta, uint64_t *di
  *   iters    number of iterations (exactly; no convergence test)
  *   scores   dev, float[n], indexed by original ID
  *
- * Calls of more than a few iterations build tables at a graph's first one,
+ * Calls of more than a few iterations (on large unrelabeled graphs, of any)
+ * build tables for propagation blocking at a graph's first one,
  * kept until lg_free: about 8.3 bytes per stored entry and 20 per vertex, and
  * during the build up to 8 more per entry (4 for lists that are not one stream
  * of fixed-width entries, up to 4 for counts).  Where they do not fit, this

@@ -218,7 +218,7 @@ __global__ __launch_bounds__(kThreads) void bfs_batch_large_kernel(
 
 // A graph's three bitmaps (visited, frontier, next) in LDS, at most: one
 // workgroup per compute unit, which is still 14 times faster at 2^18 vertices
-// (96 KB).  Above it (349,525 vertices) the large kernel.
+// (96 KB).  Above it (349,504 vertices) the large kernel.
 constexpr uint64_t kBatchLdsBytes = 128u << 10;
 inline uint64_t batch_bitmap_bytes(uint64_t n) { return (n + 63) / 64 * 8 * 3; }
 

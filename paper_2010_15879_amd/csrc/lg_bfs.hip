@@ -441,36 +441,31 @@ __global__ __launch_bounds__(kTdBinThreads) void td_bin_kernel(
             const uint32_t last = (uint32_t)__builtin_amdgcn_readlane((int)sc, kWave - 1);
             carry = last > carry ? last : carry;
         }
-        // the edges, all of a thread's list and bitmap loads in flight together
-        // (slots past the end read the tile's last row, and the list's start)
-        constexpr uint32_t kIn = kTdBinSteps;
-        uint32_t v[kTdBinSteps], rank[kTdBinSteps];
+        // the edges, all of a thread's list loads in flight together (slots past
+        // the end read the tile's last row, and the list's start)
+        uint64_t pos[kTdBinSteps];
+        uint32_t w[kTdBinSteps], v[kTdBinSteps], rank[kTdBinSteps];
 #pragma unroll
-        for (uint32_t q0 = 0; q0 < kTdBinSteps; q0 += kIn) {
-            uint64_t pos[kIn];
-            uint32_t w[kIn];
-#pragma unroll
-            for (uint32_t k = 0; k < kIn; ++k) {
-                const uint32_t x = x0 + (q0 + k) * kWave, r = row[q0 + k];
-                uint64_t base;
-                if (r < kTdBinRows) {
-                    base = s_base[r];
-                    w[k] = (uint32_t)(base >> 56);
-                    if constexpr (kParent) row[q0 + k] = s_id[r];
-                } else {
-                    w[k] = fw[i0 + r];
-                    base = fstart[i0 + r] - fscan[i0 + r] * Acc::step(w[k]);
-                    if constexpr (kParent) row[q0 + k] = queue[i0 + r];
-                }
-                pos[k] = x < len ? (base + (e0 + x) * Acc::step(w[k])) & kPlace : 0ull;
+        for (uint32_t q = 0; q < kTdBinSteps; ++q) {
+            const uint32_t x = x0 + q * kWave, r = row[q];
+            uint64_t base;
+            if (r < kTdBinRows) {
+                base = s_base[r];
+                w[q] = (uint32_t)(base >> 56);
+                if constexpr (kParent) row[q] = s_id[r];
+            } else {
+                w[q] = fw[i0 + r];
+                base = fstart[i0 + r] - fscan[i0 + r] * Acc::step(w[q]);
+                if constexpr (kParent) row[q] = queue[i0 + r];
             }
+            pos[q] = x < len ? (base + (e0 + x) * Acc::step(w[q])) & kPlace : 0ull;
+        }
 #pragma unroll
-            for (uint32_t k = 0; k < kIn; ++k) v[q0 + k] = acc.get(pos[k], Acc::mask(w[k]));
+        for (uint32_t q = 0; q < kTdBinSteps; ++q) v[q] = acc.get(pos[q], Acc::mask(w[q]));
 #pragma unroll
-            for (uint32_t k = 0; k < kIn; ++k) {
-                if (x0 + (q0 + k) * kWave >= len) v[q0 + k] = 0xFFFFFFFFu;
-                rank[q0 + k] = v[q0 + k] != 0xFFFFFFFFu ? atomicAdd(&s_bin[v[q0 + k] >> shift], 1u) : 0u;
-            }
+        for (uint32_t q = 0; q < kTdBinSteps; ++q) {
+            if (x0 + q * kWave >= len) v[q] = 0xFFFFFFFFu;
+            rank[q] = v[q] != 0xFFFFFFFFu ? atomicAdd(&s_bin[v[q] >> shift], 1u) : 0u;
         }
         __syncthreads();
         // counts -> starts, and each bin's room
@@ -813,8 +808,8 @@ __global__ void bu_pending_kernel(Acc acc, uint32_t threshold, uint64_t np, cons
 // it has threads, one per lane, and reserves their entries with one atomic:
 // all reservations meet in one counter, some 18 ns each, which was this
 // kernel's time when every wave made its own (uniform graph, 2^24 vertices,
-// 4,096 reservations: 77 us a launch; 256 of them: 33).  A wave writes its 64 words' entries in order,
-// 64 consecutive queue slots per step: slot j's word is the one whose
+// 4,096 reservations: 77 us a launch; 256 of them: 33).  A wave writes its 64
+// words' entries in order, 64 consecutive queue slots per step: slot j's word is the one whose
 // prefix count range holds j (a binary search of the wave's inclusive
 // counts), its bit the (j - count before)-th one of that word.  One lane
 // writing its word's ones one after another scattered every store.
@@ -2333,7 +2328,8 @@ template <class Acc, bool kParent, bool kTD, class Out>
 __global__ __launch_bounds__(kMsThreads, MsWavesPerEU<Acc>::value) void ms_resolve_kernel(
     Acc acc, uint32_t n, int32_t next_depth, unsigned long long active, const unsigned long long *__restrict__ fr,
     unsigned long long *__restrict__ vis, unsigned long long *__restrict__ nx, Out out,
-    uint64_t *__restrict__ bits, uint32_t *__restrict__ pend_v, unsigned long long *__restrict__ pend_m, unsigned long long *__restrict__ ctr) {
+    uint64_t *__restrict__ bits, uint32_t *__restrict__ pend_v, unsigned long long *__restrict__ pend_m,
+    unsigned long long *__restrict__ ctr) {
     __shared__ uint8_t s_par[kParent ? kMsThreads * kMsParStride : 4];
     __shared__ unsigned long long s_act[kMsThreads / kWave];
     uint8_t *par = &s_par[kParent ? threadIdx.x * kMsParStride : 0];
@@ -2441,23 +2437,23 @@ __global__ __launch_bounds__(kMsThreads, MsWavesPerEU<Acc>::value) void ms_resol
             // any bit is found, and drop it)
             for (unsigned long long bb = wave_or64(found); bb;) {
                 uint32_t rr[4];
-    #pragma unroll
+#pragma unroll
                 for (int k = 0; k < 4; ++k) {
                     rr[k] = bb ? (uint32_t)__ffsll((long long)bb) - 1 : kMsRoots;
                     bb &= bb - 1;
                 }
                 bool has[4];
-    #pragma unroll
+#pragma unroll
                 for (int k = 0; k < 4; ++k) has[k] = rr[k] < kMsRoots && ((found >> rr[k]) & 1ull);
                 uint32_t pu[4];
                 if constexpr (kParent && !kTD) {
-    #pragma unroll
+#pragma unroll
                     for (int k = 0; k < 4; ++k) {
                         const uint64_t pos = has[k] ? vi.start + (uint64_t)par[rr[k]] * st : 0ull;
                         pu[k] = acc.get(pos, mk);
                     }
                 }
-    #pragma unroll
+#pragma unroll
                 for (int k = 0; k < 4; ++k) {
                     if (has[k]) {
                         out.depth[out.at(rr[k], v)] = next_depth;

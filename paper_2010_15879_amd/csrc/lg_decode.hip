@@ -369,8 +369,10 @@ __global__ __launch_bounds__(256) void dec_walk_kernel(Acc acc, const uint32_t *
 constexpr uint32_t kSortWave = 1024;
 constexpr uint32_t kSortMid = 8192;
 constexpr uint32_t kSortRangeBits = 20;  // a range's bitmap: 128 KB
-// every range of a long list reads the whole list: with more ranges than
-// this the radix sort moves less
+// every range of a long list reads the whole list, a workgroup each: up to
+// here it is far ahead of the radix sort (one list of 2^23 IDs in 16 ranges 4.3
+// ms, by the radix sort 101; 2^20 IDs in 2 ranges 1.5 against 8); beyond it the
+// radix sort stays, unmeasured
 constexpr uint32_t kSortMaxRanges = 16;
 
 // Bitonic sort of up to 64 kR values in a wave: element e of lane e mod 64,

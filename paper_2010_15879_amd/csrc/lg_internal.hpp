@@ -136,11 +136,11 @@ struct MsWork {
     DevBuf bits;                 // u64[words]: vertices of the next frontier
     DevBuf pend_v, pend_m;       // u32[n], u64[n]: vertices left for the wave pass, their open bits
     DevBuf roots;                // u32[64]: the batch's roots
-    // relabeled graphs: the batch's results in label space, 64 roots a vertex
+    // relabeled graphs: the batch's results in label space, 16, 32 or 64 roots a vertex
     DevBuf cell_depth, cell_wide, cell_parent;  // u8, i32 (searches deeper than a byte), i32
     uint64_t bytes() const {
-        return vis.bytes + fr.bytes + nx.bytes + bits.bytes + pend_v.bytes + pend_m.bytes + roots.bytes + cell_depth.bytes +
-               cell_wide.bytes + cell_parent.bytes;
+        return vis.bytes + fr.bytes + nx.bytes + bits.bytes + pend_v.bytes + pend_m.bytes + roots.bytes +
+               cell_depth.bytes + cell_wide.bytes + cell_parent.bytes;
     }
 };
 struct BfsPool {
@@ -361,7 +361,6 @@ constexpr double kBfsAlphaShared = 15.0;
 constexpr double kBfsAlphaLate = 15.0;
 constexpr double kBfsProbeCost = 1.0 / 6.0;
 
-// BFS from host roots on an explicit workspace (lg_bfs without argument checks)
 // Calls of up to 15 roots (from 16 a batch shares the traversal) on a small
 // graph run in one launch, a workgroup per root (lg_batch.hip).  A workgroup's
 // time grows with the entries, the other paths' hardly does: one root up to
@@ -377,6 +376,7 @@ lg_status bfs_small(lg_graph *g, const uint32_t *roots, uint32_t r, int32_t *dep
 // `rows` searches' results in label space to rows by original ID
 lg_status bfs_unpermute(lg_graph *g, const int32_t *depth_i, const uint32_t *parent_i, uint32_t rows, int32_t *depth,
                         int32_t *parent, hipStream_t stream);
+// BFS from host roots on an explicit workspace (lg_bfs without argument checks)
 lg_status bfs_run(lg_graph *g, BfsWork &w, const uint32_t *roots, uint32_t r, int32_t *depth, int32_t *parent,
                   int32_t max_depth, uint32_t flags, hipStream_t stream, double alpha = kBfsAlphaLatency);
 // bytes of DecodeWork::head for k requests

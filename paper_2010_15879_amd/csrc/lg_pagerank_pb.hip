@@ -8,8 +8,9 @@
 // neighbour v computes the same sums.  Here every entry's place on the way is
 // fixed once per graph, so that an iteration moves nothing but contributions:
 //
-//   The vertices are cut into source blocks of 2^15 (their contributions fit
-//   LDS) and destination bins of 2^11 to 2^14 (their 64-bit sums fit LDS).
+//   The vertices are cut into source blocks of 2^13 to 2^15 (their
+//   contributions fit LDS) and destination bins of 2^8 to 2^14 (their 64-bit
+//   sums fit LDS).
 //   The entries of (source block, bin) are one tile, in an order fixed by the
 //   build, padded to a multiple of four entries (a quad).  Three arrays:
 //     src   u16 an entry: the source within its block, block by block
@@ -36,8 +37,8 @@
 
 namespace lg {
 
-constexpr uint32_t kMinSrcShift = 13, kMaxSrcShift = 15;   // source block: at most 128 KB of contributions
-constexpr uint32_t kMinFineShift = 8, kMaxFineShift = 14;  // bin: at most 128 KB of sums
+constexpr uint32_t kMaxSrcShift = 15;   // source block: at most 128 KB of contributions
+constexpr uint32_t kMaxFineShift = 14;  // bin: at most 128 KB of sums
 constexpr double kFixScale = 1152921504606846976.0;  // 2^60
 constexpr double kFixUnit = 1.0 / 1152921504606846976.0;
 constexpr double kFixMinBase = 1.0 / 34359738368.0;  // 2^-35
@@ -742,7 +743,7 @@ static lg_status pb_build_tiles(lg_graph *g, PbEntries<kPacked> ent, const uint6
     // 27.1; 2^25 (15, 14) 50.9, (15, 13) 54.4
     const uint32_t logn = bitlen_u64((uint64_t)n - 1);
     W.ss = logn < 20 ? 13 : (logn < 25 ? 14 : kMaxSrcShift);
-    W.fs = logn <= 16 ? kMinFineShift : (logn <= 20 ? 9 : (logn < 25 ? std::min(13u, logn - 10) : kMaxFineShift));
+    W.fs = logn <= 16 ? 8 : (logn <= 20 ? 9 : (logn < 25 ? std::min(13u, logn - 10) : kMaxFineShift));
     W.ns = (uint32_t)(((uint64_t)n + (1u << W.ss) - 1) >> W.ss);
     W.nf = (uint32_t)(((uint64_t)n + (1u << W.fs) - 1) >> W.fs);
     const uint32_t ns = W.ns, nf = W.nf;
@@ -775,8 +776,9 @@ static lg_status pb_build_tiles(lg_graph *g, PbEntries<kPacked> ent, const uint6
         LG_CHECK_LAUNCH();
     }
     const uint32_t cgrid = grid_for(cells, 256, 1u << 15);
-    LG_LAUNCH(pb_tiles_kernel, ns * ((nf + kWave - 1) / kWave), kTileWaves * kWave, 0, s, ns, nf, (const uint64_t *)part_off.p, pcnt.as<uint32_t>(),
-              cnt.as<uint32_t>(), tq.as<uint32_t>(), tqb.as<uint32_t>());
+    LG_LAUNCH(pb_tiles_kernel, ns * ((nf + kWave - 1) / kWave), kTileWaves * kWave, 0, s, ns, nf,
+              (const uint64_t *)part_off.p, pcnt.as<uint32_t>(), cnt.as<uint32_t>(), tq.as<uint32_t>(),
+              tqb.as<uint32_t>());
     LG_CHECK_LAUNCH();
     LG_TRY(exclusive_scan_u32(tq.as<uint32_t>(), sq.as<uint64_t>(), cells, tmp, s));
     LG_TRY(exclusive_scan_u32(tqb.as<uint32_t>(), dq.as<uint64_t>(), cells, tmp, s));
@@ -899,12 +901,12 @@ static lg_status pb_build(lg_graph *g, hipStream_t s) {
     return pb_build_tiles(g, PbEntries<false>{col.as<uint32_t>(), 32u}, eoff.as<uint64_t>(), s);
 }
 
-// fn(std::integral_constant<uint32_t, shift>) for lo <= shift <= hi
-template <uint32_t lo, uint32_t hi, class Fn>
+// fn(std::integral_constant<uint32_t, shift>) for the shifts that a build picks
+template <uint32_t... kShifts, class Fn>
 static lg_status pb_by_shift(uint32_t shift, Fn &&fn) {
-    if constexpr (lo < hi)
-        if (shift > lo) return pb_by_shift<lo + 1, hi>(shift, fn);
-    return fn(std::integral_constant<uint32_t, lo>{});
+    lg_status st = LG_ERR_UNSUPPORTED;
+    (void)((shift == kShifts && (st = fn(std::integral_constant<uint32_t, kShifts>{}), true)) || ...);
+    return st;
 }
 
 lg_status pagerank_pb(lg_graph *g, float damping, uint32_t iters, float *scores, hipStream_t s) {
@@ -951,14 +953,14 @@ lg_status pagerank_pb(lg_graph *g, float damping, uint32_t iters, float *scores,
         float *sc = last ? scores : (float *)nullptr;
         const uint32_t *pm = last ? perm : (const uint32_t *)nullptr;
         if (W.n_send) {
-            LG_TRY((pb_by_shift<kMinSrcShift, kMaxSrcShift>(W.ss, [&](auto shift) -> lg_status {
+            LG_TRY((pb_by_shift<13, 14, 15>(W.ss, [&](auto shift) -> lg_status {
                 constexpr uint32_t S = decltype(shift)::value, T = S >= 15 ? 1024 : 512;
                 LG_LAUNCH((pb_send_kernel<S, T>), W.n_send, T, 0, s, n, send, (const float *)cin, src, val);
                 LG_CHECK_LAUNCH();
                 return LG_OK;
             })));
         }
-        LG_TRY((pb_by_shift<kMinFineShift, kMaxFineShift>(W.fs, [&](auto shift) -> lg_status {
+        LG_TRY((pb_by_shift<8, 9, 11, 12, 13, 14>(W.fs, [&](auto shift) -> lg_status {
             constexpr uint32_t S = decltype(shift)::value, T = S >= 14 ? 1024 : (S >= 12 ? 512 : 256);
             LG_LAUNCH((pb_sum_kernel<S, T>), W.n_sum, T, 0, s, n, W.ns, sum, run_dst, run_src, dst, (const float *)val,
                       (float)b, (float)a, deg, cout, sc, pm, gsum);

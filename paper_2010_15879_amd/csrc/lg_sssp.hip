@@ -198,8 +198,8 @@ constexpr uint64_t kCollectTile = 64;  // words of a tile, at most
 
 __global__ __launch_bounds__(kCollectThreads) void sssp_count_kernel(
     uint32_t n, uint64_t words, uint32_t tile, const SsspState *__restrict__ state,
-    const uint32_t *__restrict__ vdeg, const uint64_t *__restrict__ dist, uint64_t *__restrict__ upd, uint64_t *__restrict__ tmask,
-    uint64_t *__restrict__ wdeg, SsspPart *__restrict__ parts) {
+    const uint32_t *__restrict__ vdeg, const uint64_t *__restrict__ dist, uint64_t *__restrict__ upd,
+    uint64_t *__restrict__ tmask, uint64_t *__restrict__ wdeg, SsspPart *__restrict__ parts) {
     if (state->done) return;
     __shared__ unsigned long long s_left[kCollectWaves], s_edges[kCollectWaves], s_count[kCollectWaves];
     const uint64_t hi = state->hi;
@@ -297,8 +297,8 @@ __device__ __forceinline__ uint64_t collect_scan(uint64_t x, uint64_t *s_wave, u
 }
 
 __global__ __launch_bounds__(kCollectThreads) void sssp_write_kernel(
-    const uint64_t *__restrict__ vstart, const uint32_t *__restrict__ vdeg, uint64_t words, uint32_t tile, uint64_t delta, uint64_t max_steps, const uint64_t *__restrict__ dist,
-    const uint64_t *__restrict__ tmask, const uint64_t *__restrict__ wdeg, const SsspPart *__restrict__ parts,
+    const uint64_t *__restrict__ vstart, const uint32_t *__restrict__ vdeg, uint64_t words, uint32_t tile,
+    uint64_t delta, uint64_t max_steps, const uint64_t *__restrict__ dist, const uint64_t *__restrict__ tmask, const uint64_t *__restrict__ wdeg, const SsspPart *__restrict__ parts,
     uint32_t *__restrict__ qv, uint64_t *__restrict__ qstart, uint64_t *__restrict__ qdist,
     uint64_t *__restrict__ qoff, SsspState *__restrict__ state) {
     __shared__ uint64_t s_wave[kCollectWaves];
@@ -535,8 +535,8 @@ static lg_status lg_sssp_impl(const lg_graph *gc, uint32_t root, uint32_t delta,
         while (!now.done) {
             for (int i = 0; i < kAhead; ++i) {
                 LG_LAUNCH(sssp_count_kernel, collect_grid, kCollectThreads, 0, stream, n, words, tile,
-                          (const SsspState *)state, (const uint32_t *)W.vdeg.as<uint32_t>(), (const uint64_t *)dist, W.upd.as<uint64_t>(),
-                          W.tmask.as<uint64_t>(), W.wdeg.as<uint64_t>(), W.parts.as<SsspPart>());
+                          (const SsspState *)state, (const uint32_t *)W.vdeg.as<uint32_t>(), (const uint64_t *)dist,
+                          W.upd.as<uint64_t>(), W.tmask.as<uint64_t>(), W.wdeg.as<uint64_t>(), W.parts.as<SsspPart>());
                 LG_CHECK_LAUNCH();
                 LG_LAUNCH(sssp_write_kernel, collect_grid, kCollectThreads, 0, stream,
                           (const uint64_t *)W.vstart.as<uint64_t>(), (const uint32_t *)W.vdeg.as<uint32_t>(), words,
@@ -547,8 +547,8 @@ static lg_status lg_sssp_impl(const lg_graph *gc, uint32_t root, uint32_t delta,
                 LG_CHECK_LAUNCH();
                 LG_LAUNCH(sssp_relax_kernel<Acc>, relax_grid, 256, 0, stream, acc, n, (const SsspState *)state,
                           (const uint64_t *)W.qoff.as<uint64_t>(), (const uint32_t *)W.qv.as<uint32_t>(),
-                          (const uint64_t *)W.qstart.as<uint64_t>(), (const uint64_t *)W.qdist.as<uint64_t>(), (unsigned long long *)dist,
-                          W.upd.as<unsigned long long>());
+                          (const uint64_t *)W.qstart.as<uint64_t>(), (const uint64_t *)W.qdist.as<uint64_t>(),
+                          (unsigned long long *)dist, W.upd.as<unsigned long long>());
                 LG_CHECK_LAUNCH();
             }
             LG_CHECK_HIP(hipMemcpyAsync(W.host, state, sizeof(SsspState), hipMemcpyDeviceToHost, stream));
