@@ -164,51 +164,38 @@ bool pb_applies(const lg_graph *g, float damping, uint32_t iters) {
     // it (relabeled star of 12 M vertices, damping 1, one iteration: mean
     // error 791 units of 2^-24, by the pull 0.3).
     if (1.0 - (double)damping < (double)g->n * kFixMinBase) return false;
+    if (!g->m) return false;
     // The iterations from which a graph's first call, build included, is no
-    // slower than the pull's: a + b n / m, for uniform graphs (the shorter the
-    // lists the more), or `skewed` where the pull waits for its hubs: an eighth
-    // of the entries or more in lists above the heavy threshold.  From where
-    // the two meet on 12 families of lists, 2^10 to 2^23 vertices, 1 to 24
-    // edges a vertex, uniform and Kronecker.  Uniform, at a mean of 2, 4, 8, 16
-    // and 32 entries, at most (vertices below 2^17; below 2^20; from 2^20):
-    //   one stream  25 17  9  5  2 | 13 10  9  6  4 |  6  5  4  3  2
-    //   local       29 22 12  7  4 | 15 13 12  8  6 |  7  6  5  3  3
-    //   gap         38 27 15  9  5 | 24 19 16 11  7 | 19 14 10  6  4
-    // (gap: the pull reads short lists fast, the build decodes them first).
-    // Kronecker: 1, 5 and 12 | 4, 4 and 10 | 5, 7 and 13.
-    struct Line {
-        uint32_t a, b, skewed;
-    };
-    static constexpr Line kStream[] = {{1, 64, 1}, {5, 34, 5}, {5, 2, 5}};
-    // (below 2^17 vertices this and the next pass 20 iterations at the same
-    // mean, so that the two, whose pulls are alike bit for bit, stay so there)
-    static constexpr Line kLocal[] = {{3, 102, 6}, {6, 52, 5}, {4, 8, 7}};
-    static constexpr Line kGap[] = {{4, 96, 12}, {8, 64, 10}, {5, 40, 13}};
+    // slower than the pull's.  12 families of lists, 2^10 to 2^23 vertices, 1
+    // to 24 edges a vertex, uniform and Kronecker, gave where the two meet.
+    // Uniform graphs: the more the shorter the lists, at a mean of 2, 4, 8, 16
+    // and 32 entries at most 25, 17, 9, 6 and 4 iterations (one stream of
+    // entries), 38, 26, 16, 11 and 7 (gap: the pull reads short lists fast,
+    // the build decodes them first; local up to 29, 22, 12, 8 and 6, under the
+    // same line, so that the two sum alike).  Skewed graphs, an eighth of the
+    // entries or more in lists above the heavy threshold, whose pull waits for
+    // its hubs: at most 5, 12.5 and 7 iterations; one stream of up to 2^16
+    // vertices wins from the first.
     const uint64_t n = g->n, m = g->m;
-    if (!m) return false;
-    const uint32_t size = n < 1u << 17 ? 0 : (n < 1u << 20 ? 1 : 2);
     const bool hub = (uint64_t)g->max_degree * 16 >= m, dense = m >= 64 * n;
     const bool skewed = hub || dense || (uint64_t)g->n_heavy * g->heavy_threshold * 8 >= m;
-    auto from = [&](const Line &l) {
-        return skewed ? iters >= l.skewed : (double)iters >= l.a + (double)l.b * (double)n / (double)m;
-    };
-    // (hubs and long lists are also summed more exactly)
-    if (plain || g->id_mode == LG_IDS_GLOBAL) return hub || dense || from(kStream[size]);
+    if (plain || g->id_mode == LG_IDS_GLOBAL) {
+        // (hubs and long lists are also summed more exactly)
+        const uint32_t least = hub || dense || (skewed && n <= 1u << 16) ? 1 : 6;
+        return iters >= least && (skewed || iters * m >= 80 * n);
+    }
     // A long list read in order that holds a sixteenth of the entries is the
     // build's whole time (gap star, 2^17 vertices, 12 iterations: 0.53 ms by
     // the pull, 1.1 with the build; 2^20.5: 1.3 and 8.8).  (Local widths, which
     // it would not hold up, follow the same line.)
     if (hub && g->max_degree > 1u << 14) return false;
-    if (g->id_mode == LG_IDS_LOCAL) return from(kLocal[size]);
-    if (g->id_mode == LG_IDS_LOCAL_GAP) return from(kGap[size]);
-    // Varint lists of a few bytes a lane reads faster than an entry's 12 bytes
-    // stream: uniform graphs below 2^20 vertices or 16 entries a list meet at
-    // 20 to hundreds, or never; the others at 14, 7 and 6 (means of 16, 32 and
-    // 48).  Kronecker: 8 to 17, from 2^13 vertices 3 to 10, from 2^20 4 to 16,
-    // above 2^22 10 to 14 (means from 16) or up to 25.
-    if (!skewed) return size == 2 && m >= 16 * n && (double)iters >= 4 + 160.0 * (double)n / (double)m;
-    if (n >= 1u << 13 && size < 2) return iters >= 10;
-    return iters >= 16 && (n <= 1u << 22 || m >= 16 * n);
+    if (g->id_mode == LG_IDS_LOCAL || g->id_mode == LG_IDS_LOCAL_GAP)
+        return iters >= 12 && (skewed || iters * m >= 140 * n);
+    // Varint lists: between 2^13 and 2^22 vertices skewed graphs meet at 3 to
+    // 17 iterations; uniform ones from 2^20 vertices and 16 entries a list at
+    // 2 to 15, others at 20 to hundreds or never (their lists are a few bytes,
+    // which a lane reads faster than an entry's 12 bytes stream)
+    return iters >= 16 && ((skewed && n >= 1u << 13 && n <= 1u << 22) || (n >= 1u << 20 && m >= 16 * n));
 }
 
 // ---------------------------------------------------------------------------

@@ -32,16 +32,15 @@ GRAPHS = {
 }
 # graph, encoding, the fewest iterations that build (None: none do)
 LINES = [
-    ("uniform4", dict(), 10), ("uniform4", dict(layout="plain", relabel=True), 10),
-    ("uniform4", dict(ids="local", offsets="ef"), 13), ("uniform4", dict(ids="local-gap"), 17),
+    ("uniform4", dict(), 11), ("uniform4", dict(layout="plain", relabel=True), 11),
+    ("uniform4", dict(ids="local", offsets="ef"), 18), ("uniform4", dict(ids="local-gap"), 18),
     ("uniform4", dict(ids="varint-diff"), None),
-    ("uniform16", dict(relabel="greedy"), 4), ("uniform16", dict(ids="local", relabel=True), 7),
-    ("uniform16", dict(ids="local-gap", offsets="ef"), 8), ("uniform16", dict(ids="varint-full"), None),
-    ("kron14", dict(), 1), ("kron14", dict(ids="varint-diff", relabel=True), 10),
-    ("kron14", dict(ids="local"), 6), ("kron14", dict(ids="local-gap"), 12),
-    ("kron17", dict(relabel=True), 5), ("kron17", dict(ids="local-gap"), 10),
-    ("star", dict(layout="plain"), 1), ("star", dict(ids="local", offsets="ef"), 6),
-    ("star", dict(ids="varint-full"), 10),
+    ("uniform16", dict(relabel="greedy"), 6), ("uniform16", dict(ids="local", relabel=True), 12),
+    ("uniform16", dict(ids="local-gap", offsets="ef"), 12), ("uniform16", dict(ids="varint-full"), None),
+    ("kron14", dict(), 1), ("kron14", dict(ids="varint-diff", relabel=True), 16),
+    ("kron17", dict(relabel=True), 6), ("kron17", dict(ids="local-gap"), 12),
+    ("star", dict(layout="plain"), 1), ("star", dict(ids="local", offsets="ef"), 12),
+    ("star", dict(ids="varint-full"), 16),
     ("star17", dict(ids="local", offsets="ef"), None), ("star17", dict(ids="local-gap", relabel=True), None),
 ]
 
