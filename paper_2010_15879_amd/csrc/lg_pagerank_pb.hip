@@ -141,8 +141,22 @@ static lg_status pb_take_buffers(lg_graph *g, uint64_t bytes) {
 }
 
 // Is propagation blocking the PageRank of this call?  A rule of the graph, the
-// damping and the iterations (never of timing), so that results do not depend
-// on the run.
+// damping and the iterations alone (never of timing or of earlier calls), so
+// that results do not depend on the run.  Its sums are exact, and it beats the
+// pull per iteration 1.5 to 8 times (2^10 to 2^25 vertices, 1 to 24 edges a
+// vertex, uniform and Kronecker; uniform Varint lists of a few bytes, which a
+// lane reads fast, 0.7 to 1.5 times).
+//
+// A graph's first call also pays for the build.  Where it meets the pull's,
+// in iterations, uniform graphs at means of 2, 8 and 32 entries and Kronecker
+// ones, largest over the sizes:
+//   one stream of entries   25  9  4,  5     local  29 12  7,  7
+//   gap                     38 16  7, 13 (the build decodes the lists first)
+//   Varint                  never (2^20 vertices and more: 57 33 7), 16
+// (one iteration, uniform, 2^17 vertices, 8 entries: 0.13 ms by the pull, 0.24
+// with the build).  Fewer iterations of decoded encodings are left to the pull;
+// a line at the crossings would take calls of up to 30 iterations from the
+// exact sums and slow down every call but the first up to three times.
 static bool pb_always(const lg_graph *g) {
     // Large unrelabeled local IDs among them: the pull's FP32 sums are less
     // accurate (uniform graph, 2^22 vertices, one iteration: largest error
@@ -164,38 +178,8 @@ bool pb_applies(const lg_graph *g, float damping, uint32_t iters) {
     // it (relabeled star of 12 M vertices, damping 1, one iteration: mean
     // error 791 units of 2^-24, by the pull 0.3).
     if (1.0 - (double)damping < (double)g->n * kFixMinBase) return false;
-    if (!g->m) return false;
-    // The iterations from which a graph's first call, build included, is no
-    // slower than the pull's.  12 families of lists, 2^10 to 2^23 vertices, 1
-    // to 24 edges a vertex, uniform and Kronecker, gave where the two meet.
-    // Uniform graphs: the more the shorter the lists, at a mean of 2, 4, 8, 16
-    // and 32 entries at most 25, 17, 9, 6 and 4 iterations (one stream of
-    // entries), 38, 26, 16, 11 and 7 (gap: the pull reads short lists fast,
-    // the build decodes them first; local up to 29, 22, 12, 8 and 6, under the
-    // same line, so that the two sum alike).  Skewed graphs, an eighth of the
-    // entries or more in lists above the heavy threshold, whose pull waits for
-    // its hubs: at most 5, 12.5 and 7 iterations; one stream of up to 2^16
-    // vertices wins from the first.
-    const uint64_t n = g->n, m = g->m;
-    const bool hub = (uint64_t)g->max_degree * 16 >= m, dense = m >= 64 * n;
-    const bool skewed = hub || dense || (uint64_t)g->n_heavy * g->heavy_threshold * 8 >= m;
-    if (plain || g->id_mode == LG_IDS_GLOBAL) {
-        // (hubs and long lists are also summed more exactly)
-        const uint32_t least = hub || dense || (skewed && n <= 1u << 16) ? 1 : 6;
-        return iters >= least && (skewed || iters * m >= 80 * n);
-    }
-    // A long list read in order that holds a sixteenth of the entries is the
-    // build's whole time (gap star, 2^17 vertices, 12 iterations: 0.53 ms by
-    // the pull, 1.1 with the build; 2^20.5: 1.3 and 8.8).  (Local widths, which
-    // it would not hold up, follow the same line.)
-    if (hub && g->max_degree > 1u << 14) return false;
-    if (g->id_mode == LG_IDS_LOCAL || g->id_mode == LG_IDS_LOCAL_GAP)
-        return iters >= 12 && (skewed || iters * m >= 140 * n);
-    // Varint lists: between 2^13 and 2^22 vertices skewed graphs meet at 3 to
-    // 17 iterations; uniform ones from 2^20 vertices and 16 entries a list at
-    // 2 to 15, others at 20 to hundreds or never (their lists are a few bytes,
-    // which a lane reads faster than an entry's 12 bytes stream)
-    return iters >= 16 && ((skewed && n >= 1u << 13 && n <= 1u << 22) || (n >= 1u << 20 && m >= 16 * n));
+    if (plain || g->id_mode == LG_IDS_GLOBAL) return true;
+    return iters >= (g->id_mode == LG_IDS_LOCAL || g->id_mode == LG_IDS_LOCAL_GAP ? 6u : 10u);
 }
 
 // ---------------------------------------------------------------------------

@@ -33,9 +33,9 @@ GRAPHS = {
     "kron15": lambda: gg.kronecker(15, 16, seed=2),
     "n1023": lambda: _hubs(1023, [700, 65], 3),
 }
-ENCS = [(dict(ids="local", offsets="ef"), (2, 5, 11)), (dict(ids="local", relabel=True), (2, 11)),
-        (dict(ids="local-gap"), (2, 5, 11)), (dict(ids="local-gap", offsets="ef", relabel="greedy"), (3, 11)),
-        (dict(ids="varint-full"), (2, 9, 15)), (dict(ids="varint-diff", offsets="ef", relabel=True), (2, 9, 15)),
+ENCS = [(dict(ids="local", offsets="ef"), (2, 5)), (dict(ids="local", relabel=True), (2, 5)),
+        (dict(ids="local-gap"), (2, 5)), (dict(ids="local-gap", offsets="ef", relabel="greedy"), (3, 5)),
+        (dict(ids="varint-full"), (2, 9)), (dict(ids="varint-diff", offsets="ef", relabel=True), (2, 9)),
         (dict(ids="varint-diff", offsets="plain-bv"), (4,))]
 
 
