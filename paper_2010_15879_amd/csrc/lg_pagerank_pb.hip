@@ -173,11 +173,14 @@ bool pb_applies(const lg_graph *g, float damping, uint32_t iters) {
     const bool plain = g->layout == LG_LAYOUT_PLAIN;
     if (!plain && (g->weighted || g->offset_mode == LG_OFFS_INTERLEAVED_BV)) return false;
     if (pb_always(g)) return true;
-    // A score is at least the base term (1 - damping) / n.  Below 2^-35 the
-    // fixed-point unit, 2^-60, is no longer small beside an FP32 rounding of
-    // it (relabeled star of 12 M vertices, damping 1, one iteration: mean
-    // error 791 units of 2^-24, by the pull 0.3).
-    if (1.0 - (double)damping < (double)g->n * kFixMinBase) return false;
+    // A score is at least the base term (1 - damping) / n, or, where that
+    // vanishes, about a first rank's share of the largest list, 1 / (n d).
+    // With both below 2^-35 the fixed-point unit, 2^-60, is no longer small
+    // beside an FP32 rounding of it (relabeled star of 12 M vertices, damping
+    // 1, one iteration: mean error 791 units of 2^-24, by the pull 0.3).
+    if (1.0 - (double)damping < (double)g->n * kFixMinBase &&
+        (double)g->n * (double)g->max_degree * kFixMinBase > 1.0)
+        return false;
     if (plain || g->id_mode == LG_IDS_GLOBAL) return true;
     return iters >= (g->id_mode == LG_IDS_LOCAL || g->id_mode == LG_IDS_LOCAL_GAP ? 6u : 10u);
 }

@@ -31,11 +31,14 @@ def test_leaves_of_a_star(enc):
     h.free()
 
 
-@pytest.mark.parametrize("damping,kept", [(0.85, True), (1.0, False)])
-def test_entry_buffers(damping, kept):
+@pytest.mark.parametrize("n,damping,kept", [(1 << 14, 0.85, True), (1 << 14, 1.0, True), (1 << 19, 0.85, True),
+                                            (1 << 19, 1.0, False), (1 << 19, 0.99, True)])
+def test_entry_buffers(n, damping, kept):
     """Which sums a call takes shows in what stays with the graph: the entry
-    buffers of the exact sums, 8 bytes an entry."""
-    g = gg.kronecker(14, 16, seed=3, device="cuda")
+    buffers of the exact sums, 8 bytes an entry.  (A star's scores go down to
+    1 / (n (n - 1)).)"""
+    lg.lib().lg_trim()
+    g = gg.canonical_csr(n, torch.zeros(n - 1, dtype=torch.int64, device="cuda"), torch.arange(1, n, device="cuda"))
     h = lg.encode(g.row_offsets, g.col, g.n, relabel=True)
     before = h.info()["device_bytes"]
     lg.pagerank(h, damping, 20)
