@@ -17,7 +17,7 @@ namespace lg {
 struct DecodeMarks {
     uint32_t bad;            // a requested vertex >= n
     uint32_t n_mid, n_long;  // lists left for the block sorts
-    uint32_t n_chunked;      // Varint lists decoded by chunks
+    uint32_t n_chunked;      // Varint lists decoded by chunks, gap lists by segments
 };
 uint64_t decode_head_bytes(uint64_t k) { return k * 8 + sizeof(DecodeMarks); }
 
@@ -208,8 +208,71 @@ __global__ __launch_bounds__(1024) void dec_varint_chunks_kernel(
     }
 }
 
-// kSorted: emit ((i << 32) | original ID) keys for the segmented sort
+// Entries [j0, j1) of a gap list to the output from entry o + j0: an element is
+// the first element plus the differences up to it; 64 at a time, a wave prefix
+// sum plus the running total of the steps before (lanes past the end read the
+// first element and drop it).  carry: the entry before j0.
 template <class Acc, bool kSorted>
+__device__ __forceinline__ void dec_gap_range(const Acc &acc, uint32_t n, const GapInfo &gi, uint64_t j0, uint64_t j1,
+                                              uint32_t carry, uint64_t i, uint64_t o,
+                                              const uint32_t *__restrict__ perm, uint32_t *__restrict__ out_ids,
+                                              uint64_t *__restrict__ keys) {
+    const uint32_t lane = lane_id();
+    for (; j0 < j1; j0 += kWave) {
+        const uint64_t j = j0 + lane;
+        const bool valid = j < j1;
+        const uint64_t jj = valid ? j : 0;
+        const uint32_t x = acc.get(Acc::entry_bit(gi, jj), jj ? gi.g : gi.w);
+        const uint32_t val = wave_incl_scan(valid ? x : 0u) + carry;
+        carry = __shfl(val, kWave - 1, kWave);
+        if (valid) {
+            // a stored label is < n; the clamp keeps the lookup in bounds
+            // whatever the stream holds
+            const uint32_t u = perm ? perm[val < n ? val : n - 1] : val;
+            if (kSorted) keys[o + j] = (i << 32) | u;
+            else out_ids[o + j] = u;
+        }
+    }
+}
+
+// Gap lists above the split of the segment tables (built with the encoding; the
+// entry before every segment is stored): the workgroups share the lists, several
+// a list when there are fewer, a wave a segment.  (One wave walked a hub's list:
+// 1.5 M entries took 8 ms of a PageRank build.)
+constexpr uint32_t kDecGapThreads = 256;
+// ... and above m / 2^8: a wave takes 5.3 ns an entry, the chip 0.06 ns, so a list
+// is the kernel's tail from m / 90 on (and was left to the waves to m / 2^8, since
+// the test and the hand-over cost 5 to 8 % of kron21-d4 where every list over the
+// tables' split was taken out)
+constexpr uint32_t kDecGapShare = 8;
+template <class Acc, bool kSorted>
+__global__ __launch_bounds__(kDecGapThreads) void dec_gap_segs_kernel(
+    Acc acc, uint32_t n, const uint32_t *__restrict__ labels, const uint64_t *__restrict__ out_off,
+    const uint32_t *__restrict__ perm, uint32_t *__restrict__ out_ids, uint64_t *__restrict__ keys,
+    const uint32_t *__restrict__ more, const DecodeMarks *__restrict__ marks, const uint32_t *__restrict__ heavy,
+    uint32_t n_heavy, const uint64_t *__restrict__ hstart, const uint32_t *__restrict__ hdeg,
+    const uint32_t *__restrict__ hw, const uint32_t *__restrict__ hg, const uint64_t *__restrict__ seg_off,
+    const uint32_t *__restrict__ seg_base, uint32_t seg_size) {
+    constexpr uint32_t kWaves = kDecGapThreads / kWave;
+    const uint32_t lists = marks->n_chunked, wv = threadIdx.x / kWave;
+    if (!lists) return;
+    const uint32_t per = lists < gridDim.x ? gridDim.x / lists : 1, groups = gridDim.x / per;
+    if (blockIdx.x >= groups * per) return;
+    for (uint32_t l = blockIdx.x / per; l < lists; l += groups) {
+        const uint32_t i = more[l], h = heavy_index(heavy, n_heavy, labels[i]);
+        const GapInfo gi{hstart[h], hdeg[h], hw[h], hg[h]};
+        const uint64_t s0 = seg_off[h], segs = seg_off[h + 1] - s0;
+        for (uint64_t k = (uint64_t)(blockIdx.x % per) * kWaves + wv; k < segs; k += (uint64_t)per * kWaves) {
+            const uint64_t j0 = k * seg_size, j1 = j0 + seg_size < gi.deg ? j0 + seg_size : gi.deg;
+            dec_gap_range<Acc, kSorted>(acc, n, gi, j0, j1, seg_base[s0 + k], i, out_off[i], perm, out_ids, keys);
+        }
+    }
+}
+
+// kSorted: emit ((i << 32) | original ID) keys for the segmented sort
+// kSplit: lists longer than `split` are left in `more` (gap lists test it only
+// where the graph has such a list: 5 to 8 % of the kernel on lists of 8)
+template <class Acc, bool kSorted, bool kSplit>
 __global__ void dec_lists_kernel(Acc acc, uint32_t n, const uint32_t *__restrict__ labels, uint32_t k,
                                  const uint64_t *__restrict__ out_off, const uint32_t *__restrict__ perm,
                                  uint32_t *__restrict__ out_ids, uint64_t *__restrict__ keys, uint64_t split,
@@ -218,28 +281,15 @@ __global__ void dec_lists_kernel(Acc acc, uint32_t n, const uint32_t *__restrict
     const uint64_t wave = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave;
     const uint64_t nwaves = ((uint64_t)gridDim.x * blockDim.x) / kWave;
     if constexpr (IsGapAcc<Acc>::value) {
-        // gap lists: element j is the first element plus the differences
-        // 1..j; 64 at a time, a wave prefix sum plus the running total of the
-        // steps before (lanes past the end read the first element and drop it)
+        // gap lists of up to `split` entries; longer ones are left in `more`
         for (uint64_t i = wave; i < k; i += nwaves) {
             const GapInfo gi = acc.info(labels[i]);
             const uint64_t o = out_off[i];
-            uint32_t carry = 0;
-            for (uint64_t j0 = 0; j0 < gi.deg; j0 += kWave) {
-                const uint64_t j = j0 + lane;
-                const bool valid = j < gi.deg;
-                const uint64_t jj = valid ? j : 0;
-                const uint32_t x = acc.get(Acc::entry_bit(gi, jj), jj ? gi.g : gi.w);
-                const uint32_t val = wave_incl_scan(valid ? x : 0u) + carry;
-                carry = __shfl(val, kWave - 1, kWave);
-                if (valid) {
-                    // a stored label is < n; the clamp keeps the lookup in
-                    // bounds whatever the stream holds
-                    const uint32_t u = perm ? perm[val < n ? val : n - 1] : val;
-                    if (kSorted) keys[o + j] = (i << 32) | u;
-                    else out_ids[o + j] = u;
-                }
+            if (kSplit && gi.deg > split) {
+                if (lane == 0) more[atomicAdd(&marks->n_chunked, 1u)] = (uint32_t)i;
+                continue;
             }
+            dec_gap_range<Acc, kSorted>(acc, n, gi, 0, gi.deg, 0u, i, o, perm, out_ids, keys);
         }
     } else if constexpr (IsVarintAcc<Acc>::value) {
         // Varint lists of up to `split` bytes; longer ones are left in `more`
@@ -578,9 +628,25 @@ static lg_status dec_lists(const lg_graph *g, Acc acc, const uint32_t *labels, u
                            const uint64_t *out_off, const uint32_t *perm, uint32_t *out_ids, uint64_t *keys,
                            uint32_t *more, DecodeMarks *marks, hipStream_t stream) {
     if constexpr (IsGapAcc<Acc>::value || IsVarintAcc<Acc>::value) {
-        LG_LAUNCH((dec_lists_kernel<Acc, kSorted>), grid_for((uint64_t)k * kWave, 256, 1u << 16), 256, 0, stream,
-                  acc, g->n, labels, k, out_off, perm, out_ids, keys, g->n_vseg ? (uint64_t)g->vseg_split : ~0ull,
-                  more, marks);
+        const uint32_t grid = grid_for((uint64_t)k * kWave, 256, 1u << 16);
+        if constexpr (IsGapAcc<Acc>::value) {
+            // a list that one wave walks longer than the chip takes for the rest
+            const uint64_t split = std::max<uint64_t>(g->pr_split, g->m >> kDecGapShare);
+            if (g->segs_built && g->n_seg && g->max_degree > split) {
+                LG_LAUNCH((dec_lists_kernel<Acc, kSorted, true>), grid, 256, 0, stream, acc, g->n, labels, k,
+                          out_off, perm, out_ids, keys, split, more, marks);
+                LG_CHECK_LAUNCH();
+                LG_LAUNCH((dec_gap_segs_kernel<Acc, kSorted>), 2048, kDecGapThreads, 0, stream, acc, g->n, labels,
+                          out_off, perm, out_ids, keys, (const uint32_t *)more, (const DecodeMarks *)marks,
+                          g->heavy.as<uint32_t>(), g->n_heavy, g->hstart.as<uint64_t>(), g->hdeg.as<uint32_t>(),
+                          g->hw.as<uint32_t>(), g->hg.as<uint32_t>(), g->seg_off.as<uint64_t>(),
+                          g->seg_base.as<uint32_t>(), g->seg_size);
+            } else
+                LG_LAUNCH((dec_lists_kernel<Acc, kSorted, false>), grid, 256, 0, stream, acc, g->n, labels, k,
+                          out_off, perm, out_ids, keys, ~0ull, more, marks);
+        } else
+            LG_LAUNCH((dec_lists_kernel<Acc, kSorted, true>), grid, 256, 0, stream, acc, g->n, labels, k, out_off,
+                      perm, out_ids, keys, g->n_vseg ? (uint64_t)g->vseg_split : ~0ull, more, marks);
         if constexpr (IsVarintAcc<Acc>::value) {
             LG_CHECK_LAUNCH();
             if (g->n_vseg)

@@ -1,0 +1,72 @@
+"""Gap lists above 4,096 entries (and above m / 2^8): the decode takes the segments
+of the pull's tables side by side.  List lengths at the edges of a
+segment, one list and many, repeated requests, every order, the
+allocation-free entry point, and PageRank by blocking over hubs that it decodes
+so.  The lists are whole numbers: equal before and after, and to the input."""
+
+import numpy as np
+import pytest
+import torch
+
+import oracle as orc
+from paper_2010_15879_amd import graphgen as gg
+from paper_2010_15879_amd import lg
+
+pytestmark = pytest.mark.gpu
+
+SIZES = [4095, 4096, 4097, 8191, 8192, 8193, 12289, 20000, 100, 1]
+
+
+def _hubs(n, sizes, seed):
+    rng = np.random.default_rng(seed)
+    h = len(sizes)
+    src = np.concatenate([np.full(d, i) for i, d in enumerate(sizes)] + [rng.integers(h, n, n // 8)])
+    dst = np.concatenate([rng.choice(np.arange(h, n), d, replace=False) for d in sizes] + [rng.integers(h, n, n // 8)])
+    return gg.canonical_csr(n, torch.from_numpy(src), torch.from_numpy(dst))
+
+
+@pytest.mark.parametrize("enc", [dict(offsets="packed"), dict(offsets="ef", relabel=True),
+                                 dict(offsets="plain-bv", relabel="greedy")], ids=["packed", "ef-dm", "bv-greedy"])
+@pytest.mark.parametrize("sizes", [SIZES, [30000], [4500] * 40 + [9000] * 5], ids=["edges", "one", "many"])
+def test_decode(sizes, enc):
+    g = _hubs(40000, sizes, 1)
+    off, col = g.numpy()
+    h = lg.encode(g.row_offsets.cuda(), g.col.cuda(), g.n, ids="local-gap", **enc)
+    rng = np.random.default_rng(2)
+    requests = [np.arange(len(sizes)), rng.permutation(np.repeat(np.arange(len(sizes)), 7)), np.arange(g.n),
+                rng.integers(0, g.n, 1025), np.array([0])]
+    before = {}
+    for turn in range(2):
+        for r, vs in enumerate(requests):
+            t = torch.from_numpy(vs.astype(np.int32)).cuda()
+            for flags in ("sorted", "original", "raw"):
+                o, ids = lg.decode_neighbors(h, t, flags)
+                if flags == "sorted":
+                    assert np.array_equal(ids.cpu().numpy(), np.concatenate([col[off[v]:off[v + 1]] for v in vs]))
+                    if ids.numel() <= lg.LG_NOALLOC_MAX_SORTED_IDS:
+                        o2, ids2 = torch.empty_like(o), torch.empty_like(ids)
+                        assert lg.decode_neighbors_noalloc(h, t, o2, ids2, flags) == lg.LG_OK
+                        assert torch.equal(o, o2) and torch.equal(ids, ids2)
+                if turn:
+                    assert torch.equal(o, before[r, flags][0]) and torch.equal(ids, before[r, flags][1]), (r, flags)
+                before[r, flags] = (o, ids)
+        if turn == 0:
+            lg.pagerank(h, 0.85, 2)
+            assert h.info()["n_segments"] > 0
+    h.free()
+
+
+@pytest.mark.parametrize("relabel", [False, True])
+def test_ranks(relabel):
+    g = _hubs(200000, [120000, 20000, 16385, 16384, 5000], 3)
+    off, col = g.numpy()
+    off, col = off.astype(np.uint64), col.view(np.uint32)
+    h = lg.encode(g.row_offsets.cuda(), g.col.cuda(), g.n, ids="local-gap", offsets="ef", relabel=relabel)
+    for t in (6, 20):
+        pr = lg.pagerank(h, 0.85, t).cpu().numpy().astype(np.float64)
+        want = np.asarray(orc.pagerank_par(off, col, 0.85, t), dtype=np.float64)
+        deg = np.diff(off.astype(np.int64))
+        # exact sums: four roundings of 2^-24 an iteration, and the fixed-point unit an entry
+        assert (np.abs(pr - want) <= (4 * t + 2) * 2.0 ** -24 * want + t * (deg + 1) * 2.0 ** -61).all(), t
+    assert h.info()["n_segments"] > 0
+    h.free()
