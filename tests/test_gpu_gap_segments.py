@@ -20,8 +20,9 @@ SIZES = [4095, 4096, 4097, 8191, 8192, 8193, 12289, 20000, 100, 1]
 def _hubs(n, sizes, seed):
     rng = np.random.default_rng(seed)
     h = len(sizes)
-    src = np.concatenate([np.full(d, i) for i, d in enumerate(sizes)] + [rng.integers(h, n, n // 8)])
-    dst = np.concatenate([rng.choice(np.arange(h, n), d, replace=False) for d in sizes] + [rng.integers(h, n, n // 8)])
+    few = min(n // 8, 1 << 18)
+    src = np.concatenate([np.full(d, i) for i, d in enumerate(sizes)] + [rng.integers(h, n, few)])
+    dst = np.concatenate([rng.choice(np.arange(h, n), d, replace=False) for d in sizes] + [rng.integers(h, n, few)])
     return gg.canonical_csr(n, torch.from_numpy(src), torch.from_numpy(dst))
 
 
@@ -69,4 +70,16 @@ def test_ranks(relabel):
         # exact sums: four roundings of 2^-24 an iteration, and the fixed-point unit an entry
         assert (np.abs(pr - want) <= (4 * t + 2) * 2.0 ** -24 * want + t * (deg + 1) * 2.0 ** -61).all(), t
     assert h.info()["n_segments"] > 0
+    h.free()
+
+
+def test_decode_keys():
+    """Relabeled, more than 2^24 vertices: the lists go out as the sort's keys."""
+    sizes = [30000, 4097, 8193, 4096, 9000]
+    g = _hubs((1 << 24) + 1000, sizes, 4)
+    off, col = g.numpy()
+    h = lg.encode(g.row_offsets.cuda(), g.col.cuda(), g.n, ids="local-gap", offsets="ef", relabel=True)
+    vs = np.concatenate([np.repeat(np.arange(len(sizes)), 3), np.random.default_rng(5).integers(0, g.n, 3000)])
+    o, ids = lg.decode_neighbors(h, torch.from_numpy(vs.astype(np.int32)).cuda(), "sorted")
+    assert np.array_equal(ids.cpu().numpy(), np.concatenate([col[off[v]:off[v + 1]] for v in vs]))
     h.free()
