@@ -301,9 +301,9 @@ lg_status lg_sssp(const lg_graph *g, uint32_t root, uint32_t delta, uint64_t *di
  *   iters    number of iterations (exactly; no convergence test)
  *   scores   dev, float[n], indexed by original ID
  *
- * Calls of more than a few iterations (on large unrelabeled graphs, of any)
- * build tables for propagation blocking at a graph's first one,
- * kept until lg_free: about 8.3 bytes per stored entry and 20 per vertex, and
+ * Calls of more than a few iterations (of any on plain graphs, global IDs and
+ * large unrelabeled local IDs) build tables for propagation blocking at a
+ * graph's first one, kept until lg_free: about 8.3 bytes per stored entry and 20 per vertex, and
  * during the build up to 8 more per entry (4 for lists that are not one stream
  * of fixed-width entries, up to 4 for counts).  Where they do not fit, this
  * and later calls on the graph run without them, more slowly.
