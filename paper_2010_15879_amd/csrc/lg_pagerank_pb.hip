@@ -819,14 +819,13 @@ static lg_status pb_build_tiles(lg_graph *g, PbEntries<kPacked> ent, const uint6
     W.n_sum = (uint32_t)items.size() - W.n_send;
     W.n_multi = (uint32_t)multi.size();
     LG_TRY(W.items.scratch(items.size() * sizeof(uint4) + multi.size() * 4 + 4, s));
-    LG_CHECK_HIP(hipMemcpyAsync(W.items.p, items.data(), items.size() * sizeof(uint4), hipMemcpyHostToDevice, s));
-    if (W.n_multi) {
-        LG_CHECK_HIP(hipMemcpyAsync(W.items.as<uint4>() + items.size(), multi.data(), multi.size() * 4,
-                                    hipMemcpyHostToDevice, s));
-        LG_TRY(W.gsum.scratch(((uint64_t)W.n_multi << W.fs) * 8, s));
-    }
+    if (W.n_multi) LG_TRY(W.gsum.scratch(((uint64_t)W.n_multi << W.fs) * 8, s));
     LG_TRY(W.ca.alloc((uint64_t)n * 4));
     LG_TRY(W.cb.alloc((uint64_t)n * 4));
+    LG_CHECK_HIP(hipMemcpyAsync(W.items.p, items.data(), items.size() * sizeof(uint4), hipMemcpyHostToDevice, s));
+    if (W.n_multi)
+        LG_CHECK_HIP(hipMemcpyAsync(W.items.as<uint4>() + items.size(), multi.data(), multi.size() * 4,
+                                    hipMemcpyHostToDevice, s));
     LG_CHECK_HIP(hipStreamSynchronize(s));  // the host's items are copied
     W.built = true;
     return LG_OK;
