@@ -809,10 +809,10 @@ __global__ void bu_pending_kernel(Acc acc, uint32_t threshold, uint64_t np, cons
 // all reservations meet in one counter, some 18 ns each, which was this
 // kernel's time when every wave made its own (uniform graph, 2^24 vertices,
 // 4,096 reservations: 77 us a launch; 256 of them: 33).  A wave writes its 64
-// words' entries in order, 64 consecutive queue slots per step: slot j's word is the one whose
-// prefix count range holds j (a binary search of the wave's inclusive
-// counts), its bit the (j - count before)-th one of that word.  One lane
-// writing its word's ones one after another scattered every store.
+// words' entries in order, 64 consecutive queue slots per step: slot j's word
+// is the one whose prefix count range holds j (a binary search of the wave's
+// inclusive counts), its bit the (j - count before)-th one of that word.  One
+// lane writing its word's ones one after another scattered every store.
 __global__ __launch_bounds__(1024) void bitmap_to_queue_kernel(uint64_t words, const uint64_t *__restrict__ bits,
                                                                uint32_t *__restrict__ queue,
                                                                unsigned long long *__restrict__ tail) {

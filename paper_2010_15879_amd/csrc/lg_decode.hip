@@ -731,7 +731,8 @@ lg_status decode_run(lg_graph *g, DecodeWork &w, const uint32_t *vertices, uint3
             // it sorts, whichever sort that is
             if (sorted && w.keys.borrowed) LG_TRY(w.keys.ensure(total * 8));
             else if (has_long) LG_TRY(w.keys.ensure(tmp.keys));
-            LG_TRY((dec_lists<Acc, false>(g, acc, labels, k, total, out_off, perm, out_ids, nullptr, deg, marks, stream)));
+            LG_TRY((dec_lists<Acc, false>(g, acc, labels, k, total, out_off, perm, out_ids, nullptr, deg, marks,
+                                          stream)));
             if (!sorted) return LG_OK;
             LG_LAUNCH(dec_sort_wave_kernel, grid_for(k, kWave, 1u << 14), 256, 0, stream, k,
                       (const uint64_t *)out_off, out_ids, deg, marks);
@@ -756,8 +757,8 @@ lg_status decode_run(lg_graph *g, DecodeWork &w, const uint32_t *vertices, uint3
         LG_TRY(w.keys2.ensure(tmp.keys2));
         LG_TRY(w.vals.ensure(tmp.vals));
         LG_TRY(w.vals2.ensure(tmp.vals2));
-        LG_TRY((dec_lists<Acc, true>(g, acc, labels, k, total, out_off, perm, out_ids, w.keys.as<uint64_t>(), deg, marks,
-                                      stream)));
+        LG_TRY((dec_lists<Acc, true>(g, acc, labels, k, total, out_off, perm, out_ids, w.keys.as<uint64_t>(), deg,
+                                     marks, stream)));
         const uint32_t bits = 32 + bitlen_u64(k - 1);
         LG_TRY(radix_sort_pairs64(w.keys.as<uint64_t>(), w.vals.as<uint32_t>(), w.keys2.as<uint64_t>(),
                                   w.vals2.as<uint32_t>(), total, bits, w.sort_tmp, stream));

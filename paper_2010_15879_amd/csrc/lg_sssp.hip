@@ -298,7 +298,8 @@ __device__ __forceinline__ uint64_t collect_scan(uint64_t x, uint64_t *s_wave, u
 
 __global__ __launch_bounds__(kCollectThreads) void sssp_write_kernel(
     const uint64_t *__restrict__ vstart, const uint32_t *__restrict__ vdeg, uint64_t words, uint32_t tile,
-    uint64_t delta, uint64_t max_steps, const uint64_t *__restrict__ dist, const uint64_t *__restrict__ tmask, const uint64_t *__restrict__ wdeg, const SsspPart *__restrict__ parts,
+    uint64_t delta, uint64_t max_steps, const uint64_t *__restrict__ dist, const uint64_t *__restrict__ tmask,
+    const uint64_t *__restrict__ wdeg, const SsspPart *__restrict__ parts,
     uint32_t *__restrict__ qv, uint64_t *__restrict__ qstart, uint64_t *__restrict__ qdist,
     uint64_t *__restrict__ qoff, SsspState *__restrict__ state) {
     __shared__ uint64_t s_wave[kCollectWaves];
